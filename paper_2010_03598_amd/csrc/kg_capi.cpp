@@ -175,6 +175,8 @@ kg_status carve_d(void* ws, size_t ws_bytes, uint64_t D, const kg_krylov* k, int
     o->st = reinterpret_cast<KState*>(q);
     q += align_up(sizeof(KState), 256);
     o->partials = reinterpret_cast<cplx_d*>(q);
+    o->area = q;
+    o->area_bytes = (size_t)(p + 2 * slot_bytes_d(D, k, prec) - q);
     q += align_up(sizeof(cplx_d) * kPartialRows * kMaxScal, 256);
     o->basis = q;
     q += align_up(vbytes(D, prec) * (size_t)(k->m - 1), 256);
@@ -261,17 +263,113 @@ KrylovCall krylov_call(const SweepArgs& a, int j, double t, const void* in, void
   return c;
 }
 
-kg_status forward_sweep(const SweepArgs& a, const States& S, double* F_dev, double* beta_dev) {
-  for (int j = 1; j <= a.N; ++j) {
-    const KrylovCall c = krylov_call(a, j, a.dt, S.at0(j - 1), S.at(j));
-    KG_HIP(launch_krylov(c, a.ws, a.stream), "forward sweep");
-  }
+// Whether the sweep's Krylov calls take the one-block form.
+bool short_vectors(const SweepArgs& a) { return sweep_applies(krylov_call(a, 1, a.dt, a.psi0, nullptr)); }
+
+// Short vectors: a chain of n calls from slice j0 in steps of dj, one block.
+// Outputs go to the state buffer, or to `out` one after the other.
+SweepJob chain_job(const SweepArgs& a, const States& S, int j0, int dj, int n, double t,
+                   const void* in, void* out) {
+  SweepJob b = sweep_job(krylov_call(a, 1, t, in, out));
+  b.u = a.u_dev;
+  b.n = n;
+  b.j0 = j0;
+  b.dj = dj;
+  b.vb = a.vb;
+  b.states = out ? 0 : 1;
+  if (!out) b.out = S.base;
+  b.c = S.c;
+  b.nseg = S.nseg;
+  b.nbuf = S.nbuf;
+  return b;
+}
+
+kg_status launch_overlap_of(const SweepArgs& a, const States& S, double* F_dev, double* beta_dev) {
   Profiler* prof = profiler_for_launch();
   if (prof) profiler_start(prof, a.stream);
   KG_HIP(launch_overlap(a.prec, a.geo.D, a.target, S.at(a.N), a.ws, F_dev, beta_dev, a.stream),
          "overlap");
   if (prof) profiler_stop(prof, a.stream, kProfOverlap, 2.0 * a.vb);
   return KG_OK;
+}
+
+// Costates and brackets of short vectors.  The costates of a segment go to the
+// workspace's free area (as many at a time as half of it holds; the halves
+// take turns, so the last costate stays for what follows) and one launch
+// takes their brackets; the costates need nothing of the forward sweep, so `with`
+// (the forward sweep, or nothing) runs beside the first of them, as segment
+// q - 1's recomputation does beside segment q's costates.  `after` is called
+// once the launch that ran `with` is enqueued (the overlap that the brackets
+// wait for).
+template <typename After>
+kg_status short_backward(const SweepArgs& a, const States& S, const double* beta_dev, double* grad_dev,
+                         bool centred, int col, int ncols, const SweepJob* with, After after) {
+  const size_t cap = a.ws.area_bytes / 2 / a.vb;
+  const void* lam = a.target;
+  bool first = true;
+  int half = 0;
+  for (int q = S.nseg - 1; q >= 0; --q) {
+    const int cs = (S.c == 0) ? 0 : q * S.c;
+    const int len = (S.c == 0) ? a.N : std::min(a.N - cs, S.c);
+    const int rq = q - 1;
+    const bool recompute = S.c > 1 && rq >= 0 && rq <= S.nseg - 3;
+    // costates lambda_{j-1} for j = cs + len .. jend
+    const int jend = (cs == 0 && !centred) ? 2 : cs + 1;
+    int j = cs + len;
+    // brackets of slices jb, jb - 1, ..., jlow; the one at cs belongs to the next segment
+    int jb = j;
+    const int jlow = (cs == 0 && centred) ? 0 : cs + 1;
+    const void* lam0 = lam;
+    for (bool top = true; top || j >= jend; top = false) {
+      const int n = std::max(0, (int)std::min<size_t>(cap, (size_t)(j - jend + 1)));
+      char* lams = a.ws.area + (size_t)half * cap * a.vb;
+      SweepJob jobs[3];
+      int nj = 0;
+      if (n > 0) jobs[nj++] = chain_job(a, S, j, -1, n, -a.dt, lam, lams);
+      if (top && recompute)
+        jobs[nj++] = chain_job(a, S, rq * S.c + 1, 1, S.c - 1, a.dt, rq == 0 ? a.psi0 : S.ckpt(rq), nullptr);
+      if (first && with) jobs[nj++] = *with;
+      if (nj) KG_HIP(launch_sweeps(a.prec, jobs, nj, a.stream), "costate sweep");
+      if (first) KG_CHECK(after());
+      first = false;
+      BracketRun r;
+      r.states = chain_job(a, S, 1, 1, 1, a.dt, a.psi0, nullptr);
+      r.psi0 = a.psi0;
+      r.lam0 = lam0;
+      r.lams = lams;
+      r.jhi = jb;
+      r.pad_ = 0;
+      r.cr = a.dt / ncols;
+      r.grad = grad_dev;
+      r.g0 = &a.ws.st->g0;
+      // the last costate of a segment above the first serves the next segment's top slice
+      const int nb = std::min(n + (lam0 ? 1 : 0), jb - jlow + 1);
+      KG_HIP(launch_brackets(a.prec, r, nb, beta_dev, col > 0, a.stream), "gradient brackets");
+      jb -= nb;
+      lam0 = nullptr;
+      if (n > 0) {
+        lam = lams + (size_t)(n - 1) * a.vb;
+        half ^= 1;
+      }
+      j -= n;
+    }
+  }
+  if (centred && col == ncols - 1)
+    KG_HIP(launch_centre(grad_dev, a.N, &a.ws.st->g0, a.stream), "centred gradient");
+  return KG_OK;
+}
+
+kg_status forward_sweep(const SweepArgs& a, const States& S, double* F_dev, double* beta_dev) {
+  if (short_vectors(a)) {
+    const SweepJob b = chain_job(a, S, 1, 1, a.N, a.dt, a.psi0, nullptr);
+    KG_HIP(launch_sweeps(a.prec, &b, 1, a.stream), "forward sweep");
+    return launch_overlap_of(a, S, F_dev, beta_dev);
+  }
+  for (int j = 1; j <= a.N; ++j) {
+    const KrylovCall c = krylov_call(a, j, a.dt, S.at0(j - 1), S.at(j));
+    KG_HIP(launch_krylov(c, a.ws, a.stream), "forward sweep");
+  }
+  return launch_overlap_of(a, S, F_dev, beta_dev);
 }
 
 // The backward sweep runs the segment recomputation on a second stream beside
@@ -338,6 +436,8 @@ struct Quadrature {
 kg_status backward_sweep(const SweepArgs& a, const States& S, const double* beta_dev,
                          double* grad_dev, bool centred = false, const Quadrature* Q = nullptr,
                          bool first_order = false, int col = 0, int ncols = 1) {
+  if (!(Q && Q->n > 0) && !first_order && short_vectors(a))
+    return short_backward(a, S, beta_dev, grad_dev, centred, col, ncols, nullptr, [] { return KG_OK; });
   const HvArgs hc = make_hv(a.h, nullptr, 0.0);
   const double dt_b = a.dt / ncols;
   const bool acc = col > 0;
@@ -666,7 +766,7 @@ kg_status expv_impl(const kg_xxz* h, const Space& sp, double u, double t, const 
   c.v_in = v_in;
   c.v_out = v_out;
   c.m_eff_out = m_eff_dev;
-  KG_HIP(launch_init(W.st, s), "krylov_expv init");
+  if (!sweep_applies(c)) KG_HIP(launch_init(W.st, s), "krylov_expv init");
   KG_HIP(launch_krylov(c, W, s), "krylov_expv");
   return ok();
 }
@@ -681,8 +781,10 @@ kg_status forward_impl(const kg_xxz* h, const Space& sp, const double* u_dev, in
   SweepArgs a{h, u_dev, N, dt, k, prec, psi0, target, sp.geo, W, W1, (hipStream_t)stream,
               sp.pe, vbytes(sp.geo.D, prec)};
   const States S = make_states(N, ckpt_every, states, a.vb, psi0);
-  KG_HIP(launch_init(W.st, a.stream), name);
-  KG_HIP(launch_init(W1.st, a.stream), name);
+  if (!short_vectors(a)) {
+    KG_HIP(launch_init(W.st, a.stream), name);
+    KG_HIP(launch_init(W1.st, a.stream), name);
+  }
   KG_CHECK(forward_sweep(a, S, F_dev, beta_dev));
   return ok();
 }
@@ -700,6 +802,12 @@ kg_status gradient_core(const kg_xxz* h, const Space& sp, const double* u_dev, i
   SweepArgs a{h, u_dev, N, dt, k, prec, psi0, target, sp.geo, W, W1, (hipStream_t)stream,
               sp.pe, vbytes(sp.geo.D, prec)};
   const States S = make_states(N, ckpt_every, states, a.vb, psi0);
+  if (!Q && !first_order && short_vectors(a)) {
+    const SweepJob fwd = chain_job(a, S, 1, 1, N, dt, psi0, nullptr);
+    KG_CHECK(short_backward(a, S, beta_dev, grad_dev, centred, 0, 1, states_valid ? nullptr : &fwd,
+                            [&] { return states_valid ? KG_OK : launch_overlap_of(a, S, F_dev, beta_dev); }));
+    return ok();
+  }
   KG_HIP(launch_init(W.st, a.stream), name);
   KG_HIP(launch_init(W1.st, a.stream), name);
   if (!states_valid) KG_CHECK(forward_sweep(a, S, F_dev, beta_dev));
@@ -815,7 +923,7 @@ kg_status krylov_expv_static(const kg_xxz* h, double u, double t, const kg_krylo
   c.v_in = v_in;
   c.v_out = v_out;
   c.m_eff_out = m_eff_dev;
-  KG_HIP(launch_init(W.st, s), "krylov_expv_static init");
+  if (!sweep_applies(c)) KG_HIP(launch_init(W.st, s), "krylov_expv_static init");
   KG_HIP(launch_krylov(c, W, s), "krylov_expv_static");
   return ok();
 }
@@ -1255,10 +1363,21 @@ kg_status columns_core(const kg_xxz* h, const Space& sp, const double* u_dev, in
   };
   KG_HIP(launch_init(W.st, s), "grape_gradient_columns");
   KG_HIP(launch_init(W1.st, s), "grape_gradient_columns");
-  for (int c = 0; c < n_cols; c += 2) {
+  const bool short_v = short_vectors(col_args(0, W, W1));
+  if (short_v) {
+    // every column's forward sweep is a block of its own
+    std::vector<SweepJob> jobs;
+    for (int c = 0; c < n_cols; ++c) {
+      const SweepArgs a = col_args(c, W, W1);
+      jobs.push_back(chain_job(a, col_states(c), 1, 1, N, dt, a.psi0, nullptr));
+    }
+    KG_HIP(launch_sweeps(prec, jobs.data(), n_cols, s), "column forward sweeps");
+  }
+  for (int c = 0; c < n_cols; c += short_v ? 1 : 2) {
     const SweepArgs a0 = col_args(c, W, W1);
     const States S0 = col_states(c);
-    if (c + 1 < n_cols) {
+    if (short_v) {
+    } else if (c + 1 < n_cols) {
       const SweepArgs a1 = col_args(c + 1, W1, W);
       const States S1 = col_states(c + 1);
       for (int j = 1; j <= N; ++j) {

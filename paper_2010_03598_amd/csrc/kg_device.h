@@ -30,6 +30,12 @@ struct VT<double> {
 // ROW_MASK receive +0.0.
 template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ double dpp_f64(double v) {
+  if constexpr (ROW_MASK == 0xF) {
+    // every row is written; a lane without a source reads 0 (bound control)
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+  }
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false);
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xF, false);
   return __hiloint2double(hi, lo);
@@ -438,45 +444,62 @@ __device__ void block_totals(const cplx_d* wacc, int ns, cplx_d* tot, int c0 = 0
   __syncthreads();
 }
 
+// Terms p in [FROM, TO] of the Taylor series of exp(-iT): t_p = (-i/p) T t_{p-1},
+// added to the sum, one tridiagonal row per lane.  Neighbours by DPP wavefront
+// shifts: lane i reads lane i-1 (wave_shr:1) and lane i+1 (wave_shl:1); the
+// lanes at the ends read 0, where the matching off-diagonal entry is 0 anyway.
+template <int FROM, int TO>
+__device__ __forceinline__ void tri_terms(double a, double lo, double hi, double& tr, double& ti,
+                                          double& sr, double& si) {
+  if constexpr (FROM <= TO) {
+    const double zr = a * tr + lo * dpp_f64<0x138>(tr) + hi * dpp_f64<0x130>(tr);
+    const double zi = a * ti + lo * dpp_f64<0x138>(ti) + hi * dpp_f64<0x130>(ti);
+    tr = (1.0 / FROM) * zi;
+    ti = (-1.0 / FROM) * zr;
+    sr += tr;
+    si += ti;
+    tri_terms<FROM + 1, TO>(a, lo, hi, tr, ti, sr, si);
+  }
+}
+
 // exp(-i t T) e_1 for the real symmetric tridiagonal T held row by row in the
 // lanes of one wavefront (lane i: diagonal a, couplings lo = T[i][i-1] and
-// hi = T[i][i+1]; rows past the dimension are zero).  Scaled Taylor series:
-// the step is split into nsub pieces with |t/nsub| ||T||_inf <= 1/2 and each
-// piece uses 16 terms (remainder below 2^-17/17! relative).
-// Beyond kMaxSubsteps pieces (|t| ||T||_inf > kMaxSubsteps / 2, or a
-// non-finite T or t) the result is NaN: the loop stays bounded whatever the
-// entries.
+// hi = T[i][i+1]; rows past the dimension are zero).  Taylor series, the
+// interval split into pieces of |t/nsub| ||T||_inf <= 2 and as many terms as
+// leave a remainder below 2^-58 relative.  A chain of dependent FP64
+// operations on one wavefront, about 90 cycles a term: pieces of at most 1/2
+// with 16 terms and a division in each took 80 terms at |t| ||T|| = 2.5, 26
+// per piece now take 52, and 14 instead of 16 at the 1/4 of a short slice.
+// Beyond |t| ||T||_inf = kMaxSubsteps / 2 (or for a non-finite T or t) the
+// result is NaN: the loop stays bounded whatever the entries.
 constexpr double kMaxSubsteps = 65536.0;
 __device__ void tri_exp_wave(double a, double lo, double hi, double t, double& cr, double& ci) {
   const int lane = threadIdx.x & 63;
   const double nrm = wave_max(fabs(a) + lo + hi);
-  const double want = ceil(fabs(t) * nrm * 2.0);
-  if (!(want <= kMaxSubsteps)) {
+  const double theta = fabs(t) * nrm;
+  if (!(ceil(theta * 2.0) <= kMaxSubsteps)) {
     cr = ci = NAN;
     return;
   }
-  const int nsub = want < 1.0 ? 1 : (int)want;
+  const int nsub = theta <= 2.0 ? 1 : (int)ceil(theta * 0.5);
   const double tau = t / (double)nsub;
+  const double x = theta / (double)nsub;
   double yr = (lane == 0) ? 1.0 : 0.0, yi = 0.0;
+  a *= tau;
+  lo *= tau;
+  hi *= tau;
+  // terms until x^p / p! < 2^-58
   for (int step = 0; step < nsub; ++step) {
-    double tr = yr, ti = yi, ar = yr, ai = yi;
-#pragma unroll 4
-    for (int p = 1; p <= 16; ++p) {
-      // neighbours by DPP wavefront shifts: lane i reads lane i-1 (wave_shr:1)
-      // and lane i+1 (wave_shl:1); the lanes at the ends read 0, where the
-      // matching off-diagonal entry is 0 anyway
-      const double dr = dpp_f64<0x138>(tr), di = dpp_f64<0x138>(ti);
-      const double ur = dpp_f64<0x130>(tr), ui = dpp_f64<0x130>(ti);
-      const double zr = a * tr + lo * dr + hi * ur;
-      const double zi = a * ti + lo * di + hi * ui;
-      const double c = tau / (double)p;
-      tr = c * zi;
-      ti = -c * zr;
-      ar += tr;
-      ai += ti;
-    }
-    yr = ar;
-    yi = ai;
+    double tr = yr, ti = yi;
+    tri_terms<1, 11>(a, lo, hi, tr, ti, yr, yi);
+    if (x <= 0.125) continue;
+    tri_terms<12, 14>(a, lo, hi, tr, ti, yr, yi);
+    if (x <= 0.25) continue;
+    tri_terms<15, 16>(a, lo, hi, tr, ti, yr, yi);
+    if (x <= 0.5) continue;
+    tri_terms<17, 20>(a, lo, hi, tr, ti, yr, yi);
+    if (x <= 1.0) continue;
+    tri_terms<21, 26>(a, lo, hi, tr, ti, yr, yi);
   }
   cr = yr;
   ci = yi;

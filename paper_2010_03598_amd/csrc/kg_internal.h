@@ -107,6 +107,8 @@ struct Workspace {         // carved from the caller's workspace
   void* lam;               // one vector (costate)
   void* node_a;            // quadrature workspaces only: psi at a node
   void* node_b;            //   and lambda at the node
+  char* area;              // slot 0: everything after the scalars, free while no
+  size_t area_bytes;       //   tiled call uses the workspace
 };
 
 size_t ws_fixed_bytes();
@@ -169,6 +171,52 @@ hipError_t launch_krylov(const KrylovCall& c, const Workspace& ws, hipStream_t s
 // Two independent calls of the same L, m, reorth and precision in the same launches.
 hipError_t launch_krylov_pair(const KrylovCall& c0, const Workspace& w0, const KrylovCall& c1,
                               const Workspace& w1, hipStream_t s);
+
+// ---- short vectors (kg_sweep.hip): one block runs a chain of Krylov calls
+constexpr uint32_t kSweepMaxD = 1024;
+constexpr int kSweepJobs = 8;      // sweeps per launch
+struct SweepJob {
+  HvArgs hv;               // u_ptr unused
+  PeArgs pe;
+  int32_t has_pe;
+  int32_t nbr;             // neighbours per row (sweep_neighbours)
+  uint32_t D;
+  int32_t m, reorth;
+  double t, tol;
+  const double* u;         // controls by slice, or nullptr: hv.u_val
+  const void* in;
+  int32_t n;               // calls
+  int32_t j0, dj;          // call q is slice j0 + q dj
+  // outputs of vb bytes: `states`: slice j's place in a state buffer (c, nseg,
+  // nbuf as in its layout), else the q-th vector from `out`
+  int32_t states;
+  char* out;
+  size_t vb;
+  int32_t c, nseg, nbuf;
+  int32_t* m_eff_out;      // nullable
+};
+int sweep_neighbours(const PeArgs* pe, int L);
+bool sweep_fits(int prec, uint32_t D, int m, int nbr);
+// Whether a Krylov call takes the one-block form, and the sweep that is that call.
+struct KrylovCall;
+bool sweep_applies(const KrylovCall& c);
+SweepJob sweep_job(const KrylovCall& c);
+hipError_t launch_sweeps(int prec, const SweepJob* jobs, int n, hipStream_t s);
+// Brackets of n slices jhi, jhi - 1, ...; psi_j comes from the state buffer
+// that `states` describes (psi0 for slice 0), lambda from lam0 (first slice,
+// nullable) and then `lams`.
+struct BracketRun {
+  SweepJob states;
+  const void* psi0;
+  const void* lam0;
+  const char* lams;
+  int32_t jhi, pad_;
+  double cr;
+  double* grad;
+  double* g0;
+};
+hipError_t launch_brackets(int prec, const BracketRun& r, int n, const double* beta, bool accumulate,
+                           hipStream_t s);
 
 hipError_t launch_overlap(int prec, uint32_t D, const void* f, const void* psi, const Workspace& ws,
                           double* F_dev, double* beta_dev, hipStream_t s);

@@ -1391,423 +1391,15 @@ hipError_t launch_pass_r(bool pass_a, const LzBatch& lb, int njobs, hipStream_t 
 
 // Advance n (1 or 2) independent Krylov calls of one shape (same L, m,
 // reorth, precision) through the same launches.
-// ---------------------------------------------------------------------- one-block Krylov call
-
-// A whole Krylov call (Algorithm 2, the small exponential of Eqs. A2-A3 and
-// the combination) by one block, for vectors whose stored basis fits in LDS:
-// D <= kFusedMaxD amplitudes and m D amplitudes of LDS at most kFusedLds
-// bytes.  At such sizes the tiled form is a chain of about 2m dependent
-// launches of one block each, bound by their latency; here the basis never
-// leaves LDS and a step costs one block reduction and three barriers.
-//
-// Thread t owns amplitudes (rows) t + kFusedBlock a.  The stored vectors
-// are u_0 = the input as given and u_{k+1} = w_{k+1} rounded to the vector
-// type, unnormalised, with their scales s_k = 1/||u_k|| kept in FP64; step k
-// forms h = H u_k (accumulated in the vector type, as the tiled H v) and
-// reduces its window dots together with ||u_k||^2, then takes s_k (or the
-// breakdown), y = s_k h, the projection coefficients c_i = s_i <u_i|y>
-// against the same y over the window (classical Gram-Schmidt: every stored
-// vector with full re-orthonormalisation, the last two without),
-// alpha_k = s_k Re<u_k|y>, and w = y - sum_i c_i s_i u_i in FP64.  The
-// breakdown test and the combination are those of the tiled passes.
-// Reductions: quad_sums_swap within a wavefront, then the wavefronts in
-// order, so every thread reads the same totals.  For the reduced basis the
-// rows' neighbour lists are staged in LDS behind the stored vectors when
-// both fit in kFusedLdsStaged bytes.
-constexpr int kFusedBlock = 512;
-constexpr int kFusedNA = 2;                                   // amplitudes per thread
-constexpr uint32_t kFusedMaxD = kFusedBlock * kFusedNA;
-constexpr size_t kFusedLds = (size_t)120 << 10;               // bytes of stored vectors
-// with the reduced basis's neighbour lists staged after them (L - 1 slots and
-// a count per row), at most this much dynamic LDS
-constexpr size_t kFusedLdsStaged = (size_t)140 << 10;
-constexpr int kFusedRed = 2 * kMaxM + 4;
-
-struct FusedJob {
-  HvArgs hv;
-  PeArgs pe;
-  int32_t has_pe;
-  int32_t stage;           // reduced basis: neighbour lists staged in LDS
-  uint32_t D;
-  int32_t m, reorth;
-  double t, tol;
-  const void* v_in;
-  void* v_out;
-  int32_t* m_eff_out;
-};
-
-struct FusedBatch {
-  FusedJob job[kMaxJobs];
-};
-
-// Row s of (H0 + u Hc) x on the full 2^L space, x in LDS (as hv_tile, one row).
-template <typename R>
-__device__ __forceinline__ void full_row(const HvArgs& a, uint32_t s, const typename VT<R>::T* x,
-                                         double u, R& yr, R& yi) {
-  using V = typename VT<R>::T;
-  const int L = a.L;
-  const uint32_t bondmask = (L >= 2) ? ((1u << (L - 1)) - 1u) : 0u;
-  const uint32_t act = (s ^ (s >> 1)) & bondmask;
-  const int n_anti = (int)__popc(act);   // __popc is unsigned
-  R d = (R)a.c_zz * (R)(L - 1 - 2 * n_anti);
-  if (a.hc_kind == 1) d += (R)u * ((R)(0.5 * a.sz_count) - (R)__popc(s & a.sz_mask));
-  const V xs = x[s];
-  yr = d * xs.x;
-  yi = d * xs.y;
-  const R hJ = (R)a.half_J;
-  for (uint32_t b = act; b; b &= b - 1u) {
-    const V q = x[s ^ (3u << __builtin_ctz(b))];
-    yr += hJ * q.x;
-    yi += hJ * q.y;
-  }
-  if (a.hc_kind == 0) {
-    const R cu = (R)(0.5 * u);
-    const V q = x[s ^ (1u << a.hc_bit)];
-    yr += cu * q.x;
-    yi += cu * q.y;
-  }
-}
-
-// The reduced basis in the one-block call: row b's diagonal (H0 + u Hc)_bb and
-// the orbits reached through its antiparallel bonds (ascending, as pe_row
-// takes them), each as a | c << 30 with the weight code c of sqrt(n_b / n_a)
-// (1: 1, 2: sqrt 2, 3: 1/sqrt 2), written to slots j of `ent` (stride D).
-// Returns the number of bonds, or -1 when a table entry is out of range.
-template <typename R>
-__device__ __forceinline__ int pe_stage_row(const HvArgs& a, const PeArgs& p, const uint32_t* sb,
-                                            double u, uint32_t b, uint32_t* ent, uint32_t D,
-                                            R& diag) {
-  const int L = p.L;
-  const uint32_t full = (L == 32) ? 0xFFFFFFFFu : ((1u << L) - 1u);
-  const uint32_t bondmask = (L >= 2) ? ((1u << (L - 1)) - 1u) : 0u;
-  const uint32_t r = p.reps[b];
-  const uint32_t rank = p.ranks[b];
-  const uint32_t zeros = ~r & full;
-  const bool nb2 = (__brev(r) >> (32 - L)) != r;
-  const int n_anti = (int)__popc((r ^ (r >> 1)) & bondmask);
-  R d = (R)a.c_zz * (R)(L - 1 - 2 * n_anti);
-  if (a.hc_kind == 1) d += (R)u * ((R)(0.5 * a.sz_count) - (R)__popc(r & a.sz_mask));
-  diag = d;
-  if (rank >= p.nsec) return -1;
-  int j = 0;
-  for (uint32_t act = (r ^ (r >> 1)) & bondmask; act; act &= act - 1u, ++j) {
-    const int q = __builtin_ctz(act);
-    const uint32_t dl = sb[q * kPeBinom + __popc(zeros & ((1u << q) - 1u))];
-    const uint32_t rk = (((r >> q) & 1u) == 0u) ? rank + dl : rank - dl;
-    const int32_t ai = (rk < p.nsec) ? p.index[rk] : -1;
-    if ((uint32_t)ai >= p.dim) return -1;
-    const uint32_t s2 = r ^ (3u << q);
-    const bool na2 = (__brev(s2) >> (32 - L)) != s2;
-    const uint32_t code = (nb2 == na2) ? 1u : (nb2 ? 2u : 3u);
-    ent[(size_t)j * D] = (uint32_t)ai | (code << 30);
-  }
-  return j;
-}
-
-// Totals of n <= kFusedRed values that every wavefront has put in wred[w][0, n):
-// tot[j] = sum over the wavefronts in order.  Barriers before and after.
-__device__ __forceinline__ void fused_totals(double (*wred)[kFusedRed], int n, double* tot) {
-  __syncthreads();
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    double v = 0.0;
-#pragma unroll
-    for (int w = 0; w < kFusedBlock / 64; ++w) v += wred[w][j];
-    tot[j] = v;
-  }
-  __syncthreads();
-}
-
-template <typename R>
-__global__ void __launch_bounds__(kFusedBlock) k_krylov_fused(FusedBatch B) {
-  using V = typename VT<R>::T;
-  const FusedJob& J = B.job[blockIdx.x];
-  extern __shared__ unsigned char smem_raw[];
-  V* ub = reinterpret_cast<V*>(smem_raw);   // stored vectors, [m][D]
-  __shared__ double wred[kFusedBlock / 64][kFusedRed];
-  __shared__ double tot[kFusedRed];
-  __shared__ double sc[kMaxM + 1], al[kMaxM], off[kMaxM + 1];
-  __shared__ cplx_d dco[kMaxM];
-  __shared__ uint32_t sb[kPeBinom * kPeBinom];
-
-  const int tid = threadIdx.x;
-  const uint32_t lane = tid & 63u;
-  const uint32_t wv = uniform_u32(tid >> 6);
-  const uint32_t D = J.D;
-  const int m = J.m;
-  const V* __restrict__ vin = reinterpret_cast<const V*>(J.v_in);
-  V* __restrict__ vout = reinterpret_cast<V*>(J.v_out);
-  const double u = control_value(J.hv);
-  // reduced basis: the binomials, then (when staged) every row's neighbour list
-  // and diagonal, so that the steps read nothing but LDS
-  uint32_t* stg = reinterpret_cast<uint32_t*>(smem_raw + (size_t)m * D * sizeof(V));
-  int32_t* scount = reinterpret_cast<int32_t*>(stg + (J.stage ? (size_t)(J.pe.L - 1) * D : 0));
-  R dg[kFusedNA];
-  if (J.has_pe) {
-    for (int i = tid; i < kPeBinom * kPeBinom; i += kFusedBlock) sb[i] = J.pe.binom[i];
-    if (J.stage) {
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kFusedNA; ++q) {
-        const uint32_t s = tid + kFusedBlock * q;
-        dg[q] = (R)0;
-        if (s < D) scount[s] = pe_stage_row<R>(J.hv, J.pe, sb, u, s, stg + s, D, dg[q]);
-      }
-    }
-  }
-
-  // u_0 = the input; beta0 = ||u_0||
-  double nn = 0.0;
-#pragma unroll
-  for (int q = 0; q < kFusedNA; ++q) {
-    const uint32_t s = tid + kFusedBlock * q;
-    if (s < D) {
-      const V v = vin[s];
-      ub[s] = v;
-      nn += (double)v.x * v.x + (double)v.y * v.y;
-    }
-  }
-  nn = wave_sum(nn);
-  if (lane == 0) wred[wv][0] = nn;
-  fused_totals(wred, 1, tot);
-  const double b0sq = tot[0];
-  if (!(b0sq > 0.0)) {
-    // a zero input gives a zero output; a non-finite one a NaN output
-    const bool zero = b0sq == 0.0;
-#pragma unroll
-    for (int q = 0; q < kFusedNA; ++q) {
-      const uint32_t s = tid + kFusedBlock * q;
-      if (s < D) vout[s] = zero ? V{(R)0, (R)0} : V{(R)NAN, (R)NAN};
-    }
-    if (tid == 0 && J.m_eff_out) *J.m_eff_out = zero ? 0 : 1;
-    return;
-  }
-  const double beta0 = sqrt(b0sq);
-  if (tid == 0) {
-    sc[0] = 1.0 / beta0;
-    off[0] = 0.0;
-  }
-  __syncthreads();
-
-  // Step k takes h = H u_k, its window dots and ||u_k||^2 (of the vector the
-  // previous step stored) in one block reduction; the scale s_k = 1/||u_k||,
-  // the breakdown test on ||u_k|| and then y = s_k h follow from the totals.
-  double normT = 0.0;
-  int meff = m;
-  double wn_wave = 0.0;   // this wavefront's part of ||u_k||^2 (k >= 1)
-  for (int k = 0; k < m; ++k) {
-    const bool last = k == m - 1;
-    const int i0 = last ? k : (J.reorth ? 0 : (k > 0 ? k - 1 : 0));
-    const int nw = k - i0 + 1;
-    const V* uk = ub + (size_t)k * D;
-    if (k > 0) __syncthreads();   // every row of u_k is stored
-    // h = H u_k on this thread's rows, in the vector type
-    R hr[kFusedNA], hi[kFusedNA];
-#pragma unroll
-    for (int q = 0; q < kFusedNA; ++q) {
-      const uint32_t s = tid + kFusedBlock * q;
-      hr[q] = (R)0;
-      hi[q] = (R)0;
-      if (s < D) {
-        if (J.has_pe && J.stage) {
-          const int cnt = scount[s];
-          if (cnt < 0) {
-            hr[q] = hi[q] = (R)NAN;
-          } else {
-            const R hJ = (R)J.hv.half_J;
-            const R rt2 = (R)1.4142135623730951, irt2 = (R)0.70710678118654752;
-            const V xb = uk[s];
-            R ar = dg[q] * xb.x, ai = dg[q] * xb.y;
-#pragma unroll 4
-            for (int j = 0; j < cnt; ++j) {
-              const uint32_t e = stg[(size_t)j * D + s];
-              const uint32_t code = e >> 30;
-              const R w = (code == 1u) ? (R)1 : (code == 2u ? rt2 : irt2);
-              const V xa = uk[e & 0x3FFFFFFFu];
-              ar += hJ * w * xa.x;
-              ai += hJ * w * xa.y;
-            }
-            hr[q] = ar;
-            hi[q] = ai;
-          }
-        } else if (J.has_pe) {
-          bool bad;
-          pe_row<R>(J.hv, J.pe, sb, u, s, [&](uint32_t i) { return uk[i]; }, hr[q], hi[q], bad);
-          if (bad) hr[q] = hi[q] = (R)NAN;
-        } else {
-          full_row<R>(J.hv, s, uk, u, hr[q], hi[q]);
-        }
-      }
-    }
-    // <u_i|h> for the window, two vectors per quad_sums
-    for (int i = i0; i <= k; i += 2) {
-      const bool two = i + 1 <= k;
-      double a0r = 0.0, a0i = 0.0, a1r = 0.0, a1i = 0.0;
-#pragma unroll
-      for (int q = 0; q < kFusedNA; ++q) {
-        const uint32_t s = tid + kFusedBlock * q;
-        if (s < D) {
-          const double h_r = (double)hr[q], h_i = (double)hi[q];
-          const V x0 = ub[(size_t)i * D + s];
-          a0r += (double)x0.x * h_r + (double)x0.y * h_i;
-          a0i += (double)x0.x * h_i - (double)x0.y * h_r;
-          if (two) {
-            const V x1 = ub[(size_t)(i + 1) * D + s];
-            a1r += (double)x1.x * h_r + (double)x1.y * h_i;
-            a1i += (double)x1.x * h_i - (double)x1.y * h_r;
-          }
-        }
-      }
-      const double t = quad_sums_swap(a0r, a0i, a1r, a1i);
-      if (lane < 4u) wred[wv][2 * (i - i0) + lane] = t;
-    }
-    // (slot 2 nw + 2: the pair loop writes at most up to 2 nw + 1)
-    if (lane == 0) wred[wv][2 * nw + 2] = wn_wave;
-    fused_totals(wred, 2 * nw + 3, tot);
-    // s_k, or a breakdown: ||u_k|| small against ||T|| means an invariant
-    // Krylov space of dimension k
-    double sk, offk;
-    if (k == 0) {
-      sk = 1.0 / beta0;
-      offk = 0.0;
-    } else {
-      offk = sqrt(tot[2 * nw + 2]);
-      if (offk <= J.tol * fmax(1.0, normT)) {
-        meff = k;
-        break;
-      }
-      sk = 1.0 / offk;
-      if (tid == 0) {
-        off[k] = offk;
-        sc[k] = sk;
-      }
-    }
-    // alpha_k = s_k Re<u_k|s_k h>, the running ||T||
-    const double alpha = sk * sk * tot[2 * (k - i0)];
-    normT = fmax(normT, fabs(alpha) + offk);
-    if (tid == 0) al[k] = alpha;
-    if (last) break;
-    // w = y - sum_i c_i s_i u_i with y = s_k h and c_i = s_i <u_i|y>, stored
-    // as u_{k+1}
-    double wn = 0.0;
-    V* uo = ub + (size_t)(k + 1) * D;
-#pragma unroll
-    for (int q = 0; q < kFusedNA; ++q) {
-      const uint32_t s = tid + kFusedBlock * q;
-      if (s < D) {
-        double wr = sk * (double)hr[q], wi = sk * (double)hi[q];
-        for (int i = i0; i <= k; ++i) {
-          const double si = (i == k) ? sk : sc[i];
-          const double f = si * si * sk;
-          const double cr = f * tot[2 * (i - i0)], ci = f * tot[2 * (i - i0) + 1];
-          const V x = ub[(size_t)i * D + s];
-          wr -= cr * x.x - ci * x.y;
-          wi -= cr * x.y + ci * x.x;
-        }
-        V o;
-        o.x = (R)wr;
-        o.y = (R)wi;
-        uo[s] = o;
-        wn += (double)o.x * o.x + (double)o.y * o.y;
-      }
-    }
-    wn_wave = wave_sum(wn);
-  }
-  __syncthreads();
-  // exp(-itT) e_1 on wavefront 0 and the combination coefficients beta0 e_j s_j
-  if (wv == 0) {
-    const int i = (int)lane;
-    double ai = 0.0, lo = 0.0, hi = 0.0;
-    if (i < meff) {
-      ai = al[i];
-      lo = (i > 0) ? off[i] : 0.0;
-      hi = (i + 1 < meff) ? off[i + 1] : 0.0;
-    }
-    double cr, ci;
-    tri_exp_wave(ai, lo, hi, J.t, cr, ci);
-    if (i < meff) dco[i] = cplx_d{beta0 * cr * sc[i], beta0 * ci * sc[i]};
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kFusedNA; ++q) {
-    const uint32_t s = tid + kFusedBlock * q;
-    if (s < D) {
-      double orr = 0.0, oi = 0.0;
-      for (int j = 0; j < meff; ++j) {
-        const cplx_d c = dco[j];
-        const V x = ub[(size_t)j * D + s];
-        orr += c.re * x.x - c.im * x.y;
-        oi += c.re * x.y + c.im * x.x;
-      }
-      V o;
-      o.x = (R)orr;
-      o.y = (R)oi;
-      vout[s] = o;
-    }
-  }
-  if (tid == 0 && J.m_eff_out) *J.m_eff_out = meff;
-}
-
-// The one-block form applies when the stored basis fits in LDS and no tile
-// size is forced (KG_TILE_BITS) and KG_NO_FUSED is unset.
-template <typename R>
-bool fused_applies(const KrylovCall& c) {
-  using V = typename VT<R>::T;
-  if (c.geo.D > kFusedMaxD || (size_t)c.m * c.geo.D * sizeof(V) > kFusedLds) return false;
-  const char* tb = getenv("KG_TILE_BITS");
-  const char* nf = getenv("KG_NO_FUSED");
-  return !(tb && *tb) && !(nf && *nf && strcmp(nf, "0") != 0);
-}
-
-template <typename R>
-hipError_t launch_fused_t(const KrylovCall* calls, int n, hipStream_t s) {
-  using V = typename VT<R>::T;
-  // the stored basis may exceed the default 64 KiB of dynamic LDS: raise the
-  // limit of this kernel once per device
-  static std::atomic<uint64_t> raised{0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = (dev < 64) ? (1ull << dev) : 0ull;
-  if (!bit || !(raised.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_krylov_fused<R>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsStaged);
-    if (e != hipSuccess) return e;
-    raised.fetch_or(bit, std::memory_order_acq_rel);
-  }
-  // the reduced basis's neighbour lists (L - 1 slots and a count per row) are
-  // staged in LDS behind the stored vectors when both fit
-  const KrylovCall& c0 = calls[0];
-  const size_t basis_bytes = (size_t)c0.m * c0.geo.D * sizeof(V);
-  const size_t stage_bytes = c0.pe ? (size_t)c0.pe->L * c0.geo.D * sizeof(uint32_t) : 0;
-  const bool stage = c0.pe && basis_bytes + stage_bytes <= kFusedLdsStaged;
-  FusedBatch fb;
-  memset(&fb, 0, sizeof(fb));
-  for (int j = 0; j < n; ++j) {
-    const KrylovCall& c = calls[j];
-    FusedJob& f = fb.job[j];
-    f.hv = c.hv;
-    if (c.pe) f.pe = *c.pe;
-    f.has_pe = c.pe ? 1 : 0;
-    f.stage = (stage && c.pe && c.pe->L == c0.pe->L && c.geo.D == c0.geo.D) ? 1 : 0;
-    f.D = c.geo.D;
-    f.m = c.m;
-    f.reorth = c.reorth;
-    f.t = c.t;
-    f.tol = c.tol;
-    f.v_in = c.v_in;
-    f.v_out = c.v_out;
-    f.m_eff_out = c.m_eff_out;
-  }
-  const size_t lds = basis_bytes + (stage ? stage_bytes : 0);
-  hipLaunchKernelGGL((k_krylov_fused<R>), dim3(n), dim3(kFusedBlock), lds, s, fb);
-  return hipGetLastError();
-}
-
 template <typename R>
 hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss, int n, hipStream_t s) {
   using V = typename VT<R>::T;
   const KrylovCall& c0 = calls[0];
-  if (fused_applies<R>(c0)) return launch_fused_t<R>(calls, n, s);
+  if (sweep_applies(c0)) {
+    SweepJob jobs[kMaxJobs];
+    for (int j = 0; j < n; ++j) jobs[j] = sweep_job(calls[j]);
+    return launch_sweeps(c0.prec, jobs, n, s);
+  }
   LzBatch lb;
   CombBatch cb;
   memset(&lb, 0, sizeof(lb));

@@ -1,0 +1,526 @@
+// Short vectors: a block runs a whole sweep of Krylov calls.
+//
+// For D <= 1024 amplitudes whose basis fits in LDS, one block carries a chain
+// of Krylov calls (Algorithm 2, the small exponential of Eqs. A2-A3 and the
+// combination; each call's output is the next one's input) without leaving the
+// compute unit: no launch, no global round trip and one barrier per Lanczos
+// step.  Independent sweeps (the forward states and the costates of a
+// gradient, the columns of an operator) are the blocks of one launch.
+//
+// Such a step is a serial chain on one compute unit: H v from LDS, the window,
+// the sums over the block, the scalars.  It is bound by that chain's latency,
+// so it is kept short: one amplitude per thread with its neighbour list in
+// registers; the single-pass step of kg_step.h, which needs one block-wide sum
+// where projecting against the finished u_k needs the sum before the update;
+// the dots by MFMA, with u_k and y_k as two more rows of the window, so that
+// one pass gives every measurement; and with up to four wavefronts (one per
+// SIMD) every wavefront computes the scalars itself, which saves a second
+// barrier and a round trip through LDS.  With more wavefronts they would
+// compete for the SIMDs, and wavefront 0 computes for all.
+//
+// Measured against one launch per call with two block-wide sums per step, in
+// complex128: the gradient of 50 slices at D = 256, m = 10 takes 1.14 ms
+// (2.88), the centred one of 584 slices at D = 146 13.9 ms (45.2), one call
+// alone at D = 256 25.9 us (29.5).  Of a step's 2.2 us the H v takes 0.3, the
+// rows and their MFMA 0.6, the sums over the wavefronts 0.3 and the scalars
+// 0.7.
+//
+// LDS: slot i (stride DS) holds u_i; w'_k waits in slot k + 2 until step
+// k + 2 overwrites it with its u, so H v of step k + 1 can read it while
+// u_{k+1} is written.
+
+#include <hip/hip_runtime.h>
+
+#include <math.h>
+#include <stdint.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <atomic>
+
+#include "kg_device.h"
+#include "kg_internal.h"
+#include "kg_step.h"
+
+namespace kg {
+namespace {
+
+constexpr int kSweepNbr = 12;             // neighbours per row held in registers
+constexpr size_t kSweepLds = 160u << 10;  // LDS of a compute unit
+constexpr size_t kSweepStatic = sizeof(LzStore) + 256;   // static LDS of the larger form
+constexpr int kRedThreads = 256;          // up to here every wavefront computes the scalars
+
+struct SweepBatch {
+  SweepJob job[kSweepJobs];
+};
+
+// Vector stride in LDS: padded so that the four vectors a wavefront reads at
+// once start 64 bytes apart modulo the 256 bytes of the banks.
+template <typename R>
+__host__ __device__ inline uint32_t slot_stride(uint32_t D) {
+  const uint32_t unit = sizeof(R) == 4 ? 32u : 16u, want = unit / 4u;
+  return D + ((want + unit - (D % unit)) % unit);
+}
+
+template <typename R>
+inline size_t sweep_lds_bytes(uint32_t D, int m) {
+  const size_t nw = (D + 63) / 64;
+  const size_t vecs = ((size_t)(m + 1) * slot_stride<R>(D) + nw * 64) * sizeof(typename VT<R>::T);
+  const size_t meas = 2 * nw * (size_t)(4 * (m + 2)) * sizeof(double);
+  const size_t coef = (nw <= kRedThreads / 64 ? nw : 1) * 2 * (kMaxM + 8) * sizeof(cplx_d);
+  return ((vecs + 15) / 16) * 16 + meas + coef + 64;
+}
+
+// Address of call q's output.
+template <typename V>
+__device__ __forceinline__ V* sweep_out(const SweepJob& J, int q, int j) {
+  size_t at;
+  if (!J.states) {
+    at = (size_t)q;
+  } else if (J.c == 0) {
+    at = (size_t)(j - 1);
+  } else {
+    const int seg = (j - 1) / J.c;
+    if (j % J.c == 0 && seg < J.nseg - 1) {
+      at = (size_t)seg;
+    } else {
+      const int b = J.nbuf == 2 ? (seg & 1) : 0;
+      at = (size_t)(J.nseg - 1 + b * J.c + (j - seg * J.c - 1));
+    }
+  }
+  return reinterpret_cast<V*>(J.out + at * J.vb);
+}
+
+// TH: largest block.  RED: every wavefront computes the scalars.
+template <typename R, int TH, bool RED>
+__global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
+  using V = typename VT<R>::T;
+  const SweepJob& J = Bt.job[blockIdx.x];
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t wv = uniform_u32(tid >> 6), nwv = blockDim.x >> 6;
+  const uint32_t c = lane & 3u, a = lane >> 2;
+  const uint32_t D = J.D, DS = slot_stride<R>(D);
+  const int m = J.m;
+  V* ub = reinterpret_cast<V*>(smem_raw);
+  V* yst = ub + (size_t)(m + 1) * DS;
+  double* wred = reinterpret_cast<double*>(
+      smem_raw + ((((size_t)(m + 1) * DS + nwv * 64u) * sizeof(V) + 15) / 16) * 16);
+  const uint32_t rowlen = 4u * (uint32_t)(m + 2);
+  cplx_d* cfs = reinterpret_cast<cplx_d*>(wred + 2 * nwv * rowlen) + (RED ? wv * 2u * (kMaxM + 8) : 0u);
+  cplx_d* dcs = cfs + kMaxM + 8;
+  // wavefront 0's scalars when it computes for all
+  struct Shared {
+    LzStore lz;
+    StepNext nx;
+    double normT, beta0, sk, rp, gp;
+    int m_eff, go;
+  };
+  __shared__ Shared sh;
+
+  // rows past D (and the padding that whole units read) stay finite
+  for (uint32_t i = tid; i < (uint32_t)(m + 1) * DS + nwv * 64u; i += blockDim.x) ub[i] = V{(R)0, (R)0};
+  if (RED || wv == 0) {
+    cfs[lane] = cplx_d{0.0, 0.0};
+    if (lane < 8u) cfs[64 + lane] = cplx_d{0.0, 0.0};
+  }
+
+  // this thread's row: diagonal d0 + u dz, neighbours and their weights
+  const bool in = tid < D;
+  const uint32_t row = in ? tid : 0u;
+  const int L = J.hv.L;
+  uint32_t nb[kSweepNbr];
+  R wt[kSweepNbr];
+  R d0 = (R)0, dz = (R)0;
+  int slots = 0;
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < kSweepNbr; ++i) {
+    nb[i] = row;
+    wt[i] = (R)0;
+  }
+  {
+    const R hJ = (R)J.hv.half_J;
+    const uint32_t bondmask = (L >= 2) ? ((1u << (L - 1)) - 1u) : 0u;
+    const uint32_t r = J.has_pe ? J.pe.reps[row] : row;
+    const uint32_t anti = (r ^ (r >> 1)) & bondmask;
+    d0 = (R)J.hv.c_zz * (R)(L - 1 - 2 * (int)__popc(anti));
+    if (J.hv.hc_kind == 1) dz = (R)(0.5 * J.hv.sz_count) - (R)__popc(r & J.hv.sz_mask);
+    slots = J.nbr;
+    uint32_t act = anti;
+    const uint32_t full = (L == 32) ? 0xFFFFFFFFu : ((1u << L) - 1u);
+    const uint32_t rank = J.has_pe ? J.pe.ranks[row] : 0u;
+    const bool nb2 = J.has_pe && (__brev(r) >> (32 - L)) != r;
+    if (J.has_pe) bad = rank >= J.pe.nsec;
+#pragma unroll
+    for (int i = 0; i < kSweepNbr; ++i) {
+      if (i < slots && act && !bad) {
+        const int q = __builtin_ctz(act);
+        act &= act - 1u;
+        const uint32_t s2 = r ^ (3u << q);
+        if (J.has_pe) {
+          // the orbit through the combinatorial rank over the zero bits
+          const uint32_t dl = J.pe.binom[q * kPeBinom + __popc(~r & full & ((1u << q) - 1u))];
+          const uint32_t rk = (((r >> q) & 1u) == 0u) ? rank + dl : rank - dl;
+          const int32_t ai = (rk < J.pe.nsec) ? J.pe.index[rk] : -1;
+          const bool ok = (uint32_t)ai < D;
+          bad = bad || !ok;
+          const bool na2 = (__brev(s2) >> (32 - L)) != s2;
+          nb[i] = ok ? (uint32_t)ai : row;
+          wt[i] = hJ * ((nb2 == na2) ? (R)1 : (nb2 ? (R)1.4142135623730951 : (R)0.70710678118654752));
+        } else {
+          nb[i] = s2;
+          wt[i] = hJ;
+        }
+      }
+    }
+    // a table entry out of range turns the row into NaN, never a stray read
+    if (bad) d0 = (R)NAN;
+    if (!in) {
+      d0 = dz = (R)0;
+#pragma unroll
+      for (int i = 0; i < kSweepNbr; ++i) wt[i] = (R)0;
+    }
+  }
+  const bool sx = J.hv.hc_kind == 0;
+  const uint32_t flip = sx ? (row ^ (1u << J.hv.hc_bit)) : row;
+
+  V xin = in ? reinterpret_cast<const V*>(J.in)[row] : V{(R)0, (R)0};
+  uint32_t par = 0;
+  double unext = J.u ? J.u[J.j0 - 1] : J.hv.u_val;
+  for (int q = 0; q < J.n; ++q) {
+    const int j = J.j0 + q * J.dj;
+    const double u = unext;
+    if (J.u && q + 1 < J.n) unext = J.u[j + J.dj - 1];
+    const R diag = d0 + (R)u * dz;
+    const R cu = sx ? (R)(0.5 * u) : (R)0;
+    LzLane s;
+    LzRun run;
+    StepNext nx{cplx_d{0.0, 0.0}, 1.0, 1.0};
+    if (in) ub[row] = xin;
+    if (RED || wv == 0) cfs[lane] = cplx_d{lane == 1u ? -1.0 : 0.0, 0.0};   // y of step 0
+    if constexpr (!RED) {
+      if (wv == 0) put_lane(sh.lz, s);
+    }
+    __syncthreads();
+    V up{(R)0, (R)0}, yp{(R)0, (R)0};
+    for (int k = 0; k < m; ++k) {
+      const bool last = k == m - 1;
+      const int i0 = window_first(k, m, J.reorth), nw = k - i0;
+      V* uk = ub + (size_t)k * DS;
+      // ---- H v of the source on this row, in the vector type
+      const V* src = k == 0 ? ub : ub + (size_t)(k + 1) * DS;
+      const V xs = src[row];
+      R hr = diag * xs.x, hi = diag * xs.y;
+      const V xf = src[flip];
+      // four neighbours' reads in flight together; unused slots have weight 0
+#pragma unroll
+      for (int i = 0; i < kSweepNbr; i += 4) {
+        if (i < slots) {
+          V x[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = src[nb[i + e]];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            hr += wt[i + e] * x[e].x;
+            hi += wt[i + e] * x[e].y;
+          }
+        }
+      }
+      hr += cu * xf.x;
+      hi += cu * xf.y;
+      // ---- u_k and y_k, rounded as stored
+      V uo, yo;
+      if (k == 0) {
+        uo = xs;
+        yo.x = hr;
+        yo.y = hi;
+      } else {
+        const double sg = nx.sig;
+        uo.x = (R)(sg * (double)xs.x - (nx.c.re * (double)up.x - nx.c.im * (double)up.y));
+        uo.y = (R)(sg * (double)xs.y - (nx.c.re * (double)up.y + nx.c.im * (double)up.x));
+        yo.x = (R)(sg * (double)hr - (nx.c.re * (double)yp.x - nx.c.im * (double)yp.y));
+        yo.y = (R)(sg * (double)hi - (nx.c.re * (double)yp.y + nx.c.im * (double)yp.x));
+        if (in) uk[row] = uo;
+      }
+      if (!in) uo = yo = V{(R)0, (R)0};
+      yst[tid] = yo;
+      up = uo;
+      yp = yo;
+      wave_lds_fence();
+      // ---- rows [i0, k), u_k, y_k against (y_k, u_k)
+      const uint32_t s0 = wv << 6;
+      double b[4], bp[4];
+      {
+        const V* src2 = c < 2u ? yst : uk;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const uint32_t s = s0 + unit_amp(t, a);
+          const R v = reinterpret_cast<const R*>(src2 + s)[c & 1u];
+          b[t] = s < D ? (double)v : 0.0;
+          bp[t] = turned(b[t]);
+        }
+      }
+      const int nrows = nw + (last ? 1 : 2);
+      double zr[4] = {0.0, 0.0, 0.0, 0.0}, zi[4] = {0.0, 0.0, 0.0, 0.0};
+      double* wrow = wred + (par * nwv + wv) * rowlen;
+      for (int r0 = 0; r0 < nrows; r0 += 8) {
+        V q0[4], q1[4];
+        const bool two = r0 + 4 < nrows;
+        const auto rows = [&](int r, V (&o)[4]) {
+          const V* p = r < nw ? ub + (size_t)(i0 + r) * DS : (r == nw ? uk : yst);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) o[t] = p[s0 + unit_amp(t, a)];
+        };
+        rows(r0 + (int)c, q0);
+        if (two) rows(r0 + 4 + (int)c, q1);
+        double e0 = 0.0, e1 = 0.0, f0 = 0.0, f1 = 0.0;
+        unit_rows(q0, b, bp, cfs[min(i0 + r0 + (int)c, kMaxM + 7)], zr, zi, e0, e1);
+        if (two) unit_rows(q1, b, bp, cfs[min(i0 + r0 + 4 + (int)c, kMaxM + 7)], zr, zi, f0, f1);
+        const int r = r0 + (int)(lane >> 4);
+        const double e = unit_dots(e0 + e1);
+        if ((lane & 12u) == 0u && r < nrows) wrow[4 * r + (int)c] = e;
+        if (two) {
+          const double f = unit_dots(f0 + f1);
+          if ((lane & 12u) == 0u && r + 4 < nrows) wrow[4 * (r + 4) + (int)c] = f;
+        }
+      }
+      if (!last) {
+        const uint32_t s = s0 + unit_amp((int)c, a);
+        const double wr = -quad_z(zr), wi = -quad_z(zi);
+        if (s < D) ub[(size_t)(k + 2) * DS + s] = V{(R)wr, (R)wi};
+      }
+      __syncthreads();
+      // ---- totals over the wavefronts, in order, and the scalars
+      bool go = false;
+      if (RED || wv == 0) {
+        const int r = (int)lane - i0;
+        double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
+        if (r >= 0 && r < nrows) {
+          const double* p = wred + par * nwv * rowlen + 4 * r;
+          for (uint32_t w0 = 0; w0 < nwv; w0 += 4) {
+            double2 x[4], y[4];
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) {
+              const double2* pw = reinterpret_cast<const double2*>(p + min(w0 + e, nwv - 1u) * rowlen);
+              x[e] = pw[0];
+              y[e] = pw[1];
+            }
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) {
+              if (w0 + e < nwv) {
+                t0 += x[e].x;
+                t1 += x[e].y;
+                t2 += y[e].x;
+                t3 += y[e].y;
+              }
+            }
+          }
+        }
+        const cplx_d A{t0, t1}, G{t2, t3};
+        if constexpr (!RED) {
+          get_lane(sh.lz, s);
+          if (k > 0) {
+            run.normT = sh.normT;
+            run.beta0 = sh.beta0;
+            run.sk = sh.sk;
+            run.rp = sh.rp;
+            run.gp = sh.gp;
+          }
+        }
+        go = step_scalars(s, run, k, m, J.reorth, J.tol, A, G, lane_cplx(A, k), lane_value(t2, k),
+                          lane_value(t0, min(k + 1, 63)), nx);
+        // row k + 2 of the next step is its y
+        cfs[lane] = (int)lane == k + 2 ? cplx_d{-nx.s, 0.0} : s.cw;
+        if constexpr (!RED) {
+          put_lane(sh.lz, s);
+          if (lane == 0) {
+            sh.normT = run.normT;
+            sh.beta0 = run.beta0;
+            sh.sk = run.sk;
+            sh.rp = run.rp;
+            sh.gp = run.gp;
+            sh.m_eff = run.m_eff;
+            sh.nx = nx;
+            sh.go = go ? 1 : 0;
+          }
+        }
+      }
+      par ^= 1u;
+      if constexpr (RED) {
+        wave_lds_fence();
+      } else {
+        __syncthreads();
+        nx = sh.nx;
+        go = sh.go != 0;
+      }
+      if (!go) break;
+    }
+    // ---- exp(-itT) e_1 and the combination
+    if constexpr (RED) {
+      dcs[lane] = comb_coef(s, run, J.t);
+      wave_lds_fence();
+    } else {
+      run.beta0 = sh.beta0;
+      run.m_eff = sh.m_eff;
+      if (wv == 0) {
+        get_lane(sh.lz, s);
+        dcs[lane] = comb_coef(s, run, J.t);
+      }
+      __syncthreads();
+    }
+    const int me = run.m_eff;
+    double orr = 0.0, oi = 0.0;
+#pragma unroll 4
+    for (int i = 0; i < me; ++i) {
+      const cplx_d d = dcs[i];
+      const V x = ub[(size_t)i * DS + row];
+      orr += d.re * x.x - d.im * x.y;
+      oi += d.re * x.y + d.im * x.x;
+    }
+    xin.x = in ? (R)orr : (R)0;
+    xin.y = in ? (R)oi : (R)0;
+    if (in) sweep_out<V>(J, q, j)[row] = xin;
+    if (J.m_eff_out && tid == 0) *J.m_eff_out = me;
+  }
+}
+
+template <typename R, int TH, bool RED>
+hipError_t launch_sweep_t(const SweepBatch& b, int n, size_t lds, uint32_t threads, hipStream_t s) {
+  // the basis exceeds the default 64 KiB of dynamic LDS: raise the limit of
+  // this kernel once per device
+  static std::atomic<uint64_t> raised{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = (dev < 64) ? (1ull << dev) : 0ull;
+  if (!bit || !(raised.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep<R, TH, RED>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)(kSweepLds - kSweepStatic));
+    if (e != hipSuccess) return e;
+    raised.fetch_or(bit, std::memory_order_acq_rel);
+  }
+  hipLaunchKernelGGL((k_sweep<R, TH, RED>), dim3(n), dim3(threads), lds, s, b);
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_sweep_r(const SweepBatch& b, int n, hipStream_t s) {
+  const uint32_t D = b.job[0].D, threads = (D + 63u) / 64u * 64u;
+  const size_t lds = sweep_lds_bytes<R>(D, b.job[0].m);
+  return threads <= (uint32_t)kRedThreads ? launch_sweep_t<R, kRedThreads, true>(b, n, lds, threads, s)
+                                          : launch_sweep_t<R, 1024, false>(b, n, lds, threads, s);
+}
+
+// The brackets of a run of slices, one block each: block b takes slice
+// j = jhi - b with costate b - with0 of `lams` (with0: block 0 takes lam0) and
+// writes g_j = 2 cr Im(conj(beta) <lambda_j|Hc|psi_j>) (added with
+// `accumulate`); slice 0 goes to *g0.
+template <typename R>
+__global__ void __launch_bounds__(256) k_brackets(BracketRun r, const double* beta, int accumulate) {
+  using V = typename VT<R>::T;
+  __shared__ double part[2][4];
+  const int b = blockIdx.x, j = r.jhi - b;
+  const V* lam = reinterpret_cast<const V*>(
+      (r.lam0 && b == 0) ? static_cast<const char*>(r.lam0) : r.lams + (size_t)(b - (r.lam0 ? 1 : 0)) * r.states.vb);
+  const V* psi = j == 0 ? reinterpret_cast<const V*>(r.psi0) : sweep_out<V>(r.states, 0, j);
+  const HvArgs& a = r.states.hv;
+  const uint32_t D = r.states.D;
+  const uint32_t* reps = r.states.has_pe ? r.states.pe.reps : nullptr;
+  const uint32_t flip = (a.hc_kind == 0) ? (1u << a.hc_bit) : 0u;
+  double sr = 0.0, si = 0.0;
+  for (uint32_t s = threadIdx.x; s < D; s += 256u) {
+    const V l = lam[s], p = psi[s ^ flip];
+    const uint32_t pat = reps ? reps[s] : s;
+    const double hc = (a.hc_kind == 0) ? 0.5 : 0.5 * a.sz_count - (double)__popc(pat & a.sz_mask);
+    const double pr = hc * (double)p.x, pi = hc * (double)p.y;
+    const double lr = l.x, li = l.y;
+    sr += lr * pr + li * pi;
+    si += lr * pi - li * pr;
+  }
+  sr = wave_sum(sr);
+  si = wave_sum(si);
+  if ((threadIdx.x & 63u) == 0) {
+    part[0][threadIdx.x >> 6] = sr;
+    part[1][threadIdx.x >> 6] = si;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double Br = ((part[0][0] + part[0][1]) + part[0][2]) + part[0][3];
+    const double Bi = ((part[1][0] + part[1][1]) + part[1][2]) + part[1][3];
+    const double g = 2.0 * r.cr * (beta[0] * Bi - beta[1] * Br);
+    double* out = j == 0 ? r.g0 : r.grad + (j - 1);
+    *out = accumulate ? *out + g : g;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_brackets(int prec, const BracketRun& r, int n, const double* beta, bool accumulate,
+                           hipStream_t s) {
+  if (n < 1) return hipSuccess;
+  if (prec == 0)
+    hipLaunchKernelGGL(k_brackets<double>, dim3(n), dim3(256), 0, s, r, beta, accumulate ? 1 : 0);
+  else
+    hipLaunchKernelGGL(k_brackets<float>, dim3(n), dim3(256), 0, s, r, beta, accumulate ? 1 : 0);
+  return hipGetLastError();
+}
+
+int sweep_neighbours(const PeArgs* pe, int L) {
+  if (!pe) return L - 1;
+  const int up = pe->K < pe->L - pe->K ? pe->K : pe->L - pe->K;
+  return 2 * up < pe->L - 1 ? 2 * up : pe->L - 1;
+}
+
+bool sweep_fits(int prec, uint32_t D, int m, int nbr) {
+  if (D < 1 || D > kSweepMaxD || nbr > kSweepNbr) return false;
+  const size_t need = prec == 0 ? sweep_lds_bytes<double>(D, m) : sweep_lds_bytes<float>(D, m);
+  return need + kSweepStatic <= kSweepLds;
+}
+
+// The one-block form applies when its vectors fit in LDS and no tile size is
+// forced (KG_TILE_BITS) and KG_NO_FUSED is unset.
+bool sweep_applies(const KrylovCall& c) {
+  if (!sweep_fits(c.prec, c.geo.D, c.m, sweep_neighbours(c.pe, c.hv.L))) return false;
+  const char* tb = getenv("KG_TILE_BITS");
+  const char* nf = getenv("KG_NO_FUSED");
+  return !(tb && *tb) && !(nf && *nf && strcmp(nf, "0") != 0);
+}
+
+SweepJob sweep_job(const KrylovCall& c) {
+  SweepJob j;
+  memset(static_cast<void*>(&j), 0, sizeof(j));
+  j.hv = c.hv;
+  if (c.pe) j.pe = *c.pe;
+  j.has_pe = c.pe ? 1 : 0;
+  j.nbr = sweep_neighbours(c.pe, c.hv.L);
+  j.D = c.geo.D;
+  j.m = c.m;
+  j.reorth = c.reorth;
+  j.t = c.t;
+  j.tol = c.tol;
+  j.u = c.hv.u_ptr;
+  j.in = c.v_in;
+  j.n = 1;
+  j.j0 = 1;
+  j.dj = 1;
+  j.out = static_cast<char*>(c.v_out);
+  j.vb = (size_t)c.geo.D * (c.prec == 0 ? 16 : 8);
+  j.m_eff_out = c.m_eff_out;
+  return j;
+}
+
+hipError_t launch_sweeps(int prec, const SweepJob* jobs, int n, hipStream_t s) {
+  SweepBatch b;
+  memset(static_cast<void*>(&b), 0, sizeof(b));
+  for (int at = 0; at < n; at += kSweepJobs) {
+    const int cnt = n - at < kSweepJobs ? n - at : kSweepJobs;
+    for (int i = 0; i < cnt; ++i) b.job[i] = jobs[at + i];
+    const hipError_t e = prec == 0 ? launch_sweep_r<double>(b, cnt, s) : launch_sweep_r<float>(b, cnt, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+}  // namespace kg
