@@ -528,7 +528,9 @@ kg_status kg_debug_index_map(int32_t L, uint32_t s0, uint32_t count, int32_t* n_
  * at most max_launches kernels.  kg_profile_end waits for the last event and
  * fills, per kernel class (KG_PROF_NCLASS entries each; NULL skips an array):
  * launches timed, summed duration in ms, and summed algorithmic bytes
- * (vectors each kernel must read and write once, no cache re-reads).
+ * (vectors each kernel must read and write once, no cache re-reads).  A launch
+ * that does both passes of a Lanczos step counts once in each of their classes,
+ * its time divided by their bytes.
  * Errors: KG_EINVAL, KG_EDEVICE. */
 #define KG_PROF_PASS_A 0    /* Lanczos pass A: H v_k and the projection dots */
 #define KG_PROF_PASS_B 1    /* Lanczos pass B: new basis vector and its norm */

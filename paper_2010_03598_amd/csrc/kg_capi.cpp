@@ -133,11 +133,15 @@ HvArgs make_hv(const kg_xxz* h, const double* u_ptr, double u_val) {
 
 size_t vbytes(uint64_t D, int32_t prec) { return (size_t)D * (prec == KG_C128 ? 16 : 8); }
 
-// A Krylov slot: scalars, reduction partials, basis vectors 1..m-1 and the
-// vector y_k = H v_k of the running step.
+// A Krylov slot: scalars, reduction partials, basis vectors 1..m-1 (and one
+// more for the single-pass steps) and the vector y_k = H v_k of the running step.
+size_t basis_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec) {
+  const int n = k->m - 1 + ((D <= kStepMaxD && k->m > 1) ? 1 : 0);
+  return align_up(vbytes(D, prec) * (size_t)n, 256);
+}
+
 size_t slot_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec) {
-  return ws_fixed_bytes() + align_up(vbytes(D, prec) * (size_t)(k->m - 1), 256) +
-         align_up(vbytes(D, prec), 256);
+  return ws_fixed_bytes() + basis_bytes_d(D, k, prec) + align_up(vbytes(D, prec), 256);
 }
 
 // workspace of vectors of D amplitudes; `extended` adds the two node vectors
@@ -179,7 +183,7 @@ kg_status carve_d(void* ws, size_t ws_bytes, uint64_t D, const kg_krylov* k, int
     o->area_bytes = (size_t)(p + 2 * slot_bytes_d(D, k, prec) - q);
     q += align_up(sizeof(cplx_d) * kPartialRows * kMaxScal, 256);
     o->basis = q;
-    q += align_up(vbytes(D, prec) * (size_t)(k->m - 1), 256);
+    q += basis_bytes_d(D, k, prec);
     o->yk = q;
     o->lam = p + 2 * slot_bytes_d(D, k, prec);
     o->node_a = extended ? static_cast<char*>(o->lam) + vb : nullptr;
@@ -585,6 +589,7 @@ struct Profiler {
     int cls;
     double bytes;
     int e0, e1;
+    double share;      // of the launch's time
   };
   std::vector<Rec> recs;
 };
@@ -622,10 +627,13 @@ bool profiler_take(hipEvent_t* e0, hipEvent_t* e1) {
   return true;
 }
 
-void profiler_stop(Profiler* p, hipStream_t s, int cls, double bytes) {
+void profiler_stop(Profiler* p, hipStream_t s, int cls, double bytes, int cls2, double bytes2) {
   (void)s;
   if (p->armed >= 0 && p->taken) {
-    p->recs.push_back(Profiler::Rec{cls, bytes, p->armed, p->armed + 1});
+    const double share = cls2 >= 0 ? bytes / (bytes + bytes2) : 1.0;
+    p->recs.push_back(Profiler::Rec{cls, bytes, p->armed, p->armed + 1, share});
+    if (cls2 >= 0)
+      p->recs.push_back(Profiler::Rec{cls2, bytes2, p->armed, p->armed + 1, 1.0 - share});
     p->used += 2;
   }
   p->armed = -1;
@@ -682,6 +690,32 @@ Geo make_geo(int L, int prec, int tile_bits_override, int grid_cap, bool standal
   g.ntiles = g.small ? 1u : (1u << (L - g.TB));
   if (grid_cap == kLzGrid && g.ntiles >= kLzManyTiles) grid_cap = kLzGridLarge;
   g.grid = (int)(g.ntiles < (uint32_t)grid_cap ? g.ntiles : (uint32_t)grid_cap);
+  return g;
+}
+
+// Tiling of the single-pass steps: one tile per block, at most kLzGrid blocks.
+// Every block sums the rows of all, so the grid stays at 256 where the tile
+// allows; a tile takes up to eight wavefronts and two amplitudes per thread.
+// Timed calls (m = 16, us) at tiles of 2^7, 2^8, 2^9, 2^10 amplitudes,
+// complex64: L=11 98, 104, 119, 155; L=14 115, 107, 135, 191; L=16 203, 138,
+// 137, 169; L=17 -, 201, 160, 188; L=18 -, -, 290, 209.  complex128 the same
+// order.  The two-pass form takes 231 at L=13, 239 at L=17, 266 at L=18
+// (322 complex128: 252 here); at L=19 both take 320 (complex64), and in
+// complex128 it is ahead (430 against 496): the line is at 2^18.
+Geo make_geo_step(int L, int tile_bits_override) {
+  Geo g;
+  memset(&g, 0, sizeof(g));
+  g.L = L;
+  g.D = 1u << L;
+  int tb = L <= 12 ? 7 : std::max(8, L - 8);
+  if (tile_bits_override >= 6) tb = std::max(tile_bits_override, L - 9);
+  tb = std::max(6, std::min(std::min(tb, 12), L));
+  g.TB = tb;
+  g.RB = std::max(0, tb - 9);
+  g.WB = tb - 6 - g.RB;
+  g.small = (L < tb) ? 1 : 0;
+  g.ntiles = g.small ? 1u : (1u << (L - tb));
+  g.grid = (int)g.ntiles;
   return g;
 }
 
@@ -892,7 +926,9 @@ kg_status krylov_expv_static(const kg_xxz* h, double u, double t, const kg_krylo
     return fail(KG_EINVAL, "v_in and v_out overlap without being equal");
   if (m_eff_dev && (uintptr_t)m_eff_dev % 4) return fail(KG_EINVAL, "m_eff_dev misaligned");
   // one Krylov slot (scalars, partials, m-1 basis vectors and H v_k)
-  const size_t need = slot_bytes_d(geo.D, k, prec);
+  // the limit is that of m vectors; the array has room for one more up to kStepMaxD
+  const size_t need = ws_fixed_bytes() + align_up(vbytes(geo.D, prec) * (size_t)(k->m - 1), 256) +
+                      align_up(vbytes(geo.D, prec), 256);
   if (need > kStaticScratchBytes)
     return fail(KG_EWORKSPACE,
                 "krylov_expv_static: L=%d, m=%d needs %zu bytes of scratch, the static "
@@ -908,7 +944,7 @@ kg_status krylov_expv_static(const kg_xxz* h, double u, double t, const kg_krylo
   W.partials = reinterpret_cast<cplx_d*>(q);
   q += align_up(sizeof(cplx_d) * kPartialRows * kMaxScal, 256);
   W.basis = q;
-  q += align_up(vbytes(geo.D, prec) * (size_t)(k->m - 1), 256);
+  q += basis_bytes_d(geo.D, k, prec);
   W.yk = q;
   const hipStream_t s = (hipStream_t)stream;
   KrylovCall c;
@@ -1321,7 +1357,7 @@ kg_status kg_profile_end(int64_t* launches, double* ms, double* bytes) {
         if (r != hipSuccess) st = hip_fail(r, "kg_profile_end");
       }
       if (launches) launches[rec.cls] += 1;
-      if (ms) ms[rec.cls] += t;
+      if (ms) ms[rec.cls] += rec.share * t;
       if (bytes) bytes[rec.cls] += rec.bytes;
     }
   }

@@ -3,6 +3,7 @@
 // Internal; included only by kg_kernels.hip and kg_batched.hip.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -11,6 +12,20 @@
 #include "kg_internal.h"
 
 namespace kg {
+
+// A kernel launch that takes the profiler's armed event pair when one is
+// armed (the dispatch records the kernel's own start and end), and a plain
+// launch otherwise.
+template <typename... Args, typename F = void (*)(Args...)>
+inline void kg_launch(F kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, Args... args) {
+  hipEvent_t e0, e1;
+  if (profiler_take(&e0, &e1)) {
+    hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, s, e0, e1, 0u, args...);
+  } else {
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
+  }
+}
+
 namespace {
 
 template <typename R>
@@ -650,13 +665,18 @@ __device__ __forceinline__ void next_far(uint32_t& glb, R hJ, uint32_t& flip, R&
 // tile's amplitudes, the S^x partners and the first far partners are requested
 // in one round trip before anything waits (partners outside the tile with
 // coherent loads when kCoh: other workgroups of the launch wrote them).
-template <typename R, int RB, bool kCoh = false>
+struct NoWork {
+  __device__ __forceinline__ void operator()() const {}
+};
+
+template <typename R, int RB, bool kCoh = false, int kFar = FarSlots<R, RB>::n, typename Before = NoWork>
 __device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const Geo& g,
                                         uint32_t tile, const typename VT<R>::T* __restrict__ x,
-                                        typename VT<R>::T* lds, double u) {
+                                        typename VT<R>::T* lds, double u,
+                                        Before before = Before()) {
   using V = typename VT<R>::T;
   constexpr int NR = 1 << RB;
-  constexpr int NS = FarSlots<R, RB>::n;
+  constexpr int NS = kFar < FarSlots<R, RB>::n ? kFar : FarSlots<R, RB>::n;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t w = uniform_u32(threadIdx.x >> 6);
   const int L = g.L;
@@ -706,6 +726,7 @@ __device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const G
     T.xr[r] = own[r].x;
     T.xi[r] = own[r].y;
   }
+  before();
   __syncthreads();
 
   const R czz = (R)a.c_zz;

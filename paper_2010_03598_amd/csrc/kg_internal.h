@@ -98,11 +98,12 @@ struct Geo {               // tiling of one state vector
 Geo make_geo(int L, int prec, int tile_bits_override, int grid_cap = kLzGrid,
              bool standalone = false);
 int stream_grid(uint32_t D);
+int tile_override_from_env();
 
 struct Workspace {         // carved from the caller's workspace
   KState* st;
   cplx_d* partials;        // [kMaxScal][kPartialRows]: column major, one row per block
-  void* basis;             // m-1 vectors (stored Krylov vectors 1..m-1)
+  void* basis;             // stored Krylov vectors 1..m-1 (and one more up to kStepMaxD)
   void* yk;                // one vector: y_k = H v_k of the running step
   void* lam;               // one vector (costate)
   void* node_a;            // quadrature workspaces only: psi at a node
@@ -125,7 +126,10 @@ Profiler* profiler_for_launch();
 // (hipExtLaunchKernel: the kernel's own start and end, as a kernel trace
 // records them); profiler_stop files the record if a launch took them.
 void profiler_start(Profiler* p, hipStream_t s);
-void profiler_stop(Profiler* p, hipStream_t s, int cls, double bytes);
+// A launch that does the work of two classes is filed under both (cls2 >= 0),
+// its time divided by their bytes.
+void profiler_stop(Profiler* p, hipStream_t s, int cls, double bytes, int cls2 = -1,
+                   double bytes2 = 0.0);
 bool profiler_take(hipEvent_t* e0, hipEvent_t* e1);
 
 // ---- launchers (kg_kernels.hip); all enqueue on `s` and return hipSuccess or the launch error
@@ -157,6 +161,7 @@ double pe_gather_bytes(const PeArgs& p, double vb);
 struct KrylovCall {
   HvArgs hv;
   Geo geo;
+  Geo step;                    // tiling of the single-pass steps (launch_krylov sets it)
   const PeArgs* pe = nullptr;  // reduced basis (nullptr: full 2^L space)
   int prec;
   int m;
@@ -168,6 +173,12 @@ struct KrylovCall {
   int32_t* m_eff_out;      // nullable
 };
 hipError_t launch_krylov(const KrylovCall& c, const Workspace& ws, hipStream_t s);
+// One launch per Lanczos step (kg_step.hip) for vectors of up to kStepMaxD
+// amplitudes; needs one more basis vector in the workspace.
+constexpr uint64_t kStepMaxD = 1ull << 18;
+Geo make_geo_step(int L, int tile_bits_override);
+hipError_t launch_krylov_steps(const KrylovCall* calls, const Workspace* const* wss, int n,
+                               hipStream_t s);
 // Two independent calls of the same L, m, reorth and precision in the same launches.
 hipError_t launch_krylov_pair(const KrylovCall& c0, const Workspace& w0, const KrylovCall& c1,
                               const Workspace& w1, hipStream_t s);

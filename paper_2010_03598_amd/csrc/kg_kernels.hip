@@ -46,7 +46,6 @@
 // XCD b%8, and the tiles of one XCD form one contiguous range, so partner tiles
 // of the lower hopping bonds are read from the same L2.
 
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -60,19 +59,6 @@
 #include "kg_internal.h"
 
 namespace kg {
-
-// A kernel launch that takes the profiler's armed event pair when one is
-// armed (the dispatch records the kernel's own start and end), and a plain
-// launch otherwise.
-template <typename... Args, typename F = void (*)(Args...)>
-inline void kg_launch(F kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, Args... args) {
-  hipEvent_t e0, e1;
-  if (profiler_take(&e0, &e1)) {
-    hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, s, e0, e1, 0u, args...);
-  } else {
-    hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
-  }
-}
 
 namespace {
 
@@ -1399,6 +1385,17 @@ hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss,
     SweepJob jobs[kMaxJobs];
     for (int j = 0; j < n; ++j) jobs[j] = sweep_job(calls[j]);
     return launch_sweeps(c0.prec, jobs, n, s);
+  }
+  // one launch per step; a call that KG_TILE_BITS or KG_NO_FUSED keeps from the
+  // one-block form takes the two passes
+  if (!c0.pe && c0.geo.D <= kStepMaxD &&
+      !sweep_fits(c0.prec, c0.geo.D, c0.m, sweep_neighbours(c0.pe, c0.hv.L))) {
+    KrylovCall c[kMaxJobs];
+    for (int j = 0; j < n; ++j) {
+      c[j] = calls[j];
+      c[j].step = make_geo_step(c0.hv.L, tile_override_from_env());
+    }
+    return launch_krylov_steps(c, wss, n, s);
   }
   LzBatch lb;
   CombBatch cb;

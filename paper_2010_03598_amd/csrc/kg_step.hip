@@ -1,0 +1,620 @@
+// One launch per Lanczos step.
+//
+// Vectors between those a single block holds and those that fill the chip are
+// bound by the latency of a chain of launches, about 7 us each whatever they
+// move.  The step as pass A (H v and its dots), then pass B (the update) takes
+// two; in the single-pass form of kg_step.h it takes one: the launch of step k
+// reads the measurements of step k - 1, derives the coefficients, forms u_k,
+// y_k and w'_k and measures.  A Krylov call is m such launches and the
+// combination, whose blocks run the last scalars themselves.
+//
+// A block is NW wavefronts of tile work and one more for the scalars.  Every
+// wavefront sums a share of the previous step's rows (one row of values per
+// block, read in one round trip beside the tile's loads); the extra wavefront
+// turns the totals into coefficients while the others apply H to w'_{k-1},
+// which needs none of them.  All blocks compute the same scalars from the same
+// sums in the same order; block 0 keeps them for the next launch.
+//
+// A launch is about 5.9 us at L = 13 (two passes: 14.4): 1.6 between launches,
+// the rest a chain of two trips to memory, the scalars (0.7) and the block's
+// sums.  Calls at m = 16, complex64, two passes and this form: L=13 231 -> 101
+// us, L=15 232 -> 117, L=16 233 -> 138, L=17 240 -> 160, L=18 267 -> 209;
+// complex128 L=16 241 -> 145, L=18 323 -> 252.
+
+#include <hip/hip_runtime.h>
+
+#include <math.h>
+#include <stdint.h>
+#include <string.h>
+
+#include "kg_device.h"
+#include "kg_internal.h"
+#include "kg_step.h"
+
+namespace kg {
+namespace {
+
+constexpr int kStepJobs = 2;
+
+// Scalars between launches, in the partials table of the workspace (by the
+// parity of the step: a launch reads one copy and writes the other), and the
+// final ones of a basis that ended early.
+struct StepState {
+  LzStore lz[2];
+  LzStore fin;
+  double run[2][5];       // normT, beta0, sk, rp, gp
+  double fin_beta0;
+  int32_t fin_m_eff;
+  int32_t done;
+};
+
+struct StepArgs {
+  HvArgs hv;
+  Geo geo;
+  const void* slot0;
+  void* basis;            // slots 1..m
+  void* y;
+  StepState* st;
+  cplx_d* rows;           // [2][kStepRows][kStepCols]
+  int32_t k, m, reorth;
+  int32_t pad_;
+  double tol, t;
+  void* out;              // combination
+  int32_t* m_eff_out;
+};
+
+constexpr int kStepFar = 4;               // far partners per round trip
+constexpr int kStepRows = 512;            // blocks of a step
+constexpr int kStepCols = 2 * kMaxM + 2;  // values of a row, in pairs
+
+struct StepBatch {
+  StepArgs job[kStepJobs];
+};
+
+template <typename V>
+__device__ __forceinline__ V* step_slot(const StepArgs& a, int i) {
+  return i == 0 ? reinterpret_cast<V*>(const_cast<void*>(a.slot0))
+                : reinterpret_cast<V*>(a.basis) + (size_t)(i - 1) * a.geo.D;
+}
+
+__device__ __forceinline__ void get_run(const StepState& st, int b, LzRun& r) {
+  r.normT = st.run[b][0];
+  r.beta0 = st.run[b][1];
+  r.sk = st.run[b][2];
+  r.rp = st.run[b][3];
+  r.gp = st.run[b][4];
+}
+
+// The scalars of step k on one wavefront from its totals (LDS: window vector w
+// at 2w, 2w + 1, then <u_k|y_k> and (||u_k||^2, ||y_k||^2)).
+__device__ bool run_scalars(const StepArgs& a, int k, const cplx_d* tot, LzLane& s, LzRun& r,
+                            StepNext& nx) {
+  const int lane = threadIdx.x & 63;
+  const int i0 = window_first(k, a.m, a.reorth), nw = k - i0;
+  const int w = lane - i0;
+  cplx_d A{0.0, 0.0}, G{0.0, 0.0};
+  if (w >= 0 && w < nw) {
+    A = tot[2 * w];
+    G = tot[2 * w + 1];
+  }
+  const cplx_d akk = tot[2 * nw], x = tot[2 * nw + 1];
+  return step_scalars(s, r, k, a.m, a.reorth, a.tol, A, G, akk, x.re, x.im, nx);
+}
+
+// The arguments in registers after one wait: read where they are used, each
+// cache line of them costs the launch another trip to memory (L=13: 4 us of a call).
+__device__ __forceinline__ void hold_args(const StepArgs& a) {
+  asm volatile("" ::"s"(a.hv.L), "s"(a.hv.hc_kind), "s"(a.hv.hc_bit), "s"(a.hv.sz_count),
+               "s"(a.hv.sz_mask), "s"(a.hv.half_J), "s"(a.hv.c_zz), "s"(a.hv.u_ptr), "s"(a.hv.u_val),
+               "s"(a.geo.D), "s"(a.geo.TB), "s"(a.geo.ntiles), "s"(a.slot0), "s"(a.basis), "s"(a.y),
+               "s"(a.st), "s"(a.rows), "s"(a.k), "s"(a.m), "s"(a.reorth), "s"(a.tol));
+}
+
+// The previous step's rows: wavefront wv of nwv sums a share of them.  A lane
+// takes a pair of values (column); short rows go several to a load.  The
+// first loads are requested by the constructor and summed by sum(), so that
+// the tile's loads go out between the two.
+struct RowGather {
+  static constexpr uint32_t kFetch = 4;
+  const cplx_d* rows;
+  uint32_t G, nc, lg, rsub, first, step, col;
+  cplx_d v0[kFetch];
+
+  __device__ __forceinline__ void fetch(uint32_t c, uint32_t r0, cplx_d (&v)[kFetch]) const {
+#pragma unroll
+    for (uint32_t e = 0; e < kFetch; ++e)
+      v[e] = rows[min(r0 + e * step, G - 1u) * (uint32_t)kStepCols + min(c, nc - 1u)];
+  }
+  __device__ __forceinline__ void add(uint32_t r0, const cplx_d (&v)[kFetch], cplx_d& t) const {
+#pragma unroll
+    for (uint32_t e = 0; e < kFetch; ++e) {
+      const bool in = r0 + e * step < G;
+      t.re += in ? v[e].re : 0.0;
+      t.im += in ? v[e].im : 0.0;
+    }
+  }
+  __device__ __forceinline__ RowGather(const cplx_d* p, uint32_t rows_n, uint32_t cols, uint32_t wv,
+                                       uint32_t nwv)
+      : rows(p), G(rows_n), nc(cols) {
+    const uint32_t lane = threadIdx.x & 63u;
+    lg = nc <= 8 ? 3u : (nc <= 16 ? 4u : (nc <= 32 ? 5u : 6u));
+    rsub = lane >> lg;
+    step = nwv << (6u - lg);
+    first = (wv << (6u - lg)) + rsub;
+    col = lane & ((1u << lg) - 1u);
+    fetch(col, first, v0);
+  }
+  // totals of this wavefront's rows into part[0, nc)
+  __device__ __forceinline__ void sum(cplx_d* part) const {
+    cplx_d t{0.0, 0.0};
+    add(first, v0, t);
+    for (uint32_t r0 = first + kFetch * step; r0 < G + rsub; r0 += kFetch * step) {
+      cplx_d v[kFetch];
+      fetch(col, r0, v);
+      add(r0, v, t);
+    }
+    if (lg <= 3u) {
+      t.re += dpp_f64<0x128>(t.re);   // row_ror:8
+      t.im += dpp_f64<0x128>(t.im);
+    }
+    if (lg <= 4u) {
+      t.re += xor_lanes_16(t.re);
+      t.im += xor_lanes_16(t.im);
+    }
+    if (lg <= 5u) {
+      t.re += xor_lanes_32(t.re);
+      t.im += xor_lanes_32(t.im);
+    }
+    if (col < nc) part[col] = t;
+    for (uint32_t c = col + 64u; c < nc; c += 64u) {   // rows of more than 64 pairs
+      cplx_d q{0.0, 0.0};
+      for (uint32_t r0 = first; r0 < G; r0 += kFetch * step) {
+        cplx_d v[kFetch];
+        fetch(c, r0, v);
+        add(r0, v, q);
+      }
+      part[c] = q;
+    }
+  }
+};
+
+// The extra wavefront: the previous step's totals, the coefficients for the
+// others, and (in block 0) the scalars for the next launch.
+template <bool FIRST>
+__device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl, uint32_t G, uint32_t NW,
+                                                 cplx_d* part, cplx_d* tot, cplx_d* cf, StepNext* nxs,
+                                                 int* gos) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const int k = a.k;
+  StepState& ss = *a.st;
+  if constexpr (FIRST) {
+    cf[lane] = cplx_d{0.0, 0.0};
+    if (lane < 8u) cf[64 + lane] = cplx_d{0.0, 0.0};
+    if (lane == 0) {
+      *nxs = StepNext{cplx_d{0.0, 0.0}, 1.0, 1.0};
+      *gos = 1;
+    }
+    __syncthreads();
+    __syncthreads();
+    if (bl == 0 && lane == 0) ss.done = 0;
+    __syncthreads();
+    return;
+  }
+  LzLane s;
+  LzRun r;
+  const int ip = window_first(k - 1, a.m, a.reorth);
+  const uint32_t nc = 2u * (uint32_t)(k - 1 - ip) + 2u;
+  RowGather rg(a.rows + (size_t)((k - 1) & 1) * kStepRows * kStepCols, G, nc, NW, NW + 1u);
+  const int done = ss.done;
+  get_lane(ss.lz[(k - 1) & 1], s);
+  get_run(ss, (k - 1) & 1, r);
+  rg.sum(part + NW * kStepCols);
+  if (k == 1) {   // nothing kept yet
+    s = LzLane();
+    r = LzRun();
+  }
+  __syncthreads();
+  for (uint32_t col = lane; col < nc; col += 64u) {
+    double re = 0.0, im = 0.0;
+    for (uint32_t w0 = 0; w0 <= NW; w0 += 5) {
+      cplx_d v[5];
+#pragma unroll
+      for (uint32_t e = 0; e < 5; ++e) v[e] = part[min(w0 + e, NW) * kStepCols + col];
+#pragma unroll
+      for (uint32_t e = 0; e < 5; ++e) {
+        re += w0 + e <= NW ? v[e].re : 0.0;
+        im += w0 + e <= NW ? v[e].im : 0.0;
+      }
+    }
+    tot[col] = cplx_d{re, im};
+  }
+  wave_lds_fence();
+  StepNext nx{cplx_d{0.0, 0.0}, 1.0, 1.0};
+  const bool go = done == 0 && run_scalars(a, k - 1, tot, s, r, nx);
+  cf[lane] = s.cw;
+  if (lane < 8u) cf[64 + lane] = cplx_d{0.0, 0.0};
+  if (lane == 0) {
+    *nxs = nx;
+    *gos = go ? 1 : 0;
+  }
+  // the others go on; then the scalars are kept for the next launch
+  __syncthreads();
+  if (bl == 0) {
+    if (go) {
+      put_lane(ss.lz[k & 1], s);
+      if (lane == 0) {
+        const double v[5] = {r.normT, r.beta0, r.sk, r.rp, r.gp};
+#pragma unroll
+        for (int e = 0; e < 5; ++e) ss.run[k & 1][e] = v[e];
+      }
+    } else if (done == 0) {
+      put_lane(ss.fin, s);
+      if (lane == 0) {
+        ss.fin_beta0 = r.beta0;
+        ss.fin_m_eff = r.m_eff;
+        ss.done = 1;
+      }
+    }
+  }
+  if (go) __syncthreads();
+}
+
+// RAG: a vector shorter than its tile.  FIRST: step 0.  One tile per block.
+template <typename R, int RB, bool RAG, bool FIRST>
+__device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_t G) {
+  using V = typename VT<R>::T;
+  constexpr int NR = 1 << RB;
+  hold_args(a);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ cplx_d cf[kMaxM + 8];
+  __shared__ cplx_d tot[kStepCols];
+  __shared__ StepNext nxs;
+  __shared__ int gos;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wv = uniform_u32(threadIdx.x >> 6);
+  const Geo& g = a.geo;
+  const uint32_t NW = 1u << g.WB;
+  const uint32_t c = lane & 3u, aa = lane >> 2;
+  const uint32_t D = g.D;
+  const int k = FIRST ? 0 : a.k, m = a.m;
+  const bool last = k == m - 1;
+  const int i0 = window_first(k, m, a.reorth), nw = k - i0;
+  const uint32_t nv = 4u * (uint32_t)nw + 4u;                   // values of this step's row
+  V* lds = reinterpret_cast<V*>(smem_raw);
+  R* stage = reinterpret_cast<R*>(smem_raw + ((size_t)sizeof(V) << g.TB));
+  double* meas = reinterpret_cast<double*>(stage + NW * 256u);
+  cplx_d* part = reinterpret_cast<cplx_d*>(meas + NW * nv);
+  if (wv == NW) {
+    step_scalar_wave<FIRST>(a, bl, G, NW, part, tot, cf, &nxs, &gos);
+    return;
+  }
+  const int ip = window_first(FIRST ? 0 : k - 1, m, a.reorth);
+  const V* src = FIRST ? step_slot<const V>(a, 0) : step_slot<const V>(a, k + 1);
+  V* yb = reinterpret_cast<V*>(a.y);
+  const uint32_t tile = tile_of(g, 0, bl, G);
+  const uint32_t base = tile << g.TB;
+  const uint32_t sw = base | (wv << (6 + RB));                  // this wavefront's amplitudes
+  Tile<R, RB> T;
+  V up[NR], yp[NR];
+  V w0q[2][4];   // the first window vectors of the first unit, in flight beside the scalars
+  const auto load = [&](uint32_t s0, int w, V (&q)[4]) {
+    const V* p = step_slot<const V>(a, min(i0 + w, k - 1));
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t s = s0 | unit_amp(t, aa);
+      q[t] = RAG ? ld_masked(p, s, s < D) : p[s];
+    }
+  };
+  const double u = control_value(a.hv);
+  if constexpr (FIRST) {
+    hv_tile<R, RB, false, kStepFar>(T, a.hv, g, tile, src, lds, u);
+  } else {
+    RowGather rg(a.rows + (size_t)((k - 1) & 1) * kStepRows * kStepCols, G,
+                 2u * (uint32_t)(k - 1 - ip) + 2u, wv, NW + 1u);
+    load_slots<V, NR>(step_slot<const V>(a, k - 1), sw | lane, !RAG, D, up);
+    load_slots<V, NR>(yb, sw | lane, !RAG, D, yp);
+    hv_tile<R, RB, false, kStepFar>(T, a.hv, g, tile, src, lds, u, [&] {
+      if (nw > 0) {
+        load(sw, (int)c, w0q[0]);
+        load(sw, (int)c + 4, w0q[1]);
+      }
+      rg.sum(part + wv * kStepCols);
+    });
+  }
+  __syncthreads();
+  if (!gos) return;
+  const StepNext nx = nxs;
+  V* uk = FIRST ? nullptr : step_slot<V>(a, k);
+  V* wk = last ? nullptr : step_slot<V>(a, k + 2);
+  R* st = stage + wv * 256u;
+  double* row = meas + wv * nv;
+  double kr = 0.0, ki = 0.0, kk = 0.0, yy = 0.0;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const uint32_t s0 = sw | ((uint32_t)r << 6), sl = s0 | lane;
+    const bool in = !RAG || sl < D;
+    // u_k and y_k, rounded as stored
+    V uo, yo;
+    if constexpr (FIRST) {
+      uo = V{T.xr[r], T.xi[r]};
+      yo = V{T.yr[r], T.yi[r]};
+    } else {
+      uo.x = (R)(nx.sig * (double)T.xr[r] - (nx.c.re * (double)up[r].x - nx.c.im * (double)up[r].y));
+      uo.y = (R)(nx.sig * (double)T.xi[r] - (nx.c.re * (double)up[r].y + nx.c.im * (double)up[r].x));
+      yo.x = (R)(nx.sig * (double)T.yr[r] - (nx.c.re * (double)yp[r].x - nx.c.im * (double)yp[r].y));
+      yo.y = (R)(nx.sig * (double)T.yi[r] - (nx.c.re * (double)yp[r].y + nx.c.im * (double)yp[r].x));
+      if (in) uk[sl] = uo;
+    }
+    if (RAG && !in) uo = yo = V{(R)0, (R)0};
+    {
+      const double xr = uo.x, xi = uo.y, yr = yo.x, yi = yo.y;
+      kr += xr * yr + xi * yi;
+      ki += xr * yi - xi * yr;
+      kk += xr * xr + xi * xi;
+      yy += yr * yr + yi * yi;
+    }
+    if (last) continue;
+    if (in) yb[sl] = yo;
+    if (FIRST || nw == 0) {
+      if (in) wk[sl] = V{(R)(nx.s * (double)yo.x), (R)(nx.s * (double)yo.y)};
+      continue;
+    }
+    // ---- the window
+    if constexpr (sizeof(R) == 4) {
+      reinterpret_cast<float4*>(st)[lane] = float4{yo.x, yo.y, uo.x, uo.y};
+    } else {
+      reinterpret_cast<double2*>(st)[2 * lane] = double2{yo.x, yo.y};
+      reinterpret_cast<double2*>(st)[2 * lane + 1] = double2{uo.x, uo.y};
+    }
+    wave_lds_fence();
+    double b[4], bp[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      b[t] = (double)st[unit_amp(t, aa) * 4u + c];
+      bp[t] = turned(b[t]);
+    }
+    double zr[4] = {0.0, 0.0, 0.0, 0.0}, zi[4] = {0.0, 0.0, 0.0, 0.0};
+    // two groups of four vectors; the next ones are requested before these are used
+    V q[2][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      q[0][t] = w0q[0][t];
+      q[1][t] = w0q[1][t];
+    }
+    if (r > 0) {
+      load(s0, (int)c, q[0]);
+      load(s0, (int)c + 4, q[1]);
+    }
+    for (int w0 = 0; w0 < nw; w0 += 8) {
+      const bool two = w0 + 4 < nw, more = w0 + 8 < nw;
+      V n[2][4];
+      if (more) {
+        load(s0, w0 + 8 + (int)c, n[0]);
+        load(s0, w0 + 12 + (int)c, n[1]);
+      }
+      double e0 = 0.0, e1 = 0.0, f0 = 0.0, f1 = 0.0;
+      unit_rows(q[0], b, bp, cf[i0 + w0 + (int)c], zr, zi, e0, e1);
+      if (two) unit_rows(q[1], b, bp, cf[i0 + w0 + 4 + (int)c], zr, zi, f0, f1);
+      const auto put = [&](int w, double v) {
+        const double e = unit_dots(v);
+        if ((lane & 12u) == 0u && w < nw) {
+          double& d = row[4 * w + (int)c];
+          d = r == 0 ? e : d + e;
+        }
+      };
+      put(w0 + (int)(lane >> 4), e0 + e1);
+      if (two) put(w0 + 4 + (int)(lane >> 4), f0 + f1);
+      if (more) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          q[0][t] = n[0][t];
+          q[1][t] = n[1][t];
+        }
+      }
+    }
+    {
+      const uint32_t s = s0 | unit_amp((int)c, aa);
+      const R* o = st + unit_amp((int)c, aa) * 4u;
+      const double wr = nx.s * (double)o[0] - quad_z(zr), wi = nx.s * (double)o[1] - quad_z(zi);
+      if (!RAG || s < D) wk[s] = V{(R)wr, (R)wi};
+    }
+    wave_lds_fence();
+  }
+  // ---- this block's row of measurements
+  const double e4 = quad_sums_swap(kr, ki, kk, yy);
+  if (lane < 4u) row[4 * nw + (int)lane] = e4;
+  __syncthreads();
+  double* dst = reinterpret_cast<double*>(a.rows + ((size_t)(k & 1) * kStepRows + bl) * kStepCols);
+  for (uint32_t v = threadIdx.x; v < nv; v += NW * 64u) {
+    double e = 0.0;
+    for (uint32_t w0 = 0; w0 < NW; w0 += 4) {
+      double x[4];
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) x[q] = meas[min(w0 + q, NW - 1u) * nv + v];
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) e += w0 + q < NW ? x[q] : 0.0;
+    }
+    dst[v] = e;
+  }
+}
+
+// Blocks of up to four wavefronts of tile work (TH 320) get the registers of
+// two wavefronts per SIMD.
+template <typename R, int RB, bool RAG, int TH, bool FIRST>
+__global__ void __launch_bounds__(TH) k_step(StepBatch B) {
+  const uint32_t G = B.job[0].geo.grid;
+  const uint32_t j = blockIdx.x < G ? 0u : 1u;
+  step_body<R, RB, RAG, FIRST>(B.job[j], blockIdx.x - j * G, G);
+}
+
+constexpr int kCombBlock = 256;
+
+// v_out = sum_j d_j u_j (FP64 accumulation).  Every block first runs the last
+// step's scalars and the small exponential on wavefront 0 (a basis that ended
+// early has its own); four vectors per round trip after that.
+template <typename R>
+__global__ void __launch_bounds__(kCombBlock) k_step_combine(StepBatch B, uint32_t grid) {
+  using V = typename VT<R>::T;
+  __shared__ cplx_d tot[2];
+  __shared__ cplx_d cs[kMaxM];
+  __shared__ int mes;
+  const uint32_t j = blockIdx.x < grid ? 0u : 1u;
+  const StepArgs& a = B.job[j];
+  const uint32_t bl = blockIdx.x - j * grid, lane = threadIdx.x & 63u;
+  if (threadIdx.x < 64) {
+    const StepState& ss = *a.st;
+    const int k = a.m - 1;
+    LzLane s;
+    LzRun r;
+    const int done = k > 0 ? ss.done : 0;
+    if (k > 0) {
+      get_lane(ss.lz[k & 1], s);
+      get_run(ss, k & 1, r);
+    }
+    double e[4] = {0.0, 0.0, 0.0, 0.0};
+    const uint32_t G = a.geo.grid;
+    for (uint32_t q = lane; q < G; q += 64) {
+      const cplx_d* p = a.rows + ((size_t)(k & 1) * kStepRows + q) * kStepCols;
+      const cplx_d x = p[0], y = p[1];
+      e[0] += x.re;
+      e[1] += x.im;
+      e[2] += y.re;
+      e[3] += y.im;
+    }
+    if (done == 0) {
+      const cplx_d t0{wave_sum(e[0]), wave_sum(e[1])}, t1{wave_sum(e[2]), 0.0};
+      if (lane == 0) {
+        tot[0] = t0;
+        tot[1] = t1;
+      }
+      wave_lds_fence();
+      StepNext nx;
+      (void)run_scalars(a, k, tot, s, r, nx);
+    } else {
+      get_lane(ss.fin, s);
+      r.beta0 = ss.fin_beta0;
+      r.m_eff = ss.fin_m_eff;
+    }
+    cs[lane] = comb_coef(s, r, a.t);
+    if (lane == 0) {
+      mes = r.m_eff;
+      if (bl == 0 && a.m_eff_out) *a.m_eff_out = r.m_eff;
+    }
+  }
+  __syncthreads();
+  const int me = mes;
+  const uint32_t D = a.geo.D, stride = grid * kCombBlock;
+  V* out = reinterpret_cast<V*>(a.out);
+  for (uint32_t s0 = bl * kCombBlock + threadIdx.x; s0 < D; s0 += stride) {
+    double ar = 0.0, ai = 0.0;
+    for (int i0 = 0; i0 < me; i0 += 8) {
+      V v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = step_slot<const V>(a, min(i0 + e, me - 1))[s0];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (i0 + e < me) {
+          const cplx_d d = cs[i0 + e];
+          const double vr = v[e].x, vi = v[e].y;
+          ar += d.re * vr - d.im * vi;
+          ai += d.re * vi + d.im * vr;
+        }
+      }
+    }
+    out[s0] = V{(R)ar, (R)ai};
+  }
+}
+
+template <typename R, int RB>
+hipError_t launch_step_rb(const StepBatch& b, int n, size_t lds, hipStream_t s) {
+  const Geo& g = b.job[0].geo;
+  const dim3 grid(g.grid * n), block(64u * ((1u << g.WB) + 1u));
+  const bool first = b.job[0].k == 0;
+  const auto go = [&](auto zero, auto later) { kg_launch(first ? zero : later, grid, block, lds, s, b); };
+  if (g.small)
+    go(k_step<R, RB, true, 576, true>, k_step<R, RB, true, 576, false>);
+  else if (g.WB <= 2)
+    go(k_step<R, RB, false, 320, true>, k_step<R, RB, false, 320, false>);
+  else
+    go(k_step<R, RB, false, 576, true>, k_step<R, RB, false, 576, false>);
+  return hipGetLastError();
+}
+
+template <typename R>
+size_t step_lds(const Geo& g, int k, int m, int reorth) {
+  using V = typename VT<R>::T;
+  const size_t NW = (size_t)1 << g.WB;
+  const int i0 = k == m - 1 ? k : (reorth ? 0 : (k > 0 ? k - 1 : 0));
+  const size_t nv = (size_t)(4 * (k - i0) + 4);
+  return (sizeof(V) << g.TB) + NW * 256 * sizeof(R) + NW * nv * sizeof(double) +
+         (NW + 1) * kStepCols * sizeof(cplx_d);
+}
+
+template <typename R>
+hipError_t launch_krylov_steps_r(const KrylovCall* calls, const Workspace* const* wss, int n,
+                                 hipStream_t s) {
+  StepBatch b;
+  memset(static_cast<void*>(&b), 0, sizeof(b));
+  for (int j = 0; j < n; ++j) {
+    const KrylovCall& c = calls[j];
+    StepArgs& a = b.job[j];
+    a.hv = c.hv;
+    a.geo = c.step;
+    a.slot0 = c.v_in;
+    a.basis = wss[j]->basis;
+    a.y = wss[j]->yk;
+    a.rows = wss[j]->partials;
+    a.st = reinterpret_cast<StepState*>(wss[j]->partials + 2 * (size_t)kStepRows * kStepCols);
+    a.m = c.m;
+    a.reorth = c.reorth;
+    a.tol = c.tol;
+    a.t = c.t;
+    a.out = c.v_out;
+    a.m_eff_out = c.m_eff_out;
+  }
+  const Geo& g = b.job[0].geo;
+  hipError_t e = hipSuccess;
+  Profiler* prof = profiler_for_call();
+  const int m = calls[0].m;
+  const double vb = (double)g.D * sizeof(typename VT<R>::T) * n;
+  for (int k = 0; k < m; ++k) {
+    for (int j = 0; j < n; ++j) b.job[j].k = k;
+    if (prof) profiler_start(prof, s);
+    const size_t lds = step_lds<R>(g, k, calls[0].m, calls[0].reorth);
+    switch (g.RB) {
+      case 0: e = launch_step_rb<R, 0>(b, n, lds, s); break;
+      case 1: e = launch_step_rb<R, 1>(b, n, lds, s); break;
+      case 2: e = launch_step_rb<R, 2>(b, n, lds, s); break;
+      default: e = launch_step_rb<R, 3>(b, n, lds, s); break;
+    }
+    if (e != hipSuccess) return e;
+    // as a pass A (v_k read, y written but in the last step) and, before the
+    // last step, a pass B (y and the window read, v_{k+1} written)
+    const int i0 = k == m - 1 ? k : (calls[0].reorth ? 0 : (k > 0 ? k - 1 : 0));
+    if (prof && k < m - 1)
+      profiler_stop(prof, s, kProfPassA, 2 * vb, kProfPassB, (k - i0 + 3) * vb);
+    else if (prof)
+      profiler_stop(prof, s, kProfPassA, vb);
+  }
+  uint32_t grid = (g.D + kCombBlock - 1) / kCombBlock;
+  if (grid > 1024u) grid = 1024u;
+  if (prof) profiler_start(prof, s);
+  kg_launch(k_step_combine<R>, dim3(grid * n), dim3(kCombBlock), 0, s, b, grid);
+  e = hipGetLastError();
+  if (prof) profiler_stop(prof, s, kProfCombine, (m + 1) * vb);
+  return e;
+}
+
+}  // namespace
+
+static_assert(2 * kStepRows * kStepCols + (sizeof(StepState) + sizeof(cplx_d) - 1) / sizeof(cplx_d) <=
+                  (size_t)kPartialRows * kMaxScal,
+              "the rows and the scalars fit in the partials table");
+
+hipError_t launch_krylov_steps(const KrylovCall* calls, const Workspace* const* wss, int n,
+                               hipStream_t s) {
+  return calls[0].prec == 0 ? launch_krylov_steps_r<double>(calls, wss, n, s)
+                            : launch_krylov_steps_r<float>(calls, wss, n, s);
+}
+
+}  // namespace kg
