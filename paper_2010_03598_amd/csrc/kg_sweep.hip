@@ -21,7 +21,7 @@
 // Measured against one launch per call with two block-wide sums per step, in
 // complex128: the gradient of 50 slices at D = 256, m = 10 takes 1.14 ms
 // (2.88), the centred one of 584 slices at D = 146 13.9 ms (45.2), one call
-// alone at D = 256 25.9 us (29.5).  Of a step's 2.2 us the H v takes 0.3, the
+// alone at D = 256 25.6 us (29.5), at D = 512 and m = 12 39.6 us (42.0).  Of a step's 2.2 us the H v takes 0.3, the
 // rows and their MFMA 0.6, the sums over the wavefronts 0.3 and the scalars
 // 0.7.
 //
@@ -62,10 +62,16 @@ __host__ __device__ inline uint32_t slot_stride(uint32_t D) {
   return D + ((want + unit - (D % unit)) % unit);
 }
 
+// Rows per thread: one up to eight wavefronts; beyond, two (16 wavefronts of
+// one row would run four to a SIMD and repeat the per-wavefront work).  At
+// D = 512, m = 12, complex128: one row per thread 39.6 us, two on four
+// wavefronts 42.4.
+inline int sweep_rows(uint32_t D) { return D <= 2u * kRedThreads ? 1 : 2; }
+
 template <typename R>
 inline size_t sweep_lds_bytes(uint32_t D, int m) {
-  const size_t nw = (D + 63) / 64;
-  const size_t vecs = ((size_t)(m + 1) * slot_stride<R>(D) + nw * 64) * sizeof(typename VT<R>::T);
+  const size_t na = sweep_rows(D), nw = (D + 64 * na - 1) / (64 * na);
+  const size_t vecs = ((size_t)(m + 1) * slot_stride<R>(D) + na * nw * 64) * sizeof(typename VT<R>::T);
   const size_t meas = 2 * nw * (size_t)(4 * (m + 2)) * sizeof(double);
   const size_t coef = (nw <= kRedThreads / 64 ? nw : 1) * 2 * (kMaxM + 8) * sizeof(cplx_d);
   return ((vecs + 15) / 16) * 16 + meas + coef + 64;
@@ -91,21 +97,22 @@ __device__ __forceinline__ V* sweep_out(const SweepJob& J, int q, int j) {
   return reinterpret_cast<V*>(J.out + at * J.vb);
 }
 
-// TH: largest block.  RED: every wavefront computes the scalars.
-template <typename R, int TH, bool RED>
+// NA: rows per thread, blockDim apart.  TH: largest block.  RED: every
+// wavefront computes the scalars.  PE: the reduced basis.
+template <typename R, int NA, int TH, bool RED, bool PE>
 __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
   using V = typename VT<R>::T;
   const SweepJob& J = Bt.job[blockIdx.x];
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const uint32_t tid = threadIdx.x, lane = tid & 63u;
-  const uint32_t wv = uniform_u32(tid >> 6), nwv = blockDim.x >> 6;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, T = blockDim.x;
+  const uint32_t wv = uniform_u32(tid >> 6), nwv = T >> 6;
   const uint32_t c = lane & 3u, a = lane >> 2;
   const uint32_t D = J.D, DS = slot_stride<R>(D);
   const int m = J.m;
   V* ub = reinterpret_cast<V*>(smem_raw);
   V* yst = ub + (size_t)(m + 1) * DS;
-  double* wred = reinterpret_cast<double*>(
-      smem_raw + ((((size_t)(m + 1) * DS + nwv * 64u) * sizeof(V) + 15) / 16) * 16);
+  const uint32_t vecs = (uint32_t)(m + 1) * DS + NA * T;
+  double* wred = reinterpret_cast<double*>(smem_raw + (((size_t)vecs * sizeof(V) + 15) / 16) * 16);
   const uint32_t rowlen = 4u * (uint32_t)(m + 2);
   cplx_d* cfs = reinterpret_cast<cplx_d*>(wred + 2 * nwv * rowlen) + (RED ? wv * 2u * (kMaxM + 8) : 0u);
   cplx_d* dcs = cfs + kMaxM + 8;
@@ -119,46 +126,57 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
   __shared__ Shared sh;
 
   // rows past D (and the padding that whole units read) stay finite
-  for (uint32_t i = tid; i < (uint32_t)(m + 1) * DS + nwv * 64u; i += blockDim.x) ub[i] = V{(R)0, (R)0};
+  if (D != NA * T)
+    for (uint32_t i = tid; i < vecs; i += T) ub[i] = V{(R)0, (R)0};
   if (RED || wv == 0) {
     cfs[lane] = cplx_d{0.0, 0.0};
     if (lane < 8u) cfs[64 + lane] = cplx_d{0.0, 0.0};
   }
 
-  // this thread's row: diagonal d0 + u dz, neighbours and their weights
-  const bool in = tid < D;
-  const uint32_t row = in ? tid : 0u;
+  // this thread's rows: diagonal d0 + u dz, neighbours and their weights
   const int L = J.hv.L;
-  uint32_t nb[kSweepNbr];
-  R wt[kSweepNbr];
-  R d0 = (R)0, dz = (R)0;
-  int slots = 0;
-  bool bad = false;
+  const bool sx = J.hv.hc_kind == 0;
+  const int slots = J.nbr;
+  uint32_t nb[NA][kSweepNbr], flip[NA];
+  R wt[NA][kSweepNbr], d0[NA], dz[NA];
+  bool in[NA];
+  uint32_t row[NA];
 #pragma unroll
-  for (int i = 0; i < kSweepNbr; ++i) {
-    nb[i] = row;
-    wt[i] = (R)0;
-  }
-  {
-    const R hJ = (R)J.hv.half_J;
-    const uint32_t bondmask = (L >= 2) ? ((1u << (L - 1)) - 1u) : 0u;
-    const uint32_t r = J.has_pe ? J.pe.reps[row] : row;
-    const uint32_t anti = (r ^ (r >> 1)) & bondmask;
-    d0 = (R)J.hv.c_zz * (R)(L - 1 - 2 * (int)__popc(anti));
-    if (J.hv.hc_kind == 1) dz = (R)(0.5 * J.hv.sz_count) - (R)__popc(r & J.hv.sz_mask);
-    slots = J.nbr;
-    uint32_t act = anti;
-    const uint32_t full = (L == 32) ? 0xFFFFFFFFu : ((1u << L) - 1u);
-    const uint32_t rank = J.has_pe ? J.pe.ranks[row] : 0u;
-    const bool nb2 = J.has_pe && (__brev(r) >> (32 - L)) != r;
-    if (J.has_pe) bad = rank >= J.pe.nsec;
+  for (int n = 0; n < NA; ++n) {
+    in[n] = tid + n * T < D;
+    row[n] = in[n] ? tid + n * T : 0u;
+    dz[n] = (R)0;
 #pragma unroll
     for (int i = 0; i < kSweepNbr; ++i) {
-      if (i < slots && act && !bad) {
-        const int q = __builtin_ctz(act);
-        act &= act - 1u;
-        const uint32_t s2 = r ^ (3u << q);
-        if (J.has_pe) {
+      nb[n][i] = row[n];
+      wt[n][i] = (R)0;
+    }
+    const R hJ = (R)J.hv.half_J;
+    const uint32_t bondmask = (L >= 2) ? ((1u << (L - 1)) - 1u) : 0u;
+    const uint32_t r = PE ? J.pe.reps[row[n]] : row[n];
+    const uint32_t anti = (r ^ (r >> 1)) & bondmask;
+    d0[n] = (R)J.hv.c_zz * (R)(L - 1 - 2 * (int)__popc(anti));
+    if (!sx) dz[n] = (R)(0.5 * J.hv.sz_count) - (R)__popc(r & J.hv.sz_mask);
+    if constexpr (!PE) {
+#pragma unroll
+      for (int i = 0; i < kSweepNbr; ++i) {
+        if ((anti >> i) & 1u) {
+          nb[n][i] = r ^ (3u << i);
+          wt[n][i] = hJ;
+        }
+      }
+    } else {
+      uint32_t act = anti;
+      const uint32_t full = (L == 32) ? 0xFFFFFFFFu : ((1u << L) - 1u);
+      const uint32_t rank = J.pe.ranks[row[n]];
+      const bool nb2 = (__brev(r) >> (32 - L)) != r;
+      bool bad = rank >= J.pe.nsec;
+#pragma unroll
+      for (int i = 0; i < kSweepNbr; ++i) {
+        if (i < slots && act && !bad) {
+          const int q = __builtin_ctz(act);
+          act &= act - 1u;
+          const uint32_t s2 = r ^ (3u << q);
           // the orbit through the combinatorial rank over the zero bits
           const uint32_t dl = J.pe.binom[q * kPeBinom + __popc(~r & full & ((1u << q) - 1u))];
           const uint32_t rk = (((r >> q) & 1u) == 0u) ? rank + dl : rank - dl;
@@ -166,117 +184,135 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
           const bool ok = (uint32_t)ai < D;
           bad = bad || !ok;
           const bool na2 = (__brev(s2) >> (32 - L)) != s2;
-          nb[i] = ok ? (uint32_t)ai : row;
-          wt[i] = hJ * ((nb2 == na2) ? (R)1 : (nb2 ? (R)1.4142135623730951 : (R)0.70710678118654752));
-        } else {
-          nb[i] = s2;
-          wt[i] = hJ;
+          nb[n][i] = ok ? (uint32_t)ai : row[n];
+          wt[n][i] = hJ * ((nb2 == na2) ? (R)1 : (nb2 ? (R)1.4142135623730951 : (R)0.70710678118654752));
         }
       }
+      // a table entry out of range turns the row into NaN, never a stray read
+      if (bad) d0[n] = (R)NAN;
     }
-    // a table entry out of range turns the row into NaN, never a stray read
-    if (bad) d0 = (R)NAN;
-    if (!in) {
-      d0 = dz = (R)0;
+    if (!in[n]) {
+      d0[n] = dz[n] = (R)0;
 #pragma unroll
-      for (int i = 0; i < kSweepNbr; ++i) wt[i] = (R)0;
+      for (int i = 0; i < kSweepNbr; ++i) wt[n][i] = (R)0;
     }
+    flip[n] = sx ? (row[n] ^ (1u << J.hv.hc_bit)) : row[n];
   }
-  const bool sx = J.hv.hc_kind == 0;
-  const uint32_t flip = sx ? (row ^ (1u << J.hv.hc_bit)) : row;
 
-  V xin = in ? reinterpret_cast<const V*>(J.in)[row] : V{(R)0, (R)0};
+  V xin[NA];
+#pragma unroll
+  for (int n = 0; n < NA; ++n)
+    xin[n] = in[n] ? reinterpret_cast<const V*>(J.in)[row[n]] : V{(R)0, (R)0};
   uint32_t par = 0;
   double unext = J.u ? J.u[J.j0 - 1] : J.hv.u_val;
   for (int q = 0; q < J.n; ++q) {
     const int j = J.j0 + q * J.dj;
     const double u = unext;
     if (J.u && q + 1 < J.n) unext = J.u[j + J.dj - 1];
-    const R diag = d0 + (R)u * dz;
     const R cu = sx ? (R)(0.5 * u) : (R)0;
     LzLane s;
     LzRun run;
     StepNext nx{cplx_d{0.0, 0.0}, 1.0, 1.0};
-    if (in) ub[row] = xin;
+#pragma unroll
+    for (int n = 0; n < NA; ++n)
+      if (in[n]) ub[row[n]] = xin[n];
     if (RED || wv == 0) cfs[lane] = cplx_d{lane == 1u ? -1.0 : 0.0, 0.0};   // y of step 0
     if constexpr (!RED) {
       if (wv == 0) put_lane(sh.lz, s);
     }
     __syncthreads();
-    V up{(R)0, (R)0}, yp{(R)0, (R)0};
+    V up[NA], yp[NA];
     for (int k = 0; k < m; ++k) {
       const bool last = k == m - 1;
       const int i0 = window_first(k, m, J.reorth), nw = k - i0;
       V* uk = ub + (size_t)k * DS;
-      // ---- H v of the source on this row, in the vector type
       const V* src = k == 0 ? ub : ub + (size_t)(k + 1) * DS;
-      const V xs = src[row];
-      R hr = diag * xs.x, hi = diag * xs.y;
-      const V xf = src[flip];
-      // four neighbours' reads in flight together; unused slots have weight 0
 #pragma unroll
-      for (int i = 0; i < kSweepNbr; i += 4) {
-        if (i < slots) {
-          V x[4];
+      for (int n = 0; n < NA; ++n) {
+        // ---- H v of the source on this row, in the vector type
+        const V xs = src[row[n]], xf = src[flip[n]];
+        const R diag = d0[n] + (R)u * dz[n];
+        R hr = diag * xs.x, hi = diag * xs.y;
+        // four neighbours' reads in flight together; unused slots have weight 0
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = src[nb[i + e]];
+        for (int i = 0; i < kSweepNbr; i += 4) {
+          if (i < slots) {
+            V x[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            hr += wt[i + e] * x[e].x;
-            hi += wt[i + e] * x[e].y;
+            for (int e = 0; e < 4; ++e) x[e] = src[nb[n][i + e]];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              hr += wt[n][i + e] * x[e].x;
+              hi += wt[n][i + e] * x[e].y;
+            }
           }
         }
+        hr += cu * xf.x;
+        hi += cu * xf.y;
+        // ---- u_k and y_k, rounded as stored
+        V uo, yo;
+        if (k == 0) {
+          uo = xs;
+          yo.x = hr;
+          yo.y = hi;
+        } else {
+          const double sg = nx.sig;
+          uo.x = (R)(sg * (double)xs.x - (nx.c.re * (double)up[n].x - nx.c.im * (double)up[n].y));
+          uo.y = (R)(sg * (double)xs.y - (nx.c.re * (double)up[n].y + nx.c.im * (double)up[n].x));
+          yo.x = (R)(sg * (double)hr - (nx.c.re * (double)yp[n].x - nx.c.im * (double)yp[n].y));
+          yo.y = (R)(sg * (double)hi - (nx.c.re * (double)yp[n].y + nx.c.im * (double)yp[n].x));
+          if (in[n]) uk[row[n]] = uo;
+        }
+        if (!in[n]) uo = yo = V{(R)0, (R)0};
+        yst[tid + n * T] = yo;
+        up[n] = uo;
+        yp[n] = yo;
       }
-      hr += cu * xf.x;
-      hi += cu * xf.y;
-      // ---- u_k and y_k, rounded as stored
-      V uo, yo;
-      if (k == 0) {
-        uo = xs;
-        yo.x = hr;
-        yo.y = hi;
-      } else {
-        const double sg = nx.sig;
-        uo.x = (R)(sg * (double)xs.x - (nx.c.re * (double)up.x - nx.c.im * (double)up.y));
-        uo.y = (R)(sg * (double)xs.y - (nx.c.re * (double)up.y + nx.c.im * (double)up.x));
-        yo.x = (R)(sg * (double)hr - (nx.c.re * (double)yp.x - nx.c.im * (double)yp.y));
-        yo.y = (R)(sg * (double)hi - (nx.c.re * (double)yp.y + nx.c.im * (double)yp.x));
-        if (in) uk[row] = uo;
-      }
-      if (!in) uo = yo = V{(R)0, (R)0};
-      yst[tid] = yo;
-      up = uo;
-      yp = yo;
       wave_lds_fence();
-      // ---- rows [i0, k), u_k, y_k against (y_k, u_k)
-      const uint32_t s0 = wv << 6;
-      double b[4], bp[4];
-      {
+      // ---- rows [i0, k), u_k, y_k against (y_k, u_k), a unit of 64 per n
+      double b[NA][4], bp[NA][4];
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
         const V* src2 = c < 2u ? yst : uk;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          const uint32_t s = s0 + unit_amp(t, a);
-          const R v = reinterpret_cast<const R*>(src2 + s)[c & 1u];
-          b[t] = s < D ? (double)v : 0.0;
-          bp[t] = turned(b[t]);
+          const uint32_t sa = ((wv + nwv * n) << 6) + unit_amp(t, a);
+          const R v = reinterpret_cast<const R*>(src2 + sa)[c & 1u];
+          b[n][t] = sa < D ? (double)v : 0.0;
+          bp[n][t] = turned(b[n][t]);
         }
       }
       const int nrows = nw + (last ? 1 : 2);
-      double zr[4] = {0.0, 0.0, 0.0, 0.0}, zi[4] = {0.0, 0.0, 0.0, 0.0};
+      double zr[NA][4], zi[NA][4];
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) zr[n][t] = zi[n][t] = 0.0;
+      }
       double* wrow = wred + (par * nwv + wv) * rowlen;
       for (int r0 = 0; r0 < nrows; r0 += 8) {
-        V q0[4], q1[4];
         const bool two = r0 + 4 < nrows;
-        const auto rows = [&](int r, V (&o)[4]) {
-          const V* p = r < nw ? ub + (size_t)(i0 + r) * DS : (r == nw ? uk : yst);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) o[t] = p[s0 + unit_amp(t, a)];
+        const auto at = [&](int r) {
+          return r < nw ? ub + (size_t)(i0 + r) * DS : (r == nw ? uk : yst);
         };
-        rows(r0 + (int)c, q0);
-        if (two) rows(r0 + 4 + (int)c, q1);
+        const V* p0 = at(r0 + (int)c);
+        const V* p1 = at(r0 + 4 + (int)c);
+        const cplx_d w0 = cfs[min(i0 + r0 + (int)c, kMaxM + 7)];
+        const cplx_d w1 = cfs[min(i0 + r0 + 4 + (int)c, kMaxM + 7)];
         double e0 = 0.0, e1 = 0.0, f0 = 0.0, f1 = 0.0;
-        unit_rows(q0, b, bp, cfs[min(i0 + r0 + (int)c, kMaxM + 7)], zr, zi, e0, e1);
-        if (two) unit_rows(q1, b, bp, cfs[min(i0 + r0 + 4 + (int)c, kMaxM + 7)], zr, zi, f0, f1);
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          const uint32_t s0 = (wv + nwv * n) << 6;
+          V q0[4], q1[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) q0[t] = p0[s0 + unit_amp(t, a)];
+          if (two) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) q1[t] = p1[s0 + unit_amp(t, a)];
+          }
+          unit_rows(q0, b[n], bp[n], w0, zr[n], zi[n], e0, e1);
+          if (two) unit_rows(q1, b[n], bp[n], w1, zr[n], zi[n], f0, f1);
+        }
         const int r = r0 + (int)(lane >> 4);
         const double e = unit_dots(e0 + e1);
         if ((lane & 12u) == 0u && r < nrows) wrow[4 * r + (int)c] = e;
@@ -286,9 +322,12 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
         }
       }
       if (!last) {
-        const uint32_t s = s0 + unit_amp((int)c, a);
-        const double wr = -quad_z(zr), wi = -quad_z(zi);
-        if (s < D) ub[(size_t)(k + 2) * DS + s] = V{(R)wr, (R)wi};
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          const uint32_t sa = ((wv + nwv * n) << 6) + unit_amp((int)c, a);
+          const double wr = -quad_z(zr[n]), wi = -quad_z(zi[n]);
+          if (sa < D) ub[(size_t)(k + 2) * DS + sa] = V{(R)wr, (R)wi};
+        }
       }
       __syncthreads();
       // ---- totals over the wavefronts, in order, and the scalars
@@ -370,22 +409,30 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
       __syncthreads();
     }
     const int me = run.m_eff;
-    double orr = 0.0, oi = 0.0;
+    double orr[NA], oi[NA];
+#pragma unroll
+    for (int n = 0; n < NA; ++n) orr[n] = oi[n] = 0.0;
 #pragma unroll 4
     for (int i = 0; i < me; ++i) {
       const cplx_d d = dcs[i];
-      const V x = ub[(size_t)i * DS + row];
-      orr += d.re * x.x - d.im * x.y;
-      oi += d.re * x.y + d.im * x.x;
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+        const V x = ub[(size_t)i * DS + row[n]];
+        orr[n] += d.re * x.x - d.im * x.y;
+        oi[n] += d.re * x.y + d.im * x.x;
+      }
     }
-    xin.x = in ? (R)orr : (R)0;
-    xin.y = in ? (R)oi : (R)0;
-    if (in) sweep_out<V>(J, q, j)[row] = xin;
+#pragma unroll
+    for (int n = 0; n < NA; ++n) {
+      xin[n].x = in[n] ? (R)orr[n] : (R)0;
+      xin[n].y = in[n] ? (R)oi[n] : (R)0;
+      if (in[n]) sweep_out<V>(J, q, j)[row[n]] = xin[n];
+    }
     if (J.m_eff_out && tid == 0) *J.m_eff_out = me;
   }
 }
 
-template <typename R, int TH, bool RED>
+template <typename R, int NA, int TH, bool RED, bool PE>
 hipError_t launch_sweep_t(const SweepBatch& b, int n, size_t lds, uint32_t threads, hipStream_t s) {
   // the basis exceeds the default 64 KiB of dynamic LDS: raise the limit of
   // this kernel once per device
@@ -395,22 +442,26 @@ hipError_t launch_sweep_t(const SweepBatch& b, int n, size_t lds, uint32_t threa
   if (e != hipSuccess) return e;
   const uint64_t bit = (dev < 64) ? (1ull << dev) : 0ull;
   if (!bit || !(raised.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep<R, TH, RED>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep<R, NA, TH, RED, PE>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(kSweepLds - kSweepStatic));
     if (e != hipSuccess) return e;
     raised.fetch_or(bit, std::memory_order_acq_rel);
   }
-  hipLaunchKernelGGL((k_sweep<R, TH, RED>), dim3(n), dim3(threads), lds, s, b);
+  hipLaunchKernelGGL((k_sweep<R, NA, TH, RED, PE>), dim3(n), dim3(threads), lds, s, b);
   return hipGetLastError();
 }
 
-template <typename R>
+template <typename R, bool PE>
 hipError_t launch_sweep_r(const SweepBatch& b, int n, hipStream_t s) {
-  const uint32_t D = b.job[0].D, threads = (D + 63u) / 64u * 64u;
+  const uint32_t D = b.job[0].D;
+  const int na = sweep_rows(D);
+  const uint32_t threads = (D + 64u * na - 1u) / (64u * na) * 64u;
   const size_t lds = sweep_lds_bytes<R>(D, b.job[0].m);
-  return threads <= (uint32_t)kRedThreads ? launch_sweep_t<R, kRedThreads, true>(b, n, lds, threads, s)
-                                          : launch_sweep_t<R, 1024, false>(b, n, lds, threads, s);
+  if (threads <= (uint32_t)kRedThreads && na == 1)
+    return launch_sweep_t<R, 1, kRedThreads, true, PE>(b, n, lds, threads, s);
+  if (na == 1) return launch_sweep_t<R, 1, 2 * kRedThreads, false, PE>(b, n, lds, threads, s);
+  return launch_sweep_t<R, 2, 2 * kRedThreads, false, PE>(b, n, lds, threads, s);
 }
 
 // The brackets of a run of slices, one block each: block b takes slice
@@ -517,7 +568,10 @@ hipError_t launch_sweeps(int prec, const SweepJob* jobs, int n, hipStream_t s) {
   for (int at = 0; at < n; at += kSweepJobs) {
     const int cnt = n - at < kSweepJobs ? n - at : kSweepJobs;
     for (int i = 0; i < cnt; ++i) b.job[i] = jobs[at + i];
-    const hipError_t e = prec == 0 ? launch_sweep_r<double>(b, cnt, s) : launch_sweep_r<float>(b, cnt, s);
+    const bool pe = b.job[0].has_pe != 0;
+    const hipError_t e =
+        prec == 0 ? (pe ? launch_sweep_r<double, true>(b, cnt, s) : launch_sweep_r<double, false>(b, cnt, s))
+                  : (pe ? launch_sweep_r<float, true>(b, cnt, s) : launch_sweep_r<float, false>(b, cnt, s));
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
