@@ -146,8 +146,8 @@ size_t slot_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec) {
 
 // workspace of vectors of D amplitudes; `extended` adds the two node vectors
 size_t ws_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec, bool extended) {
-  return 2 * slot_bytes_d(D, k, prec) + align_up(vbytes(D, prec), 256) +
-         (extended ? 2 * align_up(vbytes(D, prec), 256) : 0);
+  const size_t vb = align_up(vbytes(D, prec), 256);
+  return 2 * slot_bytes_d(D, k, prec) + vb + (D <= kPairMaxD ? vb : 0) + (extended ? 2 * vb : 0);
 }
 
 // The workspace holds two Krylov slots (scalars, reduction partials, m-1
@@ -186,8 +186,16 @@ kg_status carve_d(void* ws, size_t ws_bytes, uint64_t D, const kg_krylov* k, int
     q += basis_bytes_d(D, k, prec);
     o->yk = q;
     o->lam = p + 2 * slot_bytes_d(D, k, prec);
-    o->node_a = extended ? static_cast<char*>(o->lam) + vb : nullptr;
-    o->node_b = extended ? static_cast<char*>(o->lam) + 2 * vb : nullptr;
+    char* after = static_cast<char*>(o->lam) + vb;
+    o->tmp = D <= kPairMaxD ? after : nullptr;
+    if (o->tmp) after += vb;
+    o->node_a = extended ? after : nullptr;
+    o->node_b = extended ? after + vb : nullptr;
+    // past the rows of the steps and the measurement columns of m's windows,
+    // before the last columns
+    const size_t raw_at = std::max(step_table_pairs(), 2 * (size_t)k->m * kPartialRows);
+    o->raw = o->partials + raw_at;
+    o->raw_len = (int64_t)(2 * kMaxM * kPartialRows) - (int64_t)raw_at;
   }
   return KG_OK;
 }
@@ -418,6 +426,108 @@ const SideStream* side_stream(hipStream_t caller) {
   return &r;
 }
 
+// Both sweeps of a store-all gradient side by side.  The costates need nothing
+// of the forward sweep (lambda_N is the target; beta only scales the brackets
+// at the end), so they run on the second stream while psi moves forward.  In
+// the first half each sweep fills its own end of the state buffer; in the
+// second each meets what the other stored: psi_j is formed beside lambda_j in
+// its slot, the bracket is taken and psi_j replaces lambda_j, and lambda_j
+// meets psi_j.  One sweep's launches leave the chip mostly waiting for small
+// vectors, and its launch tails uncovered for large ones.  Timed store-all
+// gradients (60 slices, m = 16), one sweep after the other against side by
+// side: L=11 complex64 11.4 -> 6.1 ms and L=15 14.2 -> 7.7 in the same
+// launches; on two streams L=16 16.6 -> 10.1 (complex128 17.5 -> 12.9, in the
+// same launches 14.5), L=18 12.5 -> 10.6 (30 slices), L=20 17.7 -> 14.3 (20),
+// L=22 23.9 -> 21.9 (8); hence shared launches up to 2^15.
+// Raw brackets go to raw[0, N) (raw[N]: the one at the start of slice 1).
+// `side` nullptr: both sweeps in the same launches.
+kg_status paired_sweeps(const SweepArgs& a, const States& S, const SideStream* side, bool centred,
+                        cplx_d* raw) {
+  const HvArgs hc = make_hv(a.h, nullptr, 0.0);
+  const uint32_t* reps = a.pe ? a.pe->reps : nullptr;
+  const int N = a.N, h = N / 2;
+  const auto meet = [&](hipEvent_t e, hipStream_t from, hipStream_t to) {
+    const hipError_t r = hipEventRecord(e, from);
+    return r != hipSuccess ? r : hipStreamWaitEvent(to, e, 0);
+  };
+  const auto lam_at = [&](int j) { return j == N ? a.target : (const void*)S.at(j); };
+  // a forward and a costate call (either may be missing)
+  const auto calls = [&](const KrylovCall* f, const KrylovCall* b) {
+    if (!side && f && b) return launch_krylov_pair(*f, a.ws, *b, a.ws1, a.stream);
+    hipError_t e = f ? launch_krylov(*f, a.ws, a.stream) : hipSuccess;
+    if (e == hipSuccess && b) e = launch_krylov(*b, a.ws1, side ? side->s : a.stream);
+    return e;
+  };
+  const auto brackets = [&](const RawBracket* f, const RawBracket* b) {
+    if (!side && f && b) {
+      const RawBracket two[2] = {*f, *b};
+      return launch_bracket_raw(a.prec, hc, a.geo.D, two, 2, a.stream, reps);
+    }
+    hipError_t e = f ? launch_bracket_raw(a.prec, hc, a.geo.D, f, 1, a.stream, reps) : hipSuccess;
+    if (e == hipSuccess && b)
+      e = launch_bracket_raw(a.prec, hc, a.geo.D, b, 1, side ? side->s : a.stream, reps);
+    return e;
+  };
+  if (side) KG_HIP(meet(side->fork, a.stream, side->s), "paired sweeps");
+  // first half: psi_1..psi_h, and lambda_{N-1}..lambda_h (the last one aside)
+  for (int i = 1; i <= N - h; ++i) {
+    const int j = N - i;   // lambda_j from slice j + 1
+    const KrylovCall f = krylov_call(a, std::min(i, h), a.dt, S.at0(std::min(i, h) - 1), S.at(std::min(i, h)));
+    const KrylovCall b = krylov_call(a, j + 1, -a.dt, lam_at(j + 1), j == h ? a.ws.lam : S.at(j));
+    KG_HIP(calls(i <= h ? &f : nullptr, &b), "paired sweeps");
+  }
+  if (side) {
+    KG_HIP(meet(side->join, side->s, a.stream), "paired sweeps");
+    KG_HIP(meet(side->fork, a.stream, side->s), "paired sweeps");
+  }
+  // second half: psi_{h+1}..psi_N meet the stored costates, and lambda_h, ... (in
+  // ws.lam) the stored states.  psi_j's bracket follows its call, lambda_j's
+  // comes before the next one.
+  for (int i = 1; i <= N - h + 1; ++i) {
+    const int jf = h + i, jb = h + 1 - i;
+    RawBracket rf{}, rb{};
+    const bool met = i > 1, back = jb > 0 || (jb == 0 && centred);
+    if (met) rf = RawBracket{lam_at(jf - 1), a.ws.tmp, S.at(jf - 1), a.ws.st, a.ws.partials, raw + (jf - 2)};
+    if (back)
+      rb = RawBracket{a.ws.lam, S.at0(jb), nullptr, a.ws1.st, a.ws1.partials, jb > 0 ? raw + (jb - 1) : raw + N};
+    KG_HIP(brackets(met ? &rf : nullptr, back ? &rb : nullptr), "paired brackets");
+    KrylovCall f, b;
+    const bool more_f = jf <= N, more_b = jb > 1 || (jb == 1 && centred);
+    if (more_f) f = krylov_call(a, jf, a.dt, S.at0(jf - 1), a.ws.tmp);
+    if (more_b) b = krylov_call(a, jb, -a.dt, a.ws.lam, a.ws.lam);
+    KG_HIP(calls(more_f ? &f : nullptr, more_b ? &b : nullptr), "paired sweeps");
+  }
+  if (side) KG_HIP(meet(side->join, side->s, a.stream), "paired sweeps");
+  return KG_OK;
+}
+
+// Whether a store-all gradient takes paired_sweeps (with that many chains' raw
+// brackets); *side is its second stream, or nullptr for shared launches.  A
+// profile times one kernel at a time, and KG_ONE_STREAM keeps one sweep after
+// the other.
+bool take_pairs(const SweepArgs& a, const States& S, int chains, const SideStream** side) {
+  *side = nullptr;
+  if (S.c != 0 || a.N < 2 || !a.ws.tmp || profiling() || getenv("KG_ONE_STREAM")) return false;
+  if ((int64_t)chains * (a.N + 1) > a.ws.raw_len) return false;
+  if (a.geo.D <= kPairLaunchMaxD) return true;
+  *side = side_stream(a.stream);
+  return *side != nullptr;
+}
+
+// The gradient from a chain's raw brackets.
+kg_status paired_gradient(const SweepArgs& a, const cplx_d* raw, const double* beta_dev, double* grad_dev,
+                          bool centred, int col, int ncols) {
+  const double c = a.dt / ncols;
+  KG_HIP(launch_scale_brackets(raw, a.N, c, beta_dev, grad_dev, col > 0, a.stream), "gradient brackets");
+  if (centred) {
+    KG_HIP(launch_scale_brackets(raw + a.N, 1, c, beta_dev, &a.ws.st->g0, col > 0, a.stream),
+           "gradient bracket at t = 0");
+    if (col == ncols - 1)
+      KG_HIP(launch_centre(grad_dev, a.N, &a.ws.st->g0, a.stream), "centred gradient");
+  }
+  return KG_OK;
+}
+
 // Nodes of the in-slice quadrature: times s_q in (0, dt) and weights w_q.
 struct Quadrature {
   int n = 0;
@@ -603,6 +713,8 @@ Profiler* profiler_for_call() {
   const bool take = (g_prof->calls++ % g_prof->sample_every) == 0;
   return take ? g_prof : nullptr;
 }
+
+bool profiling() { return g_prof != nullptr; }
 
 Profiler* profiler_for_launch() {
   if (!g_prof) return nullptr;
@@ -844,6 +956,13 @@ kg_status gradient_core(const kg_xxz* h, const Space& sp, const double* u_dev, i
   }
   KG_HIP(launch_init(W.st, a.stream), name);
   KG_HIP(launch_init(W1.st, a.stream), name);
+  const SideStream* side = nullptr;
+  if (!states_valid && !Q && !first_order && take_pairs(a, S, 1, &side)) {
+    KG_CHECK(paired_sweeps(a, S, side, centred, a.ws.raw));
+    KG_CHECK(launch_overlap_of(a, S, F_dev, beta_dev));
+    KG_CHECK(paired_gradient(a, a.ws.raw, beta_dev, grad_dev, centred, 0, 1));
+    return ok();
+  }
   if (!states_valid) KG_CHECK(forward_sweep(a, S, F_dev, beta_dev));
   KG_CHECK(backward_sweep(a, S, beta_dev, grad_dev, centred, Q, first_order));
   return ok();
@@ -1408,6 +1527,21 @@ kg_status columns_core(const kg_xxz* h, const Space& sp, const double* u_dev, in
       jobs.push_back(chain_job(a, col_states(c), 1, 1, N, dt, a.psi0, nullptr));
     }
     KG_HIP(launch_sweeps(prec, jobs.data(), n_cols, s), "column forward sweeps");
+  }
+  const SideStream* side = nullptr;
+  if (!short_v && take_pairs(col_args(0, W, W1), col_states(0), n_cols, &side)) {
+    for (int c = 0; c < n_cols; ++c) {
+      const SweepArgs a = col_args(c, W, W1);
+      const States S = col_states(c);
+      KG_CHECK(paired_sweeps(a, S, side, centred != 0, W.raw + (size_t)c * (N + 1)));
+      KG_HIP(launch_overlap(prec, sp.geo.D, a.target, S.at(N), W, nullptr, beta_cols_dev + 2 * c, s),
+             "column overlap");
+    }
+    KG_HIP(launch_mean_overlap(beta_cols_dev, n_cols, beta_dev, F_dev, s), "mean overlap");
+    for (int c = 0; c < n_cols; ++c)
+      KG_CHECK(paired_gradient(col_args(c, W, W1), W.raw + (size_t)c * (N + 1), beta_dev, grad_dev,
+                               centred != 0, c, n_cols));
+    return ok();
   }
   for (int c = 0; c < n_cols; c += short_v ? 1 : 2) {
     const SweepArgs a0 = col_args(c, W, W1);

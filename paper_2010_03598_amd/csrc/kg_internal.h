@@ -108,6 +108,9 @@ struct Workspace {         // carved from the caller's workspace
   void* lam;               // one vector (costate)
   void* node_a;            // quadrature workspaces only: psi at a node
   void* node_b;            //   and lambda at the node
+  void* tmp;               // one vector up to kPairMaxD amplitudes (psi beside its costate)
+  cplx_d* raw;             // slot 0: brackets before beta is known
+  int64_t raw_len;
   char* area;              // slot 0: everything after the scalars, free while no
   size_t area_bytes;       //   tiled call uses the workspace
 };
@@ -121,6 +124,7 @@ struct Profiler;
 // Non-null while profiling is active and the current Krylov call is sampled.
 Profiler* profiler_for_call();
 Profiler* profiler_for_launch();
+bool profiling();
 // profiler_start arms a pair of events for the next sampled launch, which
 // takes them with profiler_take and passes them to the dispatch itself
 // (hipExtLaunchKernel: the kernel's own start and end, as a kernel trace
@@ -176,6 +180,13 @@ hipError_t launch_krylov(const KrylovCall& c, const Workspace& ws, hipStream_t s
 // One launch per Lanczos step (kg_step.hip) for vectors of up to kStepMaxD
 // amplitudes; needs one more basis vector in the workspace.
 constexpr uint64_t kStepMaxD = 1ull << 18;
+// Pairs in the table that no tiled call uses (kg_step.hip's rows and scalars
+// come first), from this offset of the partials.
+size_t step_table_pairs();
+// Largest vectors whose store-all gradient runs its two sweeps side by side,
+// and the largest that do it in the same launches (beyond, on two streams).
+constexpr uint64_t kPairMaxD = 1ull << 22;
+constexpr uint64_t kPairLaunchMaxD = 1ull << 15;
 Geo make_geo_step(int L, int tile_bits_override);
 hipError_t launch_krylov_steps(const KrylovCall* calls, const Workspace* const* wss, int n,
                                hipStream_t s);
@@ -235,6 +246,24 @@ hipError_t launch_bracket(int prec, const HvArgs& a, uint32_t D, const void* lam
                           double dt, const double* beta_dev, const Workspace& ws, double* grad_slot,
                           hipStream_t s, bool accumulate = false, double coef_im = 0.0,
                           const uint32_t* pe_reps = nullptr);
+// The bracket <lambda|Hc|psi> itself (for launch_scale_brackets), of one or two
+// pairs in one launch; with `keep`, psi is also copied there (keep may be lam).
+struct RawBracket {
+  const void* lam;
+  const void* psi;
+  void* keep;
+  KState* st;
+  cplx_d* partials;
+  cplx_d* out;
+};
+struct RawBracketPair {
+  RawBracket job[2];
+};
+hipError_t launch_bracket_raw(int prec, const HvArgs& a, uint32_t D, const RawBracket* jobs, int n,
+                              hipStream_t s, const uint32_t* pe_reps);
+// g_j = 2 c Im(conj(beta) B_j) for n brackets, added to g with `accumulate`.
+hipError_t launch_scale_brackets(const cplx_d* raw, int n, double c, const double* beta, double* g,
+                                 bool accumulate, hipStream_t s);
 hipError_t launch_hv_pe(int prec, const HvArgs& a, const PeArgs& p, const void* v, void* w,
                         hipStream_t s);
 hipError_t launch_init(KState* st, hipStream_t s);

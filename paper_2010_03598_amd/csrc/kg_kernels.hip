@@ -1105,24 +1105,18 @@ __global__ void __launch_bounds__(kStreamBlock)
   }
 }
 
-// g_j = 2 Im(conj(beta) c <lambda|Hc|psi>) with c = (cr, ci); c = dt gives Eq. 5
-// (chi = beta lambda, sign of dF).  Written to *grad_slot, or added to it with
-// `accumulate` (quadrature nodes, hierarchy terms).
+// This thread's share of <lambda|Hc|psi>; with `keep` psi is also copied there
+// (lambda's amplitudes are read first, by the same thread, so keep may be lam).
 template <typename R>
-__global__ void __launch_bounds__(kStreamBlock)
-    k_bracket(HvArgs a, uint32_t D, const typename VT<R>::T* __restrict__ lam,
-              const typename VT<R>::T* __restrict__ psi, double cr, double ci,
-              const double* beta_dev, KState* st, cplx_d* partials, double* grad_slot,
-              int accumulate, const uint32_t* __restrict__ pe_reps) {
+__device__ __forceinline__ void bracket_sum(const HvArgs& a, uint32_t D, const typename VT<R>::T* lam,
+                                            const typename VT<R>::T* __restrict__ psi,
+                                            typename VT<R>::T* keep,
+                                            const uint32_t* __restrict__ pe_reps, uint32_t T, uint32_t tid,
+                                            double& sr, double& si) {
   using V = typename VT<R>::T;
   constexpr int E = RedChunk<R>::n;
-  __shared__ cplx_d wacc[(kStreamBlock / 64) * kMaxScal];
-  __shared__ cplx_d tot[kMaxScal];
-  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
-  const uint32_t T = gridDim.x * kStreamBlock;
-  const uint32_t tid = blockIdx.x * kStreamBlock + threadIdx.x;
   const uint32_t flip = (a.hc_kind == 0) ? (1u << a.hc_bit) : 0u;
-  double sr = 0.0, si = 0.0;
+  sr = si = 0.0;
   for (uint32_t base = 0; base < D; base += T * E) {
     V l[E], p[E];
     if (base + E * T <= D) {  // the whole chunk exists (block-uniform test)
@@ -1140,6 +1134,13 @@ __global__ void __launch_bounds__(kStreamBlock)
         p[e] = ld_masked(psi, s ^ flip, s < D);
       }
     }
+    if (keep) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const uint32_t s = base + e * T + tid;
+        if (s < D) keep[s] = psi[s];
+      }
+    }
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const uint32_t s = base + e * T + tid;
@@ -1153,6 +1154,24 @@ __global__ void __launch_bounds__(kStreamBlock)
       si += lr * pi - li * pr;
     }
   }
+}
+
+// g_j = 2 Im(conj(beta) c <lambda|Hc|psi>) with c = (cr, ci); c = dt gives Eq. 5
+// (chi = beta lambda, sign of dF).  Written to *grad_slot, or added to it with
+// `accumulate` (quadrature nodes, hierarchy terms).
+template <typename R>
+__global__ void __launch_bounds__(kStreamBlock)
+    k_bracket(HvArgs a, uint32_t D, const typename VT<R>::T* __restrict__ lam,
+              const typename VT<R>::T* __restrict__ psi, double cr, double ci,
+              const double* beta_dev, KState* st, cplx_d* partials, double* grad_slot,
+              int accumulate, const uint32_t* __restrict__ pe_reps) {
+  __shared__ cplx_d wacc[(kStreamBlock / 64) * kMaxScal];
+  __shared__ cplx_d tot[kMaxScal];
+  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+  const uint32_t T = gridDim.x * kStreamBlock;
+  const uint32_t tid = blockIdx.x * kStreamBlock + threadIdx.x;
+  double sr, si;
+  bracket_sum<R>(a, D, lam, psi, nullptr, pe_reps, T, tid, sr, si);
   sr = wave_sum(sr);
   si = wave_sum(si);
   if (lane == 0) wacc[wv * kMaxScal] = cplx_d{sr, si};
@@ -1171,6 +1190,40 @@ __global__ void __launch_bounds__(kStreamBlock)
     }
     *grad_slot = accumulate ? *grad_slot + g : g;
   }
+}
+
+// The bracket <lambda|Hc|psi> itself, of one or two pairs of vectors
+// (blockIdx.y).
+template <typename R>
+__global__ void __launch_bounds__(kStreamBlock) k_bracket_raw(HvArgs a, uint32_t D, RawBracketPair p,
+                                                              const uint32_t* __restrict__ pe_reps) {
+  using V = typename VT<R>::T;
+  __shared__ cplx_d wacc[(kStreamBlock / 64) * kMaxScal];
+  __shared__ cplx_d tot[kMaxScal];
+  const RawBracket& q = p.job[blockIdx.y];
+  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+  const uint32_t T = gridDim.x * kStreamBlock;
+  const uint32_t tid = blockIdx.x * kStreamBlock + threadIdx.x;
+  double sr, si;
+  bracket_sum<R>(a, D, reinterpret_cast<const V*>(q.lam), reinterpret_cast<const V*>(q.psi),
+                 reinterpret_cast<V*>(q.keep), pe_reps, T, tid, sr, si);
+  sr = wave_sum(sr);
+  si = wave_sum(si);
+  if (lane == 0) wacc[wv * kMaxScal] = cplx_d{sr, si};
+  __syncthreads();
+  block_totals(wacc, 1, tot);
+  if (!grid_reduce(tot, 1, q.partials, q.st->counters, blockIdx.x, gridDim.x)) return;
+  if (threadIdx.x == 0) *q.out = tot[0];
+}
+
+// The brackets' share of the gradient once beta is known (k_bracket's formula).
+__global__ void __launch_bounds__(256)
+    k_scale_brackets(const cplx_d* raw, int n, double c, const double* beta, double* g, int accumulate) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const cplx_d B = raw[i];
+  const double v = 2.0 * c * (beta[0] * B.im - beta[1] * B.re);
+  g[i] = accumulate ? g[i] + v : v;
 }
 
 // u <- u + eta g / max|g| in one block (deterministic max).
@@ -1559,6 +1612,26 @@ hipError_t launch_bracket(int prec, const HvArgs& a, uint32_t D, const void* lam
                        reinterpret_cast<const float2*>(lam), reinterpret_cast<const float2*>(psi),
                        dt, coef_im, beta_dev, ws.st, ws.partials, grad_slot, acc, pe_reps);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_bracket_raw(int prec, const HvArgs& a, uint32_t D, const RawBracket* jobs, int n,
+                              hipStream_t s, const uint32_t* pe_reps) {
+  const int grid = reduce_grid(D, prec);
+  RawBracketPair p;
+  memset(static_cast<void*>(&p), 0, sizeof(p));
+  for (int i = 0; i < n; ++i) p.job[i] = jobs[i];
+  if (prec == 0)
+    kg_launch(k_bracket_raw<double>, dim3(grid, n), dim3(kStreamBlock), 0, s, a, D, p, pe_reps);
+  else
+    kg_launch(k_bracket_raw<float>, dim3(grid, n), dim3(kStreamBlock), 0, s, a, D, p, pe_reps);
+  return hipGetLastError();
+}
+
+hipError_t launch_scale_brackets(const cplx_d* raw, int n, double c, const double* beta, double* g,
+                                 bool accumulate, hipStream_t s) {
+  hipLaunchKernelGGL(k_scale_brackets, dim3((n + 255) / 256), dim3(256), 0, s, raw, n, c, beta, g,
+                     accumulate ? 1 : 0);
   return hipGetLastError();
 }
 

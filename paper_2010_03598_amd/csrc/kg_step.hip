@@ -611,6 +611,10 @@ static_assert(2 * kStepRows * kStepCols + (sizeof(StepState) + sizeof(cplx_d) - 
                   (size_t)kPartialRows * kMaxScal,
               "the rows and the scalars fit in the partials table");
 
+size_t step_table_pairs() {
+  return 2 * (size_t)kStepRows * kStepCols + (sizeof(StepState) + sizeof(cplx_d) - 1) / sizeof(cplx_d);
+}
+
 hipError_t launch_krylov_steps(const KrylovCall* calls, const Workspace* const* wss, int n,
                                hipStream_t s) {
   return calls[0].prec == 0 ? launch_krylov_steps_r<double>(calls, wss, n, s)

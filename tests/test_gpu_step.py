@@ -59,3 +59,32 @@ def test_in_place_and_breakdown():
     assert float(got[1:].abs().max()) == 0.0
     z = kg.krylov_expv(h, 0.2, 0.3, torch.zeros_like(e), k, m_eff=m_eff)
     assert int(m_eff) == 0 and float(z.abs().max()) == 0.0
+
+
+def test_paired_sweeps_equal_one_stream():
+    """The store-all gradient with both sweeps side by side (odd and even slice
+    counts, two slices) is the sequential one bit for bit, states included."""
+    import os
+    rng = np.random.default_rng(8)
+    for L, N, centred, dtype in [(11, 2, False, C128), (11, 7, True, C64), (12, 8, False, C64),
+                                 (19, 3, True, C64)]:
+        h, k = kg.XXZ(L, 1.0, 0.7), kg.Krylov(6)
+        u = torch.tensor(rng.uniform(-1.0, 1.0, N), device="cuda")
+        psi0 = dev_vec(workloads.random_phase_state(rng, h.D), dtype)
+        f = dev_vec(workloads.random_phase_state(rng, h.D), dtype)
+        a = kg.grape_gradient(h, u, 0.05, k, psi0, f, centred=centred)
+        os.environ["KG_ONE_STREAM"] = "1"
+        try:
+            b = kg.grape_gradient(h, u, 0.05, k, psi0, f, centred=centred)
+        finally:
+            del os.environ["KG_ONE_STREAM"]
+        assert torch.equal(a.F, b.F) and torch.equal(a.grad, b.grad) and torch.equal(a.states, b.states)
+        p = torch.stack([psi0, psi0 * 0.5])
+        t = torch.stack([f, f])
+        a = kg.grape_gradient_columns(h, u, 0.05, k, p, t, centred=centred)
+        os.environ["KG_ONE_STREAM"] = "1"
+        try:
+            b = kg.grape_gradient_columns(h, u, 0.05, k, p, t, centred=centred)
+        finally:
+            del os.environ["KG_ONE_STREAM"]
+        assert torch.equal(a.F, b.F) and torch.equal(a.grad, b.grad)
