@@ -1048,6 +1048,54 @@ __host__ __device__ inline bool pairs_tiling(const Geo& g) {
   return !g.small && g.RB >= 2 && g.TB > 6 + g.RB;
 }
 
+// ---------------------------------------------------------------------- reduced-basis row
+
+// Row b (slice s of 64 rows, this lane's) of the reduced H v through the
+// neighbour table, kPeNbrHops slots of the row in flight together; xat(i) is
+// the amplitude of orbit i.  Sets `bad` when an entry is out of range.
+constexpr int kPeNbrHops = 8;
+
+template <typename R, typename XAt>
+__device__ __forceinline__ void pe_row_nbr(const HvArgs& a, const PeArgs& p, double u, uint32_t s,
+                                           uint32_t b, uint32_t lane, XAt xat, R& yr, R& yi,
+                                           bool& bad) {
+  using V = typename VT<R>::T;
+  const int L = p.L;
+  const uint32_t bondmask = (1u << (L - 1)) - 1u;   // L <= 32, so the shift is at most 31
+  const R hJ = (R)a.half_J, czz = (R)a.c_zz, uR = (R)u;
+  const R rt2 = (R)1.4142135623730951, irt2 = (R)0.70710678118654752;
+  const uint32_t r = p.reps[b];
+  const int n_anti = (int)__popc((r ^ (r >> 1)) & bondmask);
+  R d = czz * (R)(L - 1 - 2 * n_anti);
+  if (a.hc_kind == 1) d += uR * ((R)(0.5 * a.sz_count) - (R)__popc(r & a.sz_mask));
+  const V xb = xat(b);
+  yr = d * xb.x;
+  yi = d * xb.y;
+  bad = false;
+  const uint32_t c = min(uniform_u32(p.scnt[s]), (uint32_t)p.nbr_slots);
+  const uint32_t* e = p.nbr + (size_t)s * (uint32_t)p.nbr_slots * 64u + lane;
+  for (uint32_t j0 = 0; j0 < c; j0 += kPeNbrHops) {
+    uint32_t ent[kPeNbrHops];
+#pragma unroll
+    for (int j = 0; j < kPeNbrHops; ++j) ent[j] = (j0 + j < c) ? e[(size_t)(j0 + j) * 64u] : b;
+    V xa[kPeNbrHops];
+#pragma unroll
+    for (int j = 0; j < kPeNbrHops; ++j) {
+      const uint32_t ai = ent[j] & 0x3FFFFFFFu;
+      const bool ok = ai < p.dim;
+      bad = bad || !ok;
+      xa[j] = xat(ok ? ai : b);
+    }
+#pragma unroll
+    for (int j = 0; j < kPeNbrHops; ++j) {
+      const uint32_t code = ent[j] >> 30;
+      const R w = code == 0u ? (R)0 : (code == 1u ? (R)1 : (code == 2u ? rt2 : irt2));
+      yr += hJ * w * xa[j].x;
+      yi += hJ * w * xa[j].y;
+    }
+  }
+}
+
 __device__ __forceinline__ double control_value(const HvArgs& a) {
   return a.u_ptr ? *a.u_ptr : a.u_val;
 }

@@ -188,6 +188,7 @@ size_t step_table_pairs();
 constexpr uint64_t kPairMaxD = 1ull << 22;
 constexpr uint64_t kPairLaunchMaxD = 1ull << 15;
 Geo make_geo_step(int L, int tile_bits_override);
+Geo make_geo_step_pe(int L, uint64_t dim);
 hipError_t launch_krylov_steps(const KrylovCall* calls, const Workspace* const* wss, int n,
                                hipStream_t s);
 // Two independent calls of the same L, m, reorth and precision in the same launches.

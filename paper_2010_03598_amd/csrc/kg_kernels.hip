@@ -221,49 +221,6 @@ __global__ void __launch_bounds__(256) k_hv_pe(HvArgs a, PeArgs p,
 // follow its bonds in ascending order, so the sums are those of pe_row, bit
 // for bit.  Slices are dealt to the XCDs in contiguous ranges, so that the
 // near neighbours of low bonds are in the XCD's own L2.
-constexpr int kPeNbrHops = 8;
-
-template <typename R, typename XAt>
-__device__ __forceinline__ void pe_row_nbr(const HvArgs& a, const PeArgs& p, double u, uint32_t s,
-                                           uint32_t b, uint32_t lane, XAt xat, R& yr, R& yi,
-                                           bool& bad) {
-  using V = typename VT<R>::T;
-  const int L = p.L;
-  const uint32_t bondmask = (1u << (L - 1)) - 1u;   // L <= 32, so the shift is at most 31
-  const R hJ = (R)a.half_J, czz = (R)a.c_zz, uR = (R)u;
-  const R rt2 = (R)1.4142135623730951, irt2 = (R)0.70710678118654752;
-  const uint32_t r = p.reps[b];
-  const int n_anti = (int)__popc((r ^ (r >> 1)) & bondmask);
-  R d = czz * (R)(L - 1 - 2 * n_anti);
-  if (a.hc_kind == 1) d += uR * ((R)(0.5 * a.sz_count) - (R)__popc(r & a.sz_mask));
-  const V xb = xat(b);
-  yr = d * xb.x;
-  yi = d * xb.y;
-  bad = false;
-  const uint32_t c = min(uniform_u32(p.scnt[s]), (uint32_t)p.nbr_slots);
-  const uint32_t* e = p.nbr + (size_t)s * (uint32_t)p.nbr_slots * 64u + lane;
-  for (uint32_t j0 = 0; j0 < c; j0 += kPeNbrHops) {
-    uint32_t ent[kPeNbrHops];
-#pragma unroll
-    for (int j = 0; j < kPeNbrHops; ++j) ent[j] = (j0 + j < c) ? e[(size_t)(j0 + j) * 64u] : b;
-    V xa[kPeNbrHops];
-#pragma unroll
-    for (int j = 0; j < kPeNbrHops; ++j) {
-      const uint32_t ai = ent[j] & 0x3FFFFFFFu;
-      const bool ok = ai < p.dim;
-      bad = bad || !ok;
-      xa[j] = xat(ok ? ai : b);
-    }
-#pragma unroll
-    for (int j = 0; j < kPeNbrHops; ++j) {
-      const uint32_t code = ent[j] >> 30;
-      const R w = code == 0u ? (R)0 : (code == 1u ? (R)1 : (code == 2u ? rt2 : irt2));
-      yr += hJ * w * xa[j].x;
-      yi += hJ * w * xa[j].y;
-    }
-  }
-}
-
 template <typename R>
 __global__ void __launch_bounds__(512) k_hv_pe_nbr(HvArgs a, PeArgs p,
                                                    const typename VT<R>::T* __restrict__ x,
@@ -1441,12 +1398,13 @@ hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss,
   }
   // one launch per step; a call that KG_TILE_BITS or KG_NO_FUSED keeps from the
   // one-block form takes the two passes
-  if (!c0.pe && c0.geo.D <= kStepMaxD &&
-      !sweep_fits(c0.prec, c0.geo.D, c0.m, sweep_neighbours(c0.pe, c0.hv.L))) {
+  const bool steps = c0.geo.D <= kStepMaxD && (!c0.pe || c0.pe->nbr);
+  if (steps && !sweep_fits(c0.prec, c0.geo.D, c0.m, sweep_neighbours(c0.pe, c0.hv.L))) {
     KrylovCall c[kMaxJobs];
     for (int j = 0; j < n; ++j) {
       c[j] = calls[j];
-      c[j].step = make_geo_step(c0.hv.L, tile_override_from_env());
+      c[j].step = c0.pe ? make_geo_step_pe(c0.hv.L, c0.geo.D)
+                        : make_geo_step(c0.hv.L, tile_override_from_env());
     }
     return launch_krylov_steps(c, wss, n, s);
   }

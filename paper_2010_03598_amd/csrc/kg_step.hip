@@ -61,6 +61,7 @@ struct StepArgs {
   double tol, t;
   void* out;              // combination
   int32_t* m_eff_out;
+  PeArgs pe;              // reduced basis: its neighbour table
 };
 
 constexpr int kStepFar = 4;               // far partners per round trip
@@ -259,12 +260,19 @@ __device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl,
   if (go) __syncthreads();
 }
 
-// RAG: a vector shorter than its tile.  FIRST: step 0.  One tile per block.
-template <typename R, int RB, bool RAG, bool FIRST>
+__device__ __forceinline__ void hold_pe_args(const PeArgs& p) {
+  asm volatile("" ::"s"(p.reps), "s"(p.scnt), "s"(p.nbr), "s"(p.nbr_slots), "s"(p.L), "s"(p.dim));
+}
+
+// RAG: the last tile reaches past the vector.  FIRST: step 0.  PE: the reduced
+// basis, H v gathered through its neighbour table (a wavefront's unit of 64
+// rows is a slice of the table).  One tile per block.
+template <typename R, int RB, bool RAG, bool FIRST, bool PE>
 __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_t G) {
   using V = typename VT<R>::T;
   constexpr int NR = 1 << RB;
   hold_args(a);
+  if constexpr (PE) hold_pe_args(a.pe);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ cplx_d cf[kMaxM + 8];
   __shared__ cplx_d tot[kStepCols];
@@ -306,18 +314,42 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
     }
   };
   const double u = control_value(a.hv);
+  const auto window_first_loads = [&] {
+    if (nw > 0) {
+      load(sw, (int)c, w0q[0]);
+      load(sw, (int)c + 4, w0q[1]);
+    }
+  };
+  // H v, with one barrier of the block on the way
+  const auto apply_h = [&](auto before) {
+    if constexpr (PE) {
+      const uint32_t ns = (D + 63u) >> 6;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const uint32_t sl = min((sw >> 6) + r, ns - 1u), b = min((sl << 6) | lane, D - 1u);
+        bool bad;
+        pe_row_nbr<R>(a.hv, a.pe, u, sl, b, lane, [&](uint32_t i) { return src[i]; }, T.yr[r], T.yi[r],
+                      bad);
+        const V x = src[b];
+        T.xr[r] = x.x;
+        T.xi[r] = x.y;
+        if (bad) T.yr[r] = T.yi[r] = (R)NAN;
+      }
+      before();
+      __syncthreads();
+    } else {
+      hv_tile<R, RB, false, kStepFar>(T, a.hv, g, tile, src, lds, u, before);
+    }
+  };
   if constexpr (FIRST) {
-    hv_tile<R, RB, false, kStepFar>(T, a.hv, g, tile, src, lds, u);
+    apply_h(NoWork());
   } else {
     RowGather rg(a.rows + (size_t)((k - 1) & 1) * kStepRows * kStepCols, G,
                  2u * (uint32_t)(k - 1 - ip) + 2u, wv, NW + 1u);
     load_slots<V, NR>(step_slot<const V>(a, k - 1), sw | lane, !RAG, D, up);
     load_slots<V, NR>(yb, sw | lane, !RAG, D, yp);
-    hv_tile<R, RB, false, kStepFar>(T, a.hv, g, tile, src, lds, u, [&] {
-      if (nw > 0) {
-        load(sw, (int)c, w0q[0]);
-        load(sw, (int)c + 4, w0q[1]);
-      }
+    apply_h([&] {
+      window_first_loads();
       rg.sum(part + wv * kStepCols);
     });
   }
@@ -440,11 +472,11 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
 
 // Blocks of up to four wavefronts of tile work (TH 320) get the registers of
 // two wavefronts per SIMD.
-template <typename R, int RB, bool RAG, int TH, bool FIRST>
+template <typename R, int RB, bool RAG, int TH, bool FIRST, bool PE = false>
 __global__ void __launch_bounds__(TH) k_step(StepBatch B) {
   const uint32_t G = B.job[0].geo.grid;
   const uint32_t j = blockIdx.x < G ? 0u : 1u;
-  step_body<R, RB, RAG, FIRST>(B.job[j], blockIdx.x - j * G, G);
+  step_body<R, RB, RAG, FIRST, PE>(B.job[j], blockIdx.x - j * G, G);
 }
 
 constexpr int kCombBlock = 256;
@@ -531,7 +563,11 @@ hipError_t launch_step_rb(const StepBatch& b, int n, size_t lds, hipStream_t s) 
   const dim3 grid(g.grid * n), block(64u * ((1u << g.WB) + 1u));
   const bool first = b.job[0].k == 0;
   const auto go = [&](auto zero, auto later) { kg_launch(first ? zero : later, grid, block, lds, s, b); };
-  if (g.small)
+  if (b.job[0].pe.nbr && g.WB <= 2)
+    go(k_step<R, RB, true, 320, true, true>, k_step<R, RB, true, 320, false, true>);
+  else if (b.job[0].pe.nbr)
+    go(k_step<R, RB, true, 576, true, true>, k_step<R, RB, true, 576, false, true>);
+  else if (g.small)
     go(k_step<R, RB, true, 576, true>, k_step<R, RB, true, 576, false>);
   else if (g.WB <= 2)
     go(k_step<R, RB, false, 320, true>, k_step<R, RB, false, 320, false>);
@@ -571,6 +607,7 @@ hipError_t launch_krylov_steps_r(const KrylovCall* calls, const Workspace* const
     a.t = c.t;
     a.out = c.v_out;
     a.m_eff_out = c.m_eff_out;
+    if (c.pe) a.pe = *c.pe;
   }
   const Geo& g = b.job[0].geo;
   hipError_t e = hipSuccess;
@@ -591,7 +628,10 @@ hipError_t launch_krylov_steps_r(const KrylovCall* calls, const Workspace* const
     // as a pass A (v_k read, y written but in the last step) and, before the
     // last step, a pass B (y and the window read, v_{k+1} written)
     const int i0 = k == m - 1 ? k : (calls[0].reorth ? 0 : (k > 0 ? k - 1 : 0));
-    if (prof && k < m - 1)
+    if (prof && calls[0].pe)
+      profiler_stop(prof, s, kProfHv, n * pe_gather_bytes(*calls[0].pe, vb / n), kProfPassB,
+                    (k < m - 1 ? k - i0 + 3 : 1) * vb);
+    else if (prof && k < m - 1)
       profiler_stop(prof, s, kProfPassA, 2 * vb, kProfPassB, (k - i0 + 3) * vb);
     else if (prof)
       profiler_stop(prof, s, kProfPassA, vb);

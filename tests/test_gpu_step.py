@@ -88,3 +88,23 @@ def test_paired_sweeps_equal_one_stream():
         finally:
             del os.environ["KG_ONE_STREAM"]
         assert torch.equal(a.F, b.F) and torch.equal(a.grad, b.grad)
+
+
+# dims 1716 and 6470: a ragged last tile, padded tiles without rows, odd dimensions
+@pytest.mark.parametrize("dtype", [C128, C64])
+@pytest.mark.parametrize("L,K,m,ckpt", [(14, 7, 6, 0), (15, 6, 9, 2), (16, 8, 10, 0)])
+def test_reduced_basis(L, K, m, ckpt, dtype):
+    from oracle import grape, pe
+    t = workloads.pe_task(L, K, 5, dt=0.1, m=m)
+    B = kg.ReducedBasis(L, K)
+    P = pe.PEChain(L, K, t.J, t.Delta, t.hc_sites)
+    rng = np.random.default_rng(L + m)
+    psi0, f = workloads.random_state(rng, B.dim), workloads.random_state(rng, B.dim)
+    ref = grape.gradient_centred(P, t.u, psi0, f, t.dt, m)
+    h = kg.XXZ(L, t.J, t.Delta, kg.KG_HC_SZ, t.hc_sites)
+    r = kg.grape_gradient_pe(h, B, torch.tensor(t.u, device="cuda"), t.dt, kg.Krylov(m),
+                             dev_vec(psi0, dtype), dev_vec(f, dtype), ckpt_every=ckpt,
+                             variant="centred")
+    tol = 1e-10 if dtype == C128 else 1e-4
+    assert abs(float(r.F) - ref.F) <= tol * ref.F
+    assert np.linalg.norm(host(r.grad) - ref.grad) <= tol * np.linalg.norm(ref.grad)
