@@ -811,9 +811,9 @@ Geo make_geo(int L, int prec, int tile_bits_override, int grid_cap, bool standal
 // Timed calls (m = 16, us) at tiles of 2^7, 2^8, 2^9, 2^10 amplitudes,
 // complex64: L=11 98, 104, 119, 155; L=14 115, 107, 135, 191; L=16 203, 138,
 // 137, 169; L=17 -, 201, 160, 188; L=18 -, -, 290, 209.  complex128 the same
-// order.  The two-pass form takes 231 at L=13, 239 at L=17, 266 at L=18
-// (322 complex128: 252 here); at L=19 both take 320 (complex64), and in
-// complex128 it is ahead (430 against 496): the line is at 2^18.
+// order.  The passes that share a stream between two steps take 199 at L=16,
+// 204 at L=17, 225 at L=18 (285 complex128: 250 here); at L=19 they are ahead
+// (273 against 316 complex64, 377 against 496 complex128): the line is at 2^18.
 Geo make_geo_step(int L, int tile_bits_override) {
   Geo g;
   memset(&g, 0, sizeof(g));

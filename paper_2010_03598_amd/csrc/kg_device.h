@@ -106,7 +106,7 @@ __device__ __forceinline__ double quad_sums(double v0, double v1, double v2, dou
 // Two quad_sums with one exchange across rows: lane l returns the total of
 // a[l mod 4] where bit 2 of l is clear and of b[l mod 4] where it is set
 // (after the sums within rows every lane of a row holds its row's totals, so
-// half of a row can carry b).  Faster in the batched kernel; in pass B of the
+// half of a row can carry b).  Faster in the batched kernel; in the passes of the
 // tiled form it made the step slower.
 __device__ __forceinline__ double quad_sums_pair(double a0, double a1, double a2, double a3,
                                                  double b0, double b1, double b2, double b3) {
@@ -635,14 +635,6 @@ __device__ __forceinline__ uint32_t tile_of(const Geo& g, uint32_t it, uint32_t 
 // about 128 bytes of partner amplitudes per thread, at most 4 vectors.
 template <typename R, int RB>
 struct FarSlots {
-  static constexpr int units = 16 / ((1 << RB) * (int)(sizeof(R) / 4));
-  static constexpr int n = units > 8 ? 8 : (units < 1 ? 1 : units);
-};
-
-// Basis vectors fetched per round trip in the projection/update loops: about
-// 128 bytes of amplitudes per thread, at most 8 vectors.
-template <typename R, int RB>
-struct WinSlots {
   static constexpr int units = 16 / ((1 << RB) * (int)(sizeof(R) / 4));
   static constexpr int n = units > 8 ? 8 : (units < 1 ? 1 : units);
 };

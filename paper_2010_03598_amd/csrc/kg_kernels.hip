@@ -19,10 +19,14 @@
 // cost one scalar branch.  The diagonal S^z S^z term is one popcount.
 //
 // Lanczos (App. A, Algorithm 2 with the full re-orthonormalisation it
-// describes).  One basis step is two passes over the tile grid:
+// describes).  Vectors of more than 2^18 amplitudes (shorter ones take a launch
+// per step or a block per call, kg_step.hip and kg_sweep.hip; these passes serve
+// them too when a tile size is forced).  With full re-orthonormalisation two
+// steps share one pass over the basis (pass C and pass P, described there); the
+// plain two-vector window takes two passes a step:
 //   pass A(k): x = stored v_k; y = H x, stored (the H v vector); each block
 //              writes its parts of <x|y> and ||x||^2 and ends (no grid-wide
-//              reduction); helper wavefronts sum the previous pass B's
+//              reduction); helper wavefronts sum the earlier pass's
 //              measurement columns over the grid;
 //   pass B(k): every block first runs the scalar update of step k on the same
 //              sums (breakdown test, window dots, projection coefficients),
@@ -30,7 +34,7 @@
 //              v_{k+1}, with the blocks' parts of ||w||^2 and of the dots the
 //              next step derives its window dots from; a streaming pass over y
 //              and the window.
-// The scalar update costs each pass B block one memory round trip and a few
+// The scalar update costs each block of a streaming pass one memory round trip and a few
 // hundred FP64 instructions on one wavefront, instead of a serial tail in
 // which the last block of pass A waits for every partial and then computes
 // alone.  Storing y costs one vector write and read; recomputing it in pass B
@@ -269,7 +273,7 @@ struct LzArgs {
   int32_t m;
   int32_t i0n;        // first index of the next step's window
   int32_t i0p;        // first index of the previous step's window
-  int32_t pad_;
+  int32_t alone;      // pass C: a step by itself, not the first of a pair
   double t;
   double tol;
   KState* st;
@@ -421,13 +425,14 @@ __device__ __forceinline__ void store_y(const Tile<R, RB>& T, typename VT<R>::T*
 // The reduced sums of step k into `tot` (LDS) and the earlier steps' scalars
 // into `fs` (LDS), in the layout the scalar update reads:
 //   tot[0, 2nb)   pass B(k-1)'s measurement totals (window dots of step k),
-//   tot[2nb]      <v_k|y_k>,  tot[2nb + 1] = (||v_k||^2, 0)  (k = 0 only),
+//   tot[2nb]      <v_k|y_k>,  tot[2nb + 1] = (||v_k||^2, 0)  (with `norm` only),
 //   tot[2nb + 2]  ||w||^2 of pass B(k-1), the square of the next off-diagonal.
 // The totals of pass B(k-1)'s columns come from pass A(k)'s helper
 // wavefronts (KState::colsum); pass A(k)'s own columns are summed here over
 // its G rows.  Every wavefront issues its loads before it waits.  Ends with a
 // barrier; false (in every thread) when the basis ended in an earlier step.
-__device__ bool gather_step(const LzArgs& a, uint32_t G, int nb, FinScalars& fs, cplx_d* tot) {
+__device__ bool gather_step(const LzArgs& a, uint32_t G, int nb, bool norm, FinScalars& fs,
+                            cplx_d* tot) {
   __shared__ int ended;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wv = uniform_u32(threadIdx.x >> 6);
@@ -435,7 +440,7 @@ __device__ bool gather_step(const LzArgs& a, uint32_t G, int nb, FinScalars& fs,
   const int k = a.k;
   const int ca = 2 * nb, ns = ca + 2;
   const KState* st = a.st;
-  // wavefronts that sum the A columns: kACol always, kACol + 1 at k = 0
+  // wavefronts that sum the A columns: kACol always, kACol + 1 with `norm`
   const uint32_t wa0 = nw >= 2 ? 1u : 0u;
   const uint32_t wa1 = nw >= 3 ? 2u : wa0;
   if (wv == 0) {
@@ -451,7 +456,7 @@ __device__ bool gather_step(const LzArgs& a, uint32_t G, int nb, FinScalars& fs,
     if (wa0 == 0) {
       const cplx_d t = column_total(a.partials + (size_t)kACol * kPartialRows, G);
       if (lane == 0) tot[ca] = t;
-      if (k == 0) {
+      if (norm) {
         const cplx_d t1 = column_total(a.partials + (size_t)(kACol + 1) * kPartialRows, G);
         if (lane == 0) tot[ca + 1] = t1;
       }
@@ -468,7 +473,7 @@ __device__ bool gather_step(const LzArgs& a, uint32_t G, int nb, FinScalars& fs,
       const cplx_d t = column_total(a.partials + (size_t)kACol * kPartialRows, G);
       if (lane == 0) tot[ca] = t;
     }
-    if (k == 0 && wv == wa1) {
+    if (norm && wv == wa1) {
       const cplx_d t = column_total(a.partials + (size_t)(kACol + 1) * kPartialRows, G);
       if (lane == 0) tot[ca + 1] = t;
     }
@@ -486,6 +491,9 @@ __device__ bool gather_step(const LzArgs& a, uint32_t G, int nb, FinScalars& fs,
 // basis goes on.  At the last step (k = m-1), or when it ends here (a zero or
 // non-finite input, a breakdown), it returns false after the combination
 // coefficients went to `dc`/*me (nullable) and, with `writer`, to the state.
+// kLocal: the first step of a pair, whose window is v_k alone: *cf is c_k, and no
+// window dots are formed.
+template <bool kLocal = false>
 __device__ bool step_update(const LzArgs& a, const FinScalars& fs, const cplx_d* tot, int nb,
                             bool writer, cplx_d* cf, double* sk_out, cplx_d* dc, int* me) {
   KState* st = a.st;
@@ -535,10 +543,12 @@ __device__ bool step_update(const LzArgs& a, const FinScalars& fs, const cplx_d*
     }
   }
   // lane l: window index i0 + l (a window holds at most kMaxM <= 64 vectors)
-  const cplx_d d = (nb > 0) ? window_dots(k, a.i0, a.i0p, fs, tot, nb, tot[ns].re,
+  const cplx_d d = (!kLocal && nb > 0) ? window_dots(k, a.i0, a.i0p, fs, tot, nb, tot[ns].re,
                                           writer ? st->gcol[(k - 1) & 1] : nullptr)
                              : cplx_d{0.0, 0.0};
-  if (lane < nwin) {
+  if (kLocal) {
+    if (cf && lane == 0) cf[0] = cplx_d{tot[ca].re * sk * sk * sk, tot[ca].im * sk * sk * sk};
+  } else if (lane < nwin) {
     const int i = a.i0 + lane;
     const double si = (i == k) ? sk : fs.scale[i];
     const double f = si * sk;
@@ -681,7 +691,7 @@ __global__ void __launch_bounds__(1024) k_pass_a_y(LzBatch B) {
 
 // Pass B(k): the scalar update of step k in its prologue (every block, on the
 // same sums: gather_step, step_update), then w = s_k y_k - sum_i c_i v_i over
-// the window [i0, k] (FP64), stored unnormalised as v_{k+1}, with this block's
+// the window [i0, k], i0 = k - 1 or k (FP64), stored unnormalised as v_{k+1}, with this block's
 // part of ||w||^2 (column kNormCol) and, when step k+1 has window dots, of
 // <v_i|y_k> (columns [0, nb)) and <v_i|v_k> (columns [nb, 2nb)) for i in the
 // window: the operands are already in registers for the update, and step k+1
@@ -729,13 +739,11 @@ __device__ __forceinline__ void bload(const V* __restrict__ p, uint32_t base, ui
   }
 }
 
-// NWO > 0 sets the number of window vectors per round trip (else WinSlots);
 // NT streams the vectors with nontemporal loads.
-template <typename R, int RB, int MODE, int NWO = 0, bool NT = false>
+template <typename R, int RB, int MODE, bool NT = false>
 __device__ __forceinline__ void pass_b_body(const LzArgs& a, uint32_t bl, uint32_t G) {
   using V = typename VT<R>::T;
   constexpr int NR = 1 << RB;
-  constexpr int NW = NWO > 0 ? NWO : WinSlots<R, RB>::n;
   extern __shared__ unsigned char smem_raw[];
   __shared__ cplx_d tot[kMaxScal];
   __shared__ FinScalars fs;
@@ -748,7 +756,7 @@ __device__ __forceinline__ void pass_b_body(const LzArgs& a, uint32_t bl, uint32
 
   // ---- the scalar update of step k (window dots of pass B(k-1)'s measurements)
   const int nb_in = (a.k > 0 && a.i0 < a.k) ? a.k - a.i0p : 0;
-  if (!gather_step(a, G, nb_in, fs, tot)) return;
+  if (!gather_step(a, G, nb_in, a.k == 0, fs, tot)) return;
   if (wv == 0) {
     const bool cont = step_update(a, fs, tot, nb_in, bl == 0, cf, &sk_s, nullptr, nullptr);
     if (lane == 0) go = cont ? 1 : 0;
@@ -812,32 +820,23 @@ __device__ __forceinline__ void pass_b_body(const LzArgs& a, uint32_t bl, uint32
       }
       add_quad(a.k - a.i0, quad_sums(sr, si, gr, 0.0));
     }
-    // window vectors other than v_k, NW per round trip
-    for (int i = a.i0; i < a.k; i += NW) {
-      V q[NW][NR];
+    if (a.i0 < a.k) {
+      V q[NR];
+      bload<MODE, RB, NT>(slot_ptr<V>(a, a.i0), base, lane, wv, D, q);
+      const cplx_d c = cf[0];
+      double sr = 0.0, si = 0.0, gr = 0.0, gi = 0.0;
 #pragma unroll
-      for (int j = 0; j < NW; ++j) {
-        if (i + j < a.k) bload<MODE, RB, NT>(slot_ptr<V>(a, i + j), base, lane, wv, D, q[j]);
+      for (int r = 0; r < NR; ++r) {
+        const double vr = q[r].x, vi = q[r].y;
+        zr[r] -= c.re * vr - c.im * vi;
+        zi[r] -= c.re * vi + c.im * vr;
+        const double yr = yo[r].x, yi = yo[r].y, xr = xo[r].x, xi = xo[r].y;
+        sr += vr * yr + vi * yi;
+        si += vr * yi - vi * yr;
+        gr += vr * xr + vi * xi;
+        gi += vr * xi - vi * xr;
       }
-#pragma unroll
-      for (int j = 0; j < NW; ++j) {
-        if (i + j < a.k) {
-          const cplx_d c = cf[i + j - a.i0];
-          double sr = 0.0, si = 0.0, gr = 0.0, gi = 0.0;
-#pragma unroll
-          for (int r = 0; r < NR; ++r) {
-            const double vr = q[j][r].x, vi = q[j][r].y;
-            zr[r] -= c.re * vr - c.im * vi;
-            zi[r] -= c.re * vi + c.im * vr;
-            const double yr = yo[r].x, yi = yo[r].y, xr = xo[r].x, xi = xo[r].y;
-            sr += vr * yr + vi * yi;
-            si += vr * yi - vi * yr;
-            gr += vr * xr + vi * xi;
-            gi += vr * xi - vi * xr;
-          }
-          if (nb) add_quad(i + j - a.i0, quad_sums(sr, si, gr, gi));
-        }
-      }
+      if (nb) add_quad(0, quad_sums(sr, si, gr, gi));
     }
     // store w; its norm from the stored (rounded) values
     double nn = 0.0;
@@ -872,13 +871,386 @@ __device__ __forceinline__ void pass_b_body(const LzArgs& a, uint32_t bl, uint32
   if (threadIdx.x == 0) a.partials[(size_t)kNormCol * kPartialRows + bl] = cplx_d{tot[2 * nb].re, 0.0};
 }
 
-template <typename R, int RB, int MODE, int NWO = 0, bool NT = false>
+template <typename R, int RB, int MODE, bool NT = false>
 __global__ void __launch_bounds__(RB >= 3 ? 512 : 1024) k_pass_b(LzBatch B) {
   const uint32_t G = B.job[0].geo.grid;
   if (blockIdx.x < G) {
-    pass_b_body<R, RB, MODE, NWO, NT>(B.job[0], blockIdx.x, G);
+    pass_b_body<R, RB, MODE, NT>(B.job[0], blockIdx.x, G);
   } else {
-    pass_b_body<R, RB, MODE, NWO, NT>(B.job[1], blockIdx.x - G, G);
+    pass_b_body<R, RB, MODE, NT>(B.job[1], blockIdx.x - G, G);
+  }
+}
+
+// Two Lanczos steps per pass over the window (full re-orthogonalisation).  A pass
+// B(k) is bound by the stream of v_0..v_k; here one stream serves two steps:
+//   pass A(b), pass C(b):      p = s_b y - alpha_b v_b - beta_b v_{b-1}, the
+//                              three-term step alone, stored in v_{b+1}'s place;
+//   pass A(b+1), pass P(b):    with y = H p: v_{b+1} = p - sum E_i v_i and
+//                              w_{b+2} = H v_{b+1} - alpha v_{b+1} - beta v_b
+//                              - (overlaps), both linear in p, H p and the window.
+// What <v_i|p> is follows, as in pass B, from the overlaps of v_b and v_{b-1} that
+// pass P(b-2) measured and H's tridiagonal form; and H v_{b+1} = H p - sum E_i H v_i
+// needs no second product, since H v_i is a sum of three window vectors.  While
+// every |e_i| = |<v_i|p>| / ||p|| is below the unit roundoff of the stored vectors
+// (random states: about that over sqrt(D)), p stands as v_{b+1}: storing the
+// difference would round the vector a second time by more than it corrects.  Larger
+// ones are taken out.  w_{b+2} is always corrected.  Per pair the vectors moved
+// fall from 2b + 7 to b + 8.
+//
+// In normalised vectors, with g_i = <v_i|v_b>, h_i = <v_i|v_{b-1}> and
+// beta = ||p||:
+//   beta e_i = beta_{i+1} g_{i+1} + (alpha_i - alpha_b) g_i + beta_i g_{i-1}
+//              - beta_b h_i                      (i < b; the exact 1s cancel),
+//   beta e_b = -beta_b conj(g_{b-1}),            E_i = beta e_i or all 0,
+//   alpha    = <p|Hp> / beta^2 - 2 Re E_b,
+//   f_i      = beta_i e_{i-1} + (alpha_i - alpha) e_i + beta_{i+1} e_{i+1} - beta g_i,
+//   w_{b+2}  = (H p - (alpha + E_b) p) / beta - beta v_b - sum f_i v_i.
+// Pass P measures <v_i|p>, <v_i|Hp> and, from its outputs, <v_{b+1}|w_{b+2}> and
+// ||w_{b+2}||^2; pass C(b+2) turns them into the next g and h.
+
+// The scalars of pass P on wavefront 0 (a.k = b + 1; tot[0] = <p|Hp>, tot[1].re =
+// ||p||^2): the coefficients of the two outputs on the stored window vectors into ec
+// and fc, that of p / beta into *kappa, whether p is corrected into *corr (`unit`: the
+// unit roundoff).  State, with `writer`: csub[i] = E_i / beta, cdiag[i] = the part of <v_i|w_{b+2}> known before the stream, cdiag[b+1] = kappa.
+// On entry fs.gprev holds g and fs.coef h.  False after a breakdown.
+__device__ bool pair_update(const LzArgs& a, const FinScalars& fs, const cplx_d* tot, bool writer,
+                            double unit, cplx_d* ec, cplx_d* fc, cplx_d* kappa,
+                            double* sp_out, int* corr) {
+  KState* st = a.st;
+  const int i = threadIdx.x;
+  const int k = a.k, b = k - 1;
+  const double bk = sqrt(tot[1].re);
+  if (bk <= a.tol * fmax(1.0, fs.normT)) {
+    finish_basis(a, fs, k, NAN, NAN, NAN, -1, 0.0, 0.0, nullptr, writer, nullptr);
+    return false;
+  }
+  const double sp = 1.0 / bk;
+  const cplx_d zero{0.0, 0.0};
+  const bool in = i <= b;
+  const double ai = in ? fs.alpha[i] : 0.0, bi = in ? fs.offd[i] : 0.0;
+  const double bn = i < b ? fs.offd[i + 1] : 0.0;
+  const double ab = fs.alpha[b], bb = fs.offd[b], si = in ? fs.scale[i] : 0.0;
+  const cplx_d g = i < b ? fs.gprev[i] : zero;
+  const cplx_d gm = (in && i > 0) ? fs.gprev[i - 1] : zero;
+  const cplx_d gp = i + 1 < b ? fs.gprev[i + 1] : zero;
+  const cplx_d h = i + 1 < b ? fs.coef[i] : zero;
+  cplx_d E = zero;
+  if (i < b) {
+    E.re = bn * gp.re + (ai - ab) * g.re + bi * gm.re - bb * h.re;
+    E.im = bn * gp.im + (ai - ab) * g.im + bi * gm.im - bb * h.im;
+  } else if (i == b) {
+    E.re = -bb * gm.re;
+    E.im = bb * gm.im;
+  }
+  const cplx_d e{E.re * sp, E.im * sp};
+  const bool out = __any(fabs(e.re) > unit || fabs(e.im) > unit);
+  if (!out) E = zero;
+  const cplx_d Eb{__shfl(E.re, b, 64), __shfl(E.im, b, 64)};
+  const cplx_d em{__shfl_up(e.re, 1, 64), __shfl_up(e.im, 1, 64)};
+  const cplx_d ep{__shfl_down(e.re, 1, 64), __shfl_down(e.im, 1, 64)};
+  const double alpha = tot[0].re * sp * sp - 2.0 * Eb.re;
+  // beta_0 = 0 and beta_{i+1} of lane b = 0 end the three-term sums
+  cplx_d S{bi * (i > 0 ? em.re : 0.0) + (ai - alpha) * e.re + bn * ep.re,
+           bi * (i > 0 ? em.im : 0.0) + (ai - alpha) * e.im + bn * ep.im};
+  cplx_d F{S.re - bk * g.re, S.im - bk * g.im};
+  if (i == b) {
+    S.re += bk;
+    F.re += bk;
+  }
+  const cplx_d kap{alpha + Eb.re, Eb.im};
+  if (in) {
+    ec[i] = cplx_d{E.re * si, E.im * si};
+    fc[i] = cplx_d{F.re * si, F.im * si};
+  }
+  if (i == 0) {
+    *kappa = kap;
+    *sp_out = sp;
+    *corr = out ? 1 : 0;
+  }
+  if (writer) {
+    if (in) {
+      st->csub[i] = cplx_d{E.re * sp, E.im * sp};
+      st->cdiag[i] = S;
+    }
+    if (i == k) st->cdiag[k] = kap;
+    if (i == 0) {
+      st->alpha[k] = alpha;
+      st->offd[k] = bk;
+      st->scale[k] = sp;
+      st->normT[k & 1] = fmax(fs.normT, fabs(alpha) + bk);
+    }
+  }
+  return true;
+}
+
+// The overlaps g_i = <v_i|v_b>, h_i = <v_i|v_{b-1}> of a pair's base b = a.k from
+// pass P(b-2)'s totals (nb = b columns a set), into the state for pass P(b).
+__device__ void pair_overlaps(const LzArgs& a, const FinScalars& fs, const cplx_d* tot, double sb) {
+  const int i = threadIdx.x, b = a.k;
+  if (i >= b) return;
+  const double s1 = fs.scale[b - 1];
+  cplx_d g, h{0.0, 0.0};
+  if (i == b - 1) {
+    g = cplx_d{tot[i].re * s1 * sb, tot[i].im * s1 * sb};
+  } else {
+    const double f = fs.scale[i] * s1;
+    const cplx_d M{tot[b + i].re * f, tot[b + i].im * f}, N{tot[i].re * f, tot[i].im * f};
+    const cplx_d kap = fs.cdiag[b - 1], S = fs.cdiag[i], e = fs.csub[i];
+    h = cplx_d{M.re - e.re, M.im - e.im};
+    g = cplx_d{(N.re - (kap.re * M.re - kap.im * M.im) - S.re) * sb,
+               (N.im - (kap.re * M.im + kap.im * M.re) - S.im) * sb};
+  }
+  a.st->gcol[(b + 1) & 1][i] = g;
+  a.st->coef[b & 1][i] = h;
+}
+
+template <int MODE, int RB, typename V, int NR>
+__device__ __forceinline__ void bstore(V* __restrict__ p, uint32_t base, uint32_t lane, uint32_t wv,
+                                       uint32_t D, const V (&o)[NR]) {
+  if constexpr (MODE == kBPairs) {
+#pragma unroll
+    for (int q = 0; q < NR / 2; ++q)
+      *reinterpret_cast<float4*>(p + bpos<MODE, RB>(base, lane, wv, 2 * q)) =
+          float4{o[2 * q].x, o[2 * q].y, o[2 * q + 1].x, o[2 * q + 1].y};
+  } else {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const uint32_t s = bpos<MODE, RB>(base, lane, wv, r);
+      if (MODE == kBSlots || s < D) p[s] = o[r];
+    }
+  }
+}
+
+// Pass C(b), b = a.k: the scalar update of step b, then the three-term step on its
+// own.  Three vectors read, one written.  `alone` (b = 0, m even): the step stands
+// for itself, so its norm and overlap with v_0 are measured.
+template <typename R, int RB, int MODE, bool NT>
+__device__ __forceinline__ void pass_c_body(const LzArgs& a, uint32_t bl, uint32_t G) {
+  using V = typename VT<R>::T;
+  constexpr int NR = 1 << RB;
+  // one row a wavefront; static arrays alone would let the compiler put the scalar
+  // update's temporaries into 64 KB of LDS, and one block fit on a CU (20 us for 8)
+  extern __shared__ unsigned char smem_raw[];
+  double* wsum = reinterpret_cast<double*>(smem_raw);
+  __shared__ cplx_d tot[kMaxScal];
+  __shared__ FinScalars fs;
+  __shared__ cplx_d cf;
+  __shared__ double sk_s;
+  __shared__ int go;
+
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wv = uniform_u32(threadIdx.x >> 6);
+  const int b = a.k;
+  if (!gather_step(a, G, b, b == 0, fs, tot)) return;
+  if (wv == 0) {
+    const bool cont = step_update<true>(a, fs, tot, b, bl == 0, &cf, &sk_s, nullptr, nullptr);
+    if (lane == 0) go = cont ? 1 : 0;
+  }
+  __syncthreads();
+  if (!go) return;
+  const double sk = sk_s;
+  if (bl == 0 && wv == 0) pair_overlaps(a, fs, tot, sk);
+  const cplx_d c = cf;
+  const double c1 = b > 0 ? fs.scale[b - 1] / sk : 0.0;
+  const V* __restrict__ x = slot_ptr<V>(a, b);
+  const V* __restrict__ x1 = slot_ptr<V>(a, b > 0 ? b - 1 : 0);
+  const V* __restrict__ yv = reinterpret_cast<const V*>(a.yk);
+  V* __restrict__ out = reinterpret_cast<V*>(a.basis) + (size_t)b * a.geo.D;
+  const uint32_t iters = a.geo.ntiles / G;
+  const uint32_t D = a.geo.D;
+  double acc = 0.0;
+  for (uint32_t it = 0; it < iters; ++it) {
+    const uint32_t base = tile_of(a.geo, it, bl, G) << a.geo.TB;
+    V yo[NR], xo[NR], xm[NR], o[NR];
+    bload<MODE, RB, NT>(yv, base, lane, wv, D, yo);
+    bload<MODE, RB, NT>(x, base, lane, wv, D, xo);
+    bload<MODE, RB, NT>(x1, base, lane, wv, D, xm);  // b = 0: v_0 again, times 0
+    double sr = 0.0, si = 0.0, nn = 0.0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const double vr = xo[r].x, vi = xo[r].y;
+      o[r].x = (R)(sk * (double)yo[r].x - (c.re * vr - c.im * vi) - c1 * (double)xm[r].x);
+      o[r].y = (R)(sk * (double)yo[r].y - (c.re * vi + c.im * vr) - c1 * (double)xm[r].y);
+      const double wr = o[r].x, wi = o[r].y;
+      sr += vr * wr + vi * wi;
+      si += vr * wi - vi * wr;
+      nn += wr * wr + wi * wi;
+    }
+    bstore<MODE, RB>(out, base, lane, wv, D, o);
+    if (a.alone) acc += quad_sums(sr, si, nn, 0.0);
+  }
+  if (!a.alone) return;
+  if (lane < 3u) wsum[3u * wv + lane] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double sr = 0.0, si = 0.0, nn = 0.0;
+    for (uint32_t q = 0; q < (blockDim.x >> 6); ++q) {
+      sr += wsum[3 * q];
+      si += wsum[3 * q + 1];
+      nn += wsum[3 * q + 2];
+    }
+    a.partials[bl] = cplx_d{sr, si};
+    a.partials[kPartialRows + bl] = cplx_d{0.0, 0.0};
+    a.partials[(size_t)kNormCol * kPartialRows + bl] = cplx_d{nn, 0.0};
+  }
+}
+
+template <typename R, int RB, int MODE, bool NT = false>
+__global__ void __launch_bounds__(RB >= 3 ? 512 : 1024) k_pass_c(LzBatch B) {
+  const uint32_t G = B.job[0].geo.grid;
+  if (blockIdx.x < G) {
+    pass_c_body<R, RB, MODE, NT>(B.job[0], blockIdx.x, G);
+  } else {
+    pass_c_body<R, RB, MODE, NT>(B.job[1], blockIdx.x - G, G);
+  }
+}
+
+// Pass P(b), a.k = b + 1: both outputs of the pair in one pass over v_0..v_b.  Bound
+// by the stream: at L=20 complex64 1.4 us per window vector of 8.4 MB (6 TB/s) on 11
+// us of prologue, two vectors and stores; pass C takes 7 us.  A call at m = 20 613 ->
+// 500 us, at L=24, m = 24 11.4 -> 8.7 ms (pass B streamed as fast, twice as much).
+// Columns of its measurements: <v_i|Hp> in [0, b + 1), <v_{b+1}|w_{b+2}> in b + 1,
+// <v_i|p> from b + 2, ||w_{b+2}||^2 in kNormCol.
+template <typename R, int RB, int MODE, int NW, bool NT>
+__device__ __forceinline__ void pass_p_body(const LzArgs& a, uint32_t bl, uint32_t G) {
+  using V = typename VT<R>::T;
+  constexpr int NR = 1 << RB;
+  extern __shared__ unsigned char smem_raw[];
+  __shared__ cplx_d tot[kMaxScal];
+  __shared__ FinScalars fs;
+  __shared__ cplx_d ec[kMaxM], fc[kMaxM];
+  __shared__ cplx_d kap_s;
+  __shared__ double sp_s;
+  __shared__ int go, corr_s;
+
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wv = uniform_u32(threadIdx.x >> 6);
+  if (!gather_step(a, G, 0, true, fs, tot)) return;
+  if (wv == 0) {
+    const bool cont = pair_update(a, fs, tot, bl == 0, sizeof(R) == 4 ? 0x1p-24 : 0x1p-53, ec, fc,
+                                  &kap_s, &sp_s, &corr_s);
+    if (lane == 0) go = cont ? 1 : 0;
+  }
+  __syncthreads();
+  if (!go) return;
+
+  const int nwin = a.k;        // window vectors 0..b
+  const int nb = a.k + 1;
+  cplx_d* wacc = reinterpret_cast<cplx_d*>(smem_raw);
+  cplx_d* wrow = wacc + wv * kMaxScal;
+  for (int j = (int)lane; j <= 2 * nb; j += 64) wrow[j] = cplx_d{0.0, 0.0};
+  const auto add_quad = [&](int w, double t) {
+    if (lane < 4u) {
+      cplx_d& d = wrow[(lane < 2u ? 0 : nb) + w];
+      if (lane & 1u) {
+        d.im += t;
+      } else {
+        d.re += t;
+      }
+    }
+  };
+  const double sp = sp_s;
+  const bool corr = uniform_u32((uint32_t)corr_s) != 0;
+  const cplx_d kp{kap_s.re * sp, kap_s.im * sp};
+  const V* __restrict__ yv = reinterpret_cast<const V*>(a.yk);
+  V* pv = reinterpret_cast<V*>(a.basis) + (size_t)(a.k - 1) * a.geo.D;  // p, then v_{b+1}
+  V* __restrict__ out = reinterpret_cast<V*>(a.basis) + (size_t)a.k * a.geo.D;
+  const uint32_t iters = a.geo.ntiles / G;
+  const uint32_t D = a.geo.D;
+  for (uint32_t it = 0; it < iters; ++it) {
+    const uint32_t base = tile_of(a.geo, it, bl, G) << a.geo.TB;
+    V yo[NR], xo[NR];
+    bload<MODE, RB, NT>(yv, base, lane, wv, D, yo);
+    bload<MODE, RB, NT>(static_cast<const V*>(pv), base, lane, wv, D, xo);
+    double ar[NR], ai[NR], zr[NR], zi[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const double vr = xo[r].x, vi = xo[r].y;
+      ar[r] = vr;
+      ai[r] = vi;
+      zr[r] = sp * (double)yo[r].x - (kp.re * vr - kp.im * vi);
+      zi[r] = sp * (double)yo[r].y - (kp.re * vi + kp.im * vr);
+    }
+    for (int i = 0; i < nwin; i += NW) {
+      V q[NW][NR];
+#pragma unroll
+      for (int j = 0; j < NW; ++j) {
+        if (i + j < nwin) bload<MODE, RB, NT>(slot_ptr<V>(a, i + j), base, lane, wv, D, q[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < NW; ++j) {
+        if (i + j < nwin) {
+          const cplx_d c = ec[i + j], f = fc[i + j];
+          double sr = 0.0, si = 0.0, gr = 0.0, gi = 0.0;
+#pragma unroll
+          for (int r = 0; r < NR; ++r) {
+            const double vr = q[j][r].x, vi = q[j][r].y;
+            zr[r] -= f.re * vr - f.im * vi;
+            zi[r] -= f.re * vi + f.im * vr;
+            // p and Hp stay in their own precision: converted once, ahead of the loop,
+            // complex64 pairs would take 16 registers more and spill
+            if constexpr (sizeof(R) == 4)
+              asm("" : "+v"(yo[r].x), "+v"(yo[r].y), "+v"(xo[r].x), "+v"(xo[r].y));
+            const double yr = yo[r].x, yi = yo[r].y, xr = xo[r].x, xi = xo[r].y;
+            sr += vr * yr + vi * yi;
+            si += vr * yi - vi * yr;
+            gr += vr * xr + vi * xi;
+            gi += vr * xi - vi * xr;
+          }
+          if (corr) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+              const double vr = q[j][r].x, vi = q[j][r].y;
+              ar[r] -= c.re * vr - c.im * vi;
+              ai[r] -= c.re * vi + c.im * vr;
+            }
+          }
+          add_quad(i + j, quad_sums(sr, si, gr, gi));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    // store both; their overlap and the norm from the stored (rounded) values
+    V o1[NR], o2[NR];
+    double sr = 0.0, si = 0.0, nn = 0.0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      o1[r].x = (R)ar[r];
+      o1[r].y = (R)ai[r];
+      o2[r].x = (R)zr[r];
+      o2[r].y = (R)zi[r];
+      const double vr = o1[r].x, vi = o1[r].y, wr = o2[r].x, wi = o2[r].y;
+      sr += vr * wr + vi * wi;
+      si += vr * wi - vi * wr;
+      nn += wr * wr + wi * wi;
+    }
+    if (corr) bstore<MODE, RB>(pv, base, lane, wv, D, o1);
+    bstore<MODE, RB>(out, base, lane, wv, D, o2);
+    const double t = quad_sums(sr, si, nn, 0.0);
+    if (lane < 2u) {
+      cplx_d& d = wrow[nb - 1];
+      if (lane & 1u) {
+        d.im += t;
+      } else {
+        d.re += t;
+      }
+    } else if (lane == 2u) {
+      wrow[2 * nb].re += t;
+    }
+  }
+  __syncthreads();
+  block_totals(wacc, 2 * nb + 1, tot);
+  for (int j = threadIdx.x; j < 2 * nb; j += blockDim.x) a.partials[(size_t)j * kPartialRows + bl] = tot[j];
+  if (threadIdx.x == 0) a.partials[(size_t)kNormCol * kPartialRows + bl] = cplx_d{tot[2 * nb].re, 0.0};
+}
+
+template <typename R, int RB, int MODE, int NW, bool NT = false>
+__global__ void __launch_bounds__(RB >= 3 ? 512 : 1024) k_pass_p(LzBatch B) {
+  const uint32_t G = B.job[0].geo.grid;
+  if (blockIdx.x < G) {
+    pass_p_body<R, RB, MODE, NW, NT>(B.job[0], blockIdx.x, G);
+  } else {
+    pass_p_body<R, RB, MODE, NW, NT>(B.job[1], blockIdx.x - G, G);
   }
 }
 
@@ -890,7 +1262,7 @@ __global__ void __launch_bounds__(64) k_finish(LzBatch B) {
   __shared__ cplx_d tot[kMaxScal];
   __shared__ FinScalars fs;
   const LzArgs& a = B.job[blockIdx.x];
-  if (gather_step(a, a.geo.grid, 0, fs, tot))
+  if (gather_step(a, a.geo.grid, 0, a.k == 0, fs, tot))
     step_update(a, fs, tot, 0, true, nullptr, nullptr, nullptr, nullptr);
 }
 
@@ -1315,11 +1687,32 @@ hipError_t launch_hv_r(const HvArgs& a, const Geo& g, const void* v, void* w, hi
   }
 }
 
-template <typename R, int RB>
-hipError_t launch_pass(bool pass_a, const LzBatch& lb, int njobs, hipStream_t s) {
+// The launches of a Lanczos step: pass A, pass B, or a pair's pass C and pass P.
+enum Pass { kPassA, kPassB, kPassC, kPassP };
+
+template <typename R, int RB, int MODE, bool NT>
+hipError_t launch_stream_pass(Pass which, const LzBatch& lb, int njobs, hipStream_t s) {
   const Geo& g = lb.job[0].geo;
   const dim3 grid(g.grid * njobs), block(64 << g.WB);
-  if (pass_a) {
+  // window vectors per round trip: 32 bytes a thread
+  constexpr int units = 8 / ((1 << RB) * (int)(sizeof(R) / 4));
+  constexpr int NW = units < 1 ? 1 : units;
+  const size_t red = ((size_t)1 << g.WB) * kMaxScal * sizeof(cplx_d);
+  if (which == kPassB) {
+    kg_launch((k_pass_b<R, RB, MODE, NT>), grid, block, red, s, lb);
+  } else if (which == kPassC) {
+    kg_launch((k_pass_c<R, RB, MODE, NT>), grid, block, 3 * sizeof(double) << g.WB, s, lb);
+  } else {
+    kg_launch((k_pass_p<R, RB, MODE, NW, NT>), grid, block, red, s, lb);
+  }
+  return hipGetLastError();
+}
+
+template <typename R, int RB>
+hipError_t launch_pass(Pass which, const LzBatch& lb, int njobs, hipStream_t s) {
+  const Geo& g = lb.job[0].geo;
+  const dim3 grid(g.grid * njobs), block(64 << g.WB);
+  if (which == kPassA) {
     bool pairs = sizeof(R) == 4 && RB >= 2 && pairs_tiling(g);
     for (int j = 0; j < njobs; ++j) {
       const LzArgs& q = lb.job[j];
@@ -1333,7 +1726,6 @@ hipError_t launch_pass(bool pass_a, const LzBatch& lb, int njobs, hipStream_t s)
     }
     kg_launch((k_pass_a<R, RB>), grid, block, lds_bytes<R>(g), s, lb);
   } else {
-    const size_t red = ((size_t)1 << g.WB) * kMaxScal * sizeof(cplx_d);
     // 16-byte pairs need whole tiles and 16-byte aligned vectors (the boundary
     // requires the alignment; checked again here, since a misaligned pair is
     // not an option)
@@ -1344,44 +1736,24 @@ hipError_t launch_pass(bool pass_a, const LzBatch& lb, int njobs, hipStream_t s)
     }
     // a basis larger than the Infinity Cache is streamed with nontemporal loads
     const bool nt = streamed_past_cache(lb.job[0].m, g.D, sizeof(typename VT<R>::T));
-    if (g.small) {
-      // vectors shorter than their tiles (the reduced basis): two window
-      // vectors per round trip as well (the L=25, K=12 centred gradient
-      // 639 -> 630 ms)
-      if constexpr (sizeof(R) == 4 && RB == 2)
-        kg_launch((k_pass_b<R, RB, kBMasked, 2>), grid, block, red, s, lb);
-      else
-        kg_launch((k_pass_b<R, RB, kBMasked>), grid, block, red, s, lb);
-    } else if (pairs) {
-      // 2^11-amplitude complex64 tiles and larger: two window vectors per round
-      // trip instead of four (timed forward sweeps, m = 20: 644 -> 615 us per
-      // Krylov call at L=20, 12.80 -> 12.70 ms at L=24; at the 2^10 tiles of
-      // L=18 two were 1-2 % slower)
-      constexpr int PM = (sizeof(R) == 4 && RB >= 1) ? kBPairs : kBSlots;
-      if constexpr (sizeof(R) == 4 && RB == 2) {
-        if (g.TB >= 11) {
-          if (nt) kg_launch((k_pass_b<R, RB, kBPairs, 2, true>), grid, block, red, s, lb);
-          else kg_launch((k_pass_b<R, RB, kBPairs, 2>), grid, block, red, s, lb);
-          return hipGetLastError();
-        }
-      }
-      if (nt) kg_launch((k_pass_b<R, RB, PM, 0, true>), grid, block, red, s, lb);
-      else kg_launch((k_pass_b<R, RB, PM>), grid, block, red, s, lb);
-    } else {
-      if (nt) kg_launch((k_pass_b<R, RB, kBSlots, 0, true>), grid, block, red, s, lb);
-      else kg_launch((k_pass_b<R, RB, kBSlots>), grid, block, red, s, lb);
-    }
+    constexpr int PM = (sizeof(R) == 4 && RB >= 1) ? kBPairs : kBSlots;
+    if (g.small) return launch_stream_pass<R, RB, kBMasked, false>(which, lb, njobs, s);
+    if (pairs)
+      return nt ? launch_stream_pass<R, RB, PM, true>(which, lb, njobs, s)
+                : launch_stream_pass<R, RB, PM, false>(which, lb, njobs, s);
+    return nt ? launch_stream_pass<R, RB, kBSlots, true>(which, lb, njobs, s)
+              : launch_stream_pass<R, RB, kBSlots, false>(which, lb, njobs, s);
   }
   return hipGetLastError();
 }
 
 template <typename R>
-hipError_t launch_pass_r(bool pass_a, const LzBatch& lb, int njobs, hipStream_t s) {
+hipError_t launch_pass_r(Pass which, const LzBatch& lb, int njobs, hipStream_t s) {
   switch (lb.job[0].geo.RB) {
-    case 0: return launch_pass<R, 0>(pass_a, lb, njobs, s);
-    case 1: return launch_pass<R, 1>(pass_a, lb, njobs, s);
-    case 2: return launch_pass<R, 2>(pass_a, lb, njobs, s);
-    default: return launch_pass<R, 3>(pass_a, lb, njobs, s);
+    case 0: return launch_pass<R, 0>(which, lb, njobs, s);
+    case 1: return launch_pass<R, 1>(which, lb, njobs, s);
+    case 2: return launch_pass<R, 2>(which, lb, njobs, s);
+    default: return launch_pass<R, 3>(which, lb, njobs, s);
   }
 }
 
@@ -1432,18 +1804,25 @@ hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss,
   // windows: all stored vectors (full re-orthogonalisation) or the last two;
   // the last step only forms alpha
   int i0p = 0;
+  // full windows two steps at a time; an even m leaves the first step by itself
+  // (against a pass B per step, both timed, m = 4 / 8 / 24: complex64 L=20 81 -> 80,
+  // 184 -> 169, 783 -> 619 us; complex128 L=22 442 -> 438, 1125 -> 1068, 5361 -> 4210)
+  const bool paired = c0.reorth != 0;
+  const int first = (c0.m - 1) & 1;
   for (int k = 0; k < c0.m; ++k) {
     const bool last = (k == c0.m - 1);
-    const int i0 = last ? k : (c0.reorth ? 0 : (k > 0 ? k - 1 : 0));
+    const Pass second = !paired ? kPassB : (k < first || !((k - first) & 1)) ? kPassC : kPassP;
+    // pass A sums the measurements that pass C reads; pass P needs none
+    const int i0 = (last || second == kPassP) ? k : (c0.reorth ? 0 : (k > 0 ? k - 1 : 0));
     const int i0n = (k + 1 == c0.m - 1) ? k + 1 : (c0.reorth ? 0 : k);
     for (int j = 0; j < n; ++j) {
       lb.job[j].k = k;
       lb.job[j].i0 = i0;
       lb.job[j].i0n = i0n;
-      lb.job[j].i0p = i0p;
+      lb.job[j].i0p = paired ? 0 : i0p;
+      lb.job[j].alone = k < first;
     }
     i0p = i0;
-    const int nwin = k - i0 + 1;
     if (c0.pe) {
       // reduced basis: y = H v_k by the gather kernel, then pass A on the given y
       for (int j = 0; j < n; ++j) {
@@ -1463,18 +1842,20 @@ hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss,
       const size_t red = ((size_t)1 << g.WB) * kMaxScal * sizeof(cplx_d);
       kg_launch((k_pass_a_y<R>), dim3(g.grid * n), dim3(64 << g.WB), red, s, lb);
       if ((e = hipGetLastError()) != hipSuccess) return e;
-    } else if ((e = launch_pass_r<R>(true, lb, n, s)) != hipSuccess) {
+    } else if ((e = launch_pass_r<R>(kPassA, lb, n, s)) != hipSuccess) {
       return e;
     }
     // algorithmic bytes: v_k is read and y = H v_k is written (not in the
     // last step; the reduced basis reads the given y instead)
-    (void)nwin;
     if (prof) profiler_stop(prof, s, kProfPassA, (1 + ((last && !c0.pe) ? 0 : 1)) * vb);
     if (!last) {
       if (prof) profiler_start(prof, s);
-      if ((e = launch_pass_r<R>(false, lb, n, s)) != hipSuccess) return e;
-      // y_k and the window are read, v_{k+1} is written
-      if (prof) profiler_stop(prof, s, kProfPassB, (nwin + 2) * vb);
+      if ((e = launch_pass_r<R>(second, lb, n, s)) != hipSuccess) return e;
+      // pass B: y_k and the window are read, v_{k+1} is written; pass C: y, v_k and
+      // v_{k-1}; pass P: y, p and the window, one written (both when p is corrected)
+      const int moved = second == kPassC ? (k > 0 ? 4 : 3)
+                        : second == kPassP ? k + 3 : k - i0 + 3;
+      if (prof) profiler_stop(prof, s, kProfPassB, moved * vb);
     }
   }
   // the last step's scalar update and the small exponential
