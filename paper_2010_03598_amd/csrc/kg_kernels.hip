@@ -1769,9 +1769,9 @@ hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss,
     return launch_sweeps(c0.prec, jobs, n, s);
   }
   // one launch per step; a call that KG_TILE_BITS or KG_NO_FUSED keeps from the
-  // one-block form takes the two passes
+  // one-block form takes the passes (its workspace has no room for the steps)
   const bool steps = c0.geo.D <= kStepMaxD && (!c0.pe || c0.pe->nbr);
-  if (steps && !sweep_fits(c0.prec, c0.geo.D, c0.m, sweep_neighbours(c0.pe, c0.hv.L))) {
+  if (steps && !sweep_fits(c0.prec, c0.geo.D, c0.m, 0)) {
     KrylovCall c[kMaxJobs];
     for (int j = 0; j < n; ++j) {
       c[j] = calls[j];
