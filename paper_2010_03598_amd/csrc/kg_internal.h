@@ -21,7 +21,7 @@ constexpr int kPartialRows = kMaxGrid + kMaxGrid / 64;  // block rows + group ro
 constexpr int kLzGrid = 512;
 // The Infinity Cache (memory-side cache) of the MI355X.  A Krylov basis of m
 // vectors well beyond it is streamed from HBM at every step, and the
-// streaming passes (pass B, the combination) then load it nontemporally.
+// streaming passes (B, C, P, the combination) then load it nontemporally.
 // Timed forward sweeps per Krylov call, plain against nontemporal loads:
 // complex64 m=20 L=22 (671 MB basis) 2.29 -> 2.21 ms, m=24 L=23 6.33 -> 5.87
 // ms, L=24 12.75 -> 11.56 ms; complex128 L=22 4.48 -> 4.04 ms, m=24 L=24
