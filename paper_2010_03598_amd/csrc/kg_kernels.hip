@@ -1694,7 +1694,9 @@ template <typename R, int RB, int MODE, bool NT>
 hipError_t launch_stream_pass(Pass which, const LzBatch& lb, int njobs, hipStream_t s) {
   const Geo& g = lb.job[0].geo;
   const dim3 grid(g.grid * njobs), block(64 << g.WB);
-  // window vectors per round trip: 32 bytes a thread
+  // window vectors per round trip: 32 bytes a thread, two complex64 vectors at the
+  // 2^11 tiles (one: L=22, m=20 1751 -> 1770 us, L=23 3476 -> 3543, L=20 the same;
+  // four spill)
   constexpr int units = 8 / ((1 << RB) * (int)(sizeof(R) / 4));
   constexpr int NW = units < 1 ? 1 : units;
   const size_t red = ((size_t)1 << g.WB) * kMaxScal * sizeof(cplx_d);
