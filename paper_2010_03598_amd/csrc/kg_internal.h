@@ -63,8 +63,8 @@ struct KState {
   double fid;
   double g0;              // centred gradient: the bracket at the start of slice 1
   uint32_t counters[kMaxGrid / 64 + 4];  // arrivals in the running grid reduction
-  // (a pair of steps, pass C(b) and pass P(b), keeps g in gcol[(b+1)&1], h in
-  // coef[b&1], E_i / beta in csub, the known parts of the next overlaps in cdiag)
+  // (a pair of steps, pass C(b) and pass P(b), keeps g in gcol[(b+1)&1], E in
+  // csub, the known parts of the next overlaps in cdiag)
   // totals of pass B(k-1)'s measurement columns (window order) and, after
   // them, of its norm column, summed by helper wavefronts of pass A(k)
   cplx_d colsum[kMaxScal];

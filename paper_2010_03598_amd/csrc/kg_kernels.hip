@@ -285,7 +285,7 @@ constexpr int kMaxJobs = 2;
 // Columns of the partials table (column major, one row per block).  Pass B(k)
 // writes its measurements <u_j|y_k> in columns [0, nb) and <u_j|u_k> in
 // [nb, 2nb) (window order) and its part of ||w||^2 in kNormCol; pass A(k)
-// writes its parts of <v_k|y_k> and ||v_k||^2 in kACol and kACol + 1, which
+// writes its parts of <v_k|y_k> and (||v_k||^2, ||y_k||^2) in kACol and kACol + 1, which
 // no pass B writes.
 constexpr int kACol = 2 * kMaxM;
 constexpr int kNormCol = kMaxScal - 1;
@@ -425,7 +425,7 @@ __device__ __forceinline__ void store_y(const Tile<R, RB>& T, typename VT<R>::T*
 // The reduced sums of step k into `tot` (LDS) and the earlier steps' scalars
 // into `fs` (LDS), in the layout the scalar update reads:
 //   tot[0, 2nb)   pass B(k-1)'s measurement totals (window dots of step k),
-//   tot[2nb]      <v_k|y_k>,  tot[2nb + 1] = (||v_k||^2, 0)  (with `norm` only),
+//   tot[2nb]      <v_k|y_k>,  tot[2nb + 1] = (||v_k||^2, ||y_k||^2)  (with `norm` only),
 //   tot[2nb + 2]  ||w||^2 of pass B(k-1), the square of the next off-diagonal.
 // The totals of pass B(k-1)'s columns come from pass A(k)'s helper
 // wavefronts (KState::colsum); pass A(k)'s own columns are summed here over
@@ -578,7 +578,7 @@ __device__ bool step_update(const LzArgs& a, const FinScalars& fs, const cplx_d*
 }
 
 // Pass A(k): y = H v_k, stored as y_k (not at the last step), and this block's
-// parts of <v_k|y> and ||v_k||^2 (row bl of the A columns).  No grid-wide
+// parts of <v_k|y>, ||v_k||^2 and ||y||^2 (row bl of the A columns).  No grid-wide
 // reduction: the scalar update of step k runs in the prologue of pass B(k)
 // (of the combination at the last step), in every block.  Helper wavefronts
 // (wavefront w of block b takes column b + w G) sum pass B(k-1)'s measurement
@@ -592,13 +592,14 @@ __device__ __forceinline__ void pass_a_body(const LzArgs& a, uint32_t bl, uint32
   constexpr int NR = 1 << RB;
   extern __shared__ unsigned char smem_raw[];
   V* lds = reinterpret_cast<V*>(smem_raw);
-  __shared__ double wsum[16][3];
+  __shared__ double wsum[16][4];
 
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wv = uniform_u32(threadIdx.x >> 6);
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t eb = lane | (wv << (6 + RB));
-  // this wavefront's totals: lane 0 Re<v_k|y>, lane 1 Im<v_k|y>, lane 2 ||v_k||^2
+  // this wavefront's totals: lane 0 Re<v_k|y>, lane 1 Im<v_k|y>, lane 2 ||v_k||^2,
+  // lane 3 ||y||^2
   double acc = 0.0;
 
   const double u = control_value(a.hv);
@@ -632,30 +633,32 @@ __device__ __forceinline__ void pass_a_body(const LzArgs& a, uint32_t bl, uint32
       hv_tile<R, RB>(T, a.hv, a.geo, tile, x, lds, u);
       if (a.k + 1 < a.m) store_y<R, RB>(T, yk, base, eb, a.geo);
     }
-    // <v_k|y> and ||v_k||^2 from registers
-    double sr = 0.0, si = 0.0, nn = 0.0;
+    // <v_k|y>, ||v_k||^2 and ||y||^2 from registers
+    double sr = 0.0, si = 0.0, nn = 0.0, yy = 0.0;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       const double vr = T.xr[r], vi = T.xi[r], yr = T.yr[r], yi = T.yi[r];
       sr += vr * yr + vi * yi;
       si += vr * yi - vi * yr;
       nn += vr * vr + vi * vi;
+      yy += yr * yr + yi * yi;
     }
-    acc += quad_sums(sr, si, nn, 0.0);
+    acc += quad_sums(sr, si, nn, yy);
   }
   if (finished) return;
   // this block's row of the A columns, the wavefronts summed in order
-  if (lane < 3u) wsum[wv][lane] = acc;
+  if (lane < 4u) wsum[wv][lane] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
-    double sr = 0.0, si = 0.0, nn = 0.0;
+    double sr = 0.0, si = 0.0, nn = 0.0, yy = 0.0;
     for (uint32_t q = 0; q < nw; ++q) {
       sr += wsum[q][0];
       si += wsum[q][1];
       nn += wsum[q][2];
+      yy += wsum[q][3];
     }
     a.partials[(size_t)kACol * kPartialRows + bl] = cplx_d{sr, si};
-    a.partials[(size_t)(kACol + 1) * kPartialRows + bl] = cplx_d{nn, 0.0};
+    a.partials[(size_t)(kACol + 1) * kPartialRows + bl] = cplx_d{nn, yy};
   }
   // helpers: totals of pass B(k-1)'s columns (written by the previous launch)
   const int nb = (a.k > 0 && a.i0 < a.k) ? a.k - a.i0p : 0;
@@ -883,39 +886,100 @@ __global__ void __launch_bounds__(RB >= 3 ? 512 : 1024) k_pass_b(LzBatch B) {
 
 // Two Lanczos steps per pass over the window (full re-orthogonalisation).  A pass
 // B(k) is bound by the stream of v_0..v_k; here one stream serves two steps:
-//   pass A(b), pass C(b):      p = s_b y - alpha_b v_b - beta_b v_{b-1}, the
-//                              three-term step alone, stored in v_{b+1}'s place;
-//   pass A(b+1), pass P(b):    with y = H p: v_{b+1} = p - sum E_i v_i and
-//                              w_{b+2} = H v_{b+1} - alpha v_{b+1} - beta v_b
-//                              - (overlaps), both linear in p, H p and the window.
+//   pass A(b), pass C(b):      v_{b+1} = p = s_b y - alpha_b v_b - beta_b v_{b-1}, the
+//                              three-term step, and - sum E_i v_i where p's overlaps
+//                              E_i = <v_i|p> with the window matter;
+//   pass A(b+1), pass P(b):    with y = H p: w_{b+2} = H v_{b+1} - alpha v_{b+1}
+//                              - beta v_b - (overlaps).
 // What <v_i|p> is follows, as in pass B, from the overlaps of v_b and v_{b-1} that
-// pass P(b-2) measured and H's tridiagonal form; and H v_{b+1} = H p - sum E_i H v_i
-// needs no second product, since H v_i is a sum of three window vectors.  While
-// every |e_i| = |<v_i|p>| / ||p|| is below the unit roundoff of the stored vectors
-// (random states: about that over sqrt(D)), p stands as v_{b+1}: storing the
-// difference would round the vector a second time by more than it corrects.  Larger
-// ones are taken out.  w_{b+2} is always corrected.  Per pair the vectors moved
-// fall from 2b + 7 to b + 8.
+// pass P(b-2) measured and H's tridiagonal form, before p is formed.  While every
+// |E_i| / ||p|| is below the unit roundoff of the stored vectors (random states: about
+// that over sqrt(D)), removing them would not change what is stored, and p reads three
+// vectors; then the overlaps enter w_{b+2} alone.  Otherwise p is projected on the whole
+// window like pass B's vectors, before it is rounded and before its norm is tested: near
+// the end of a basis p is rounding noise, whose overlaps are of its own size, and a
+// correction after the fact ended in NaN.  w_{b+2} is always corrected.  Per pair the
+// vectors moved fall from 2b + 7 to b + 8 (2b + 7 again where p is projected).
+// A vector that overlaps an earlier one by more than a half is no new direction: the
+// invariant space is exhausted in the vectors' precision though the breakdown test,
+// whose tolerance is a few units of roundoff of ||T||, let noise through; the basis ends
+// before it.  (The measured overlaps say so two steps later: the last two vectors of a
+// basis go unchecked.)
 //
 // In normalised vectors, with g_i = <v_i|v_b>, h_i = <v_i|v_{b-1}> and
 // beta = ||p||:
-//   beta e_i = beta_{i+1} g_{i+1} + (alpha_i - alpha_b) g_i + beta_i g_{i-1}
-//              - beta_b h_i                      (i < b; the exact 1s cancel),
-//   beta e_b = -beta_b conj(g_{b-1}),            E_i = beta e_i or all 0,
-//   alpha    = <p|Hp> / beta^2 - 2 Re E_b,
+//   E_i = beta_{i+1} g_{i+1} + (alpha_i - alpha_b) g_i + beta_i g_{i-1}
+//         - beta_b h_i                           (i < b; the exact 1s cancel),
+//   E_b = -beta_b conj(g_{b-1}),   e_i = E_i / beta, or 0 where p was projected,
+//   alpha    = <p|Hp> / beta^2,
 //   f_i      = beta_i e_{i-1} + (alpha_i - alpha) e_i + beta_{i+1} e_{i+1} - beta g_i,
-//   w_{b+2}  = (H p - (alpha + E_b) p) / beta - beta v_b - sum f_i v_i.
-// Pass P measures <v_i|p>, <v_i|Hp> and, from its outputs, <v_{b+1}|w_{b+2}> and
+//   w_{b+2}  = (H p - alpha p) / beta - beta v_b - sum f_i v_i.
+// Pass P measures <v_i|p>, <v_i|Hp> and, from its output, <v_{b+1}|w_{b+2}> and
 // ||w_{b+2}||^2; pass C(b+2) turns them into the next g and h.
 
+// The overlaps of a pair's p, on wavefront 0 of every block of pass C(b) (b = a.k, sb =
+// 1/||v_b||): g and h from pass P(b-2)'s totals (nb = b columns a set), then E_i.  Returns
+// kPairProject when p is projected; then ec[i] holds E_i on the stored vectors, i in [0, b].
+// ||p||^2 comes from ||y||^2 less the two coefficients; where these cancel to where the
+// estimate means little, any overlap counts.  kPairEnd: v_{b-1} or v_b is no new direction.
+// State, with `writer`: g, and E in csub (0 if p is projected), or the finished basis.
+enum { kPairPlain, kPairProject, kPairEnd };
+__device__ int pair_overlaps(const LzArgs& a, const FinScalars& fs, const cplx_d* tot, double sb,
+                              double unit, bool writer, cplx_d* ec) {
+  const int i = threadIdx.x, b = a.k;
+  const cplx_d zero{0.0, 0.0};
+  cplx_d g = zero, h = zero;
+  if (i < b) {
+    const double s1 = fs.scale[b - 1];
+    if (i == b - 1) {
+      g = cplx_d{tot[i].re * s1 * sb, tot[i].im * s1 * sb};
+    } else {
+      const double f = fs.scale[i] * s1;
+      h = cplx_d{tot[b + i].re * f, tot[b + i].im * f};
+      const cplx_d N{tot[i].re * f, tot[i].im * f}, S = fs.cdiag[i];
+      const double al = fs.alpha[b - 1];
+      g = cplx_d{(N.re - al * h.re - S.re) * sb, (N.im - al * h.im - S.im) * sb};
+    }
+  }
+  const bool old_h = __any(h.re * h.re + h.im * h.im > 0.25);
+  if (old_h || __any(g.re * g.re + g.im * g.im > 0.25)) {
+    if (writer) finish_basis(a, fs, old_h ? b - 1 : b, NAN, NAN, NAN, -1, 0.0, 0.0, nullptr, true, nullptr);
+    return kPairEnd;
+  }
+  const cplx_d gm{__shfl_up(g.re, 1, 64), __shfl_up(g.im, 1, 64)};
+  const cplx_d gp{__shfl_down(g.re, 1, 64), __shfl_down(g.im, 1, 64)};   // 0 from lane b on
+  const double ab = tot[2 * b].re * sb * sb, bb = b > 0 ? 1.0 / sb : 0.0;
+  cplx_d E = zero;
+  if (i < b) {
+    const double ai = fs.alpha[i] - ab, bi = i > 0 ? fs.offd[i] : 0.0;
+    const double bn = i + 1 < b ? fs.offd[i + 1] : 0.0;
+    E.re = bn * gp.re + ai * g.re + (i > 0 ? bi * gm.re : 0.0) - bb * h.re;
+    E.im = bn * gp.im + ai * g.im + (i > 0 ? bi * gm.im : 0.0) - bb * h.im;
+  } else if (i == b && b > 0) {
+    E.re = -bb * gm.re;
+    E.im = bb * gm.im;
+  }
+  const double normT = fmax(b > 0 ? fs.normT : 0.0, fabs(ab) + bb);
+  const double b2 = sb * sb * tot[2 * b + 1].im - ab * ab - bb * bb;
+  const double lim = b2 > 1e-10 * normT * normT ? unit * unit * b2 : 0.0;
+  const bool corr = __any(E.re * E.re > lim || E.im * E.im > lim);
+  if (i <= b) {
+    const double si = i < b ? fs.scale[i] : sb;
+    ec[i] = cplx_d{E.re * si, E.im * si};
+  }
+  if (writer && i <= b) {
+    a.st->csub[i] = corr ? zero : E;
+    if (i < b) a.st->gcol[(b + 1) & 1][i] = g;
+  }
+  return corr ? kPairProject : kPairPlain;
+}
+
 // The scalars of pass P on wavefront 0 (a.k = b + 1; tot[0] = <p|Hp>, tot[1].re =
-// ||p||^2): the coefficients of the two outputs on the stored window vectors into ec
-// and fc, that of p / beta into *kappa, whether p is corrected into *corr (`unit`: the
-// unit roundoff).  State, with `writer`: csub[i] = E_i / beta, cdiag[i] = the part of <v_i|w_{b+2}> known before the stream, cdiag[b+1] = kappa.
-// On entry fs.gprev holds g and fs.coef h.  False after a breakdown.
+// ||p||^2; fs.gprev holds g and fs.csub E): the coefficients of w_{b+2} on the stored
+// window vectors into fc, alpha and 1/||p||.  State, with `writer`: cdiag[i], the part of
+// <v_i|w_{b+2}> known before the stream.  False after a breakdown.
 __device__ bool pair_update(const LzArgs& a, const FinScalars& fs, const cplx_d* tot, bool writer,
-                            double unit, cplx_d* ec, cplx_d* fc, cplx_d* kappa,
-                            double* sp_out, int* corr) {
+                            cplx_d* fc, double* alpha_out, double* sp_out) {
   KState* st = a.st;
   const int i = threadIdx.x;
   const int k = a.k, b = k - 1;
@@ -927,52 +991,29 @@ __device__ bool pair_update(const LzArgs& a, const FinScalars& fs, const cplx_d*
   const double sp = 1.0 / bk;
   const cplx_d zero{0.0, 0.0};
   const bool in = i <= b;
-  const double ai = in ? fs.alpha[i] : 0.0, bi = in ? fs.offd[i] : 0.0;
-  const double bn = i < b ? fs.offd[i + 1] : 0.0;
-  const double ab = fs.alpha[b], bb = fs.offd[b], si = in ? fs.scale[i] : 0.0;
+  const double ai = in ? fs.alpha[i] : 0.0, bi = (in && i > 0) ? fs.offd[i] : 0.0;
+  const double bn = i < b ? fs.offd[i + 1] : 0.0, si = in ? fs.scale[i] : 0.0;
   const cplx_d g = i < b ? fs.gprev[i] : zero;
-  const cplx_d gm = (in && i > 0) ? fs.gprev[i - 1] : zero;
-  const cplx_d gp = i + 1 < b ? fs.gprev[i + 1] : zero;
-  const cplx_d h = i + 1 < b ? fs.coef[i] : zero;
-  cplx_d E = zero;
-  if (i < b) {
-    E.re = bn * gp.re + (ai - ab) * g.re + bi * gm.re - bb * h.re;
-    E.im = bn * gp.im + (ai - ab) * g.im + bi * gm.im - bb * h.im;
-  } else if (i == b) {
-    E.re = -bb * gm.re;
-    E.im = bb * gm.im;
-  }
+  const cplx_d E = in ? fs.csub[i] : zero;
   const cplx_d e{E.re * sp, E.im * sp};
-  const bool out = __any(fabs(e.re) > unit || fabs(e.im) > unit);
-  if (!out) E = zero;
-  const cplx_d Eb{__shfl(E.re, b, 64), __shfl(E.im, b, 64)};
   const cplx_d em{__shfl_up(e.re, 1, 64), __shfl_up(e.im, 1, 64)};
   const cplx_d ep{__shfl_down(e.re, 1, 64), __shfl_down(e.im, 1, 64)};
-  const double alpha = tot[0].re * sp * sp - 2.0 * Eb.re;
+  const double alpha = tot[0].re * sp * sp;
   // beta_0 = 0 and beta_{i+1} of lane b = 0 end the three-term sums
-  cplx_d S{bi * (i > 0 ? em.re : 0.0) + (ai - alpha) * e.re + bn * ep.re,
-           bi * (i > 0 ? em.im : 0.0) + (ai - alpha) * e.im + bn * ep.im};
+  cplx_d S{(i > 0 ? bi * em.re : 0.0) + (ai - alpha) * e.re + bn * ep.re,
+           (i > 0 ? bi * em.im : 0.0) + (ai - alpha) * e.im + bn * ep.im};
   cplx_d F{S.re - bk * g.re, S.im - bk * g.im};
   if (i == b) {
     S.re += bk;
     F.re += bk;
   }
-  const cplx_d kap{alpha + Eb.re, Eb.im};
-  if (in) {
-    ec[i] = cplx_d{E.re * si, E.im * si};
-    fc[i] = cplx_d{F.re * si, F.im * si};
-  }
+  if (in) fc[i] = cplx_d{F.re * si, F.im * si};
   if (i == 0) {
-    *kappa = kap;
+    *alpha_out = alpha;
     *sp_out = sp;
-    *corr = out ? 1 : 0;
   }
   if (writer) {
-    if (in) {
-      st->csub[i] = cplx_d{E.re * sp, E.im * sp};
-      st->cdiag[i] = S;
-    }
-    if (i == k) st->cdiag[k] = kap;
+    if (in) st->cdiag[i] = S;
     if (i == 0) {
       st->alpha[k] = alpha;
       st->offd[k] = bk;
@@ -981,27 +1022,6 @@ __device__ bool pair_update(const LzArgs& a, const FinScalars& fs, const cplx_d*
     }
   }
   return true;
-}
-
-// The overlaps g_i = <v_i|v_b>, h_i = <v_i|v_{b-1}> of a pair's base b = a.k from
-// pass P(b-2)'s totals (nb = b columns a set), into the state for pass P(b).
-__device__ void pair_overlaps(const LzArgs& a, const FinScalars& fs, const cplx_d* tot, double sb) {
-  const int i = threadIdx.x, b = a.k;
-  if (i >= b) return;
-  const double s1 = fs.scale[b - 1];
-  cplx_d g, h{0.0, 0.0};
-  if (i == b - 1) {
-    g = cplx_d{tot[i].re * s1 * sb, tot[i].im * s1 * sb};
-  } else {
-    const double f = fs.scale[i] * s1;
-    const cplx_d M{tot[b + i].re * f, tot[b + i].im * f}, N{tot[i].re * f, tot[i].im * f};
-    const cplx_d kap = fs.cdiag[b - 1], S = fs.cdiag[i], e = fs.csub[i];
-    h = cplx_d{M.re - e.re, M.im - e.im};
-    g = cplx_d{(N.re - (kap.re * M.re - kap.im * M.im) - S.re) * sb,
-               (N.im - (kap.re * M.im + kap.im * M.re) - S.im) * sb};
-  }
-  a.st->gcol[(b + 1) & 1][i] = g;
-  a.st->coef[b & 1][i] = h;
 }
 
 template <int MODE, int RB, typename V, int NR>
@@ -1021,10 +1041,11 @@ __device__ __forceinline__ void bstore(V* __restrict__ p, uint32_t base, uint32_
   }
 }
 
-// Pass C(b), b = a.k: the scalar update of step b, then the three-term step on its
-// own.  Three vectors read, one written.  `alone` (b = 0, m even): the step stands
-// for itself, so its norm and overlap with v_0 are measured.
-template <typename R, int RB, int MODE, bool NT>
+// Pass C(b), b = a.k: the scalar update of step b, then the three-term step.  Three
+// vectors read, one written; b - 1 more read where p is projected on the window.
+// `alone` (b = 0, m even): the step stands for itself, so its norm and overlap with
+// v_0 are measured.
+template <typename R, int RB, int MODE, int NW, bool NT>
 __device__ __forceinline__ void pass_c_body(const LzArgs& a, uint32_t bl, uint32_t G) {
   using V = typename VT<R>::T;
   constexpr int NR = 1 << RB;
@@ -1034,24 +1055,35 @@ __device__ __forceinline__ void pass_c_body(const LzArgs& a, uint32_t bl, uint32
   double* wsum = reinterpret_cast<double*>(smem_raw);
   __shared__ cplx_d tot[kMaxScal];
   __shared__ FinScalars fs;
+  __shared__ cplx_d ec[kMaxM];
   __shared__ cplx_d cf;
   __shared__ double sk_s;
-  __shared__ int go;
+  __shared__ int go, corr_s;
 
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wv = uniform_u32(threadIdx.x >> 6);
   const int b = a.k;
-  if (!gather_step(a, G, b, b == 0, fs, tot)) return;
+  if (!gather_step(a, G, b, true, fs, tot)) return;
   if (wv == 0) {
     const bool cont = step_update<true>(a, fs, tot, b, bl == 0, &cf, &sk_s, nullptr, nullptr);
-    if (lane == 0) go = cont ? 1 : 0;
+    // 1/||v_b|| again: lane 0's LDS write is not ordered before the other lanes' reads
+    const double sb = b > 0 ? 1.0 / sqrt(tot[2 * b + 2].re) : 1.0 / sqrt(tot[2 * b + 1].re);
+    const int pair = cont ? pair_overlaps(a, fs, tot, sb, sizeof(R) == 4 ? 0x1p-24 : 0x1p-53, bl == 0, ec)
+                          : kPairEnd;
+    if (lane == 0) {
+      go = pair != kPairEnd ? 1 : 0;
+      corr_s = pair == kPairProject ? 1 : 0;
+    }
   }
   __syncthreads();
   if (!go) return;
   const double sk = sk_s;
-  if (bl == 0 && wv == 0) pair_overlaps(a, fs, tot, sk);
-  const cplx_d c = cf;
-  const double c1 = b > 0 ? fs.scale[b - 1] / sk : 0.0;
+  const bool corr = uniform_u32((uint32_t)corr_s) != 0;
+  cplx_d c = cf, c1{b > 0 ? fs.scale[b - 1] / sk : 0.0, 0.0};
+  if (corr) {
+    c = cplx_d{c.re + ec[b].re, c.im + ec[b].im};
+    c1 = cplx_d{c1.re + ec[b - 1].re, ec[b - 1].im};
+  }
   const V* __restrict__ x = slot_ptr<V>(a, b);
   const V* __restrict__ x1 = slot_ptr<V>(a, b > 0 ? b - 1 : 0);
   const V* __restrict__ yv = reinterpret_cast<const V*>(a.yk);
@@ -1065,12 +1097,40 @@ __device__ __forceinline__ void pass_c_body(const LzArgs& a, uint32_t bl, uint32
     bload<MODE, RB, NT>(yv, base, lane, wv, D, yo);
     bload<MODE, RB, NT>(x, base, lane, wv, D, xo);
     bload<MODE, RB, NT>(x1, base, lane, wv, D, xm);  // b = 0: v_0 again, times 0
+    double zr[NR], zi[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const double vr = xo[r].x, vi = xo[r].y, ur = xm[r].x, ui = xm[r].y;
+      zr[r] = sk * (double)yo[r].x - (c.re * vr - c.im * vi) - (c1.re * ur - c1.im * ui);
+      zi[r] = sk * (double)yo[r].y - (c.re * vi + c.im * vr) - (c1.re * ui + c1.im * ur);
+    }
+    if (corr) {
+      for (int i = 0; i < b - 1; i += NW) {
+        V q[NW][NR];
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+          if (i + j < b - 1) bload<MODE, RB, NT>(slot_ptr<V>(a, i + j), base, lane, wv, D, q[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+          if (i + j < b - 1) {
+            const cplx_d e = ec[i + j];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+              const double vr = q[j][r].x, vi = q[j][r].y;
+              zr[r] -= e.re * vr - e.im * vi;
+              zi[r] -= e.re * vi + e.im * vr;
+            }
+          }
+        }
+      }
+    }
     double sr = 0.0, si = 0.0, nn = 0.0;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       const double vr = xo[r].x, vi = xo[r].y;
-      o[r].x = (R)(sk * (double)yo[r].x - (c.re * vr - c.im * vi) - c1 * (double)xm[r].x);
-      o[r].y = (R)(sk * (double)yo[r].y - (c.re * vi + c.im * vr) - c1 * (double)xm[r].y);
+      o[r].x = (R)zr[r];
+      o[r].y = (R)zi[r];
       const double wr = o[r].x, wi = o[r].y;
       sr += vr * wr + vi * wi;
       si += vr * wi - vi * wr;
@@ -1095,17 +1155,17 @@ __device__ __forceinline__ void pass_c_body(const LzArgs& a, uint32_t bl, uint32
   }
 }
 
-template <typename R, int RB, int MODE, bool NT = false>
+template <typename R, int RB, int MODE, int NW, bool NT = false>
 __global__ void __launch_bounds__(RB >= 3 ? 512 : 1024) k_pass_c(LzBatch B) {
   const uint32_t G = B.job[0].geo.grid;
   if (blockIdx.x < G) {
-    pass_c_body<R, RB, MODE, NT>(B.job[0], blockIdx.x, G);
+    pass_c_body<R, RB, MODE, NW, NT>(B.job[0], blockIdx.x, G);
   } else {
-    pass_c_body<R, RB, MODE, NT>(B.job[1], blockIdx.x - G, G);
+    pass_c_body<R, RB, MODE, NW, NT>(B.job[1], blockIdx.x - G, G);
   }
 }
 
-// Pass P(b), a.k = b + 1: both outputs of the pair in one pass over v_0..v_b.  Bound
+// Pass P(b), a.k = b + 1: w_{b+2} in one pass over v_0..v_b.  Bound
 // by the stream: at L=20 complex64 1.4 us per window vector of 8.4 MB (6 TB/s) on 11
 // us of prologue, two vectors and stores; pass C takes 7 us.  A call at m = 20 613 ->
 // 500 us, at L=24, m = 24 11.4 -> 8.7 ms (pass B streamed as fast, twice as much).
@@ -1118,17 +1178,15 @@ __device__ __forceinline__ void pass_p_body(const LzArgs& a, uint32_t bl, uint32
   extern __shared__ unsigned char smem_raw[];
   __shared__ cplx_d tot[kMaxScal];
   __shared__ FinScalars fs;
-  __shared__ cplx_d ec[kMaxM], fc[kMaxM];
-  __shared__ cplx_d kap_s;
-  __shared__ double sp_s;
-  __shared__ int go, corr_s;
+  __shared__ cplx_d fc[kMaxM];
+  __shared__ double alpha_s, sp_s;
+  __shared__ int go;
 
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wv = uniform_u32(threadIdx.x >> 6);
   if (!gather_step(a, G, 0, true, fs, tot)) return;
   if (wv == 0) {
-    const bool cont = pair_update(a, fs, tot, bl == 0, sizeof(R) == 4 ? 0x1p-24 : 0x1p-53, ec, fc,
-                                  &kap_s, &sp_s, &corr_s);
+    const bool cont = pair_update(a, fs, tot, bl == 0, fc, &alpha_s, &sp_s);
     if (lane == 0) go = cont ? 1 : 0;
   }
   __syncthreads();
@@ -1149,11 +1207,9 @@ __device__ __forceinline__ void pass_p_body(const LzArgs& a, uint32_t bl, uint32
       }
     }
   };
-  const double sp = sp_s;
-  const bool corr = uniform_u32((uint32_t)corr_s) != 0;
-  const cplx_d kp{kap_s.re * sp, kap_s.im * sp};
+  const double sp = sp_s, kp = alpha_s * sp;
   const V* __restrict__ yv = reinterpret_cast<const V*>(a.yk);
-  V* pv = reinterpret_cast<V*>(a.basis) + (size_t)(a.k - 1) * a.geo.D;  // p, then v_{b+1}
+  const V* __restrict__ pv = slot_ptr<V>(a, a.k);
   V* __restrict__ out = reinterpret_cast<V*>(a.basis) + (size_t)a.k * a.geo.D;
   const uint32_t iters = a.geo.ntiles / G;
   const uint32_t D = a.geo.D;
@@ -1161,15 +1217,12 @@ __device__ __forceinline__ void pass_p_body(const LzArgs& a, uint32_t bl, uint32
     const uint32_t base = tile_of(a.geo, it, bl, G) << a.geo.TB;
     V yo[NR], xo[NR];
     bload<MODE, RB, NT>(yv, base, lane, wv, D, yo);
-    bload<MODE, RB, NT>(static_cast<const V*>(pv), base, lane, wv, D, xo);
-    double ar[NR], ai[NR], zr[NR], zi[NR];
+    bload<MODE, RB, NT>(pv, base, lane, wv, D, xo);
+    double zr[NR], zi[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      const double vr = xo[r].x, vi = xo[r].y;
-      ar[r] = vr;
-      ai[r] = vi;
-      zr[r] = sp * (double)yo[r].x - (kp.re * vr - kp.im * vi);
-      zi[r] = sp * (double)yo[r].y - (kp.re * vi + kp.im * vr);
+      zr[r] = sp * (double)yo[r].x - kp * (double)xo[r].x;
+      zi[r] = sp * (double)yo[r].y - kp * (double)xo[r].y;
     }
     for (int i = 0; i < nwin; i += NW) {
       V q[NW][NR];
@@ -1180,7 +1233,7 @@ __device__ __forceinline__ void pass_p_body(const LzArgs& a, uint32_t bl, uint32
 #pragma unroll
       for (int j = 0; j < NW; ++j) {
         if (i + j < nwin) {
-          const cplx_d c = ec[i + j], f = fc[i + j];
+          const cplx_d f = fc[i + j];
           double sr = 0.0, si = 0.0, gr = 0.0, gi = 0.0;
 #pragma unroll
           for (int r = 0; r < NR; ++r) {
@@ -1197,35 +1250,24 @@ __device__ __forceinline__ void pass_p_body(const LzArgs& a, uint32_t bl, uint32
             gr += vr * xr + vi * xi;
             gi += vr * xi - vi * xr;
           }
-          if (corr) {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-              const double vr = q[j][r].x, vi = q[j][r].y;
-              ar[r] -= c.re * vr - c.im * vi;
-              ai[r] -= c.re * vi + c.im * vr;
-            }
-          }
           add_quad(i + j, quad_sums(sr, si, gr, gi));
           __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
-    // store both; their overlap and the norm from the stored (rounded) values
-    V o1[NR], o2[NR];
+    // store w; its overlap with v_{b+1} and its norm from the stored (rounded) values
+    V o[NR];
     double sr = 0.0, si = 0.0, nn = 0.0;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      o1[r].x = (R)ar[r];
-      o1[r].y = (R)ai[r];
-      o2[r].x = (R)zr[r];
-      o2[r].y = (R)zi[r];
-      const double vr = o1[r].x, vi = o1[r].y, wr = o2[r].x, wi = o2[r].y;
+      o[r].x = (R)zr[r];
+      o[r].y = (R)zi[r];
+      const double vr = xo[r].x, vi = xo[r].y, wr = o[r].x, wi = o[r].y;
       sr += vr * wr + vi * wi;
       si += vr * wi - vi * wr;
       nn += wr * wr + wi * wi;
     }
-    if (corr) bstore<MODE, RB>(pv, base, lane, wv, D, o1);
-    bstore<MODE, RB>(out, base, lane, wv, D, o2);
+    bstore<MODE, RB>(out, base, lane, wv, D, o);
     const double t = quad_sums(sr, si, nn, 0.0);
     if (lane < 2u) {
       cplx_d& d = wrow[nb - 1];
@@ -1703,7 +1745,7 @@ hipError_t launch_stream_pass(Pass which, const LzBatch& lb, int njobs, hipStrea
   if (which == kPassB) {
     kg_launch((k_pass_b<R, RB, MODE, NT>), grid, block, red, s, lb);
   } else if (which == kPassC) {
-    kg_launch((k_pass_c<R, RB, MODE, NT>), grid, block, 3 * sizeof(double) << g.WB, s, lb);
+    kg_launch((k_pass_c<R, RB, MODE, NW, NT>), grid, block, 3 * sizeof(double) << g.WB, s, lb);
   } else {
     kg_launch((k_pass_p<R, RB, MODE, NW, NT>), grid, block, red, s, lb);
   }
@@ -1854,7 +1896,7 @@ hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss,
       if (prof) profiler_start(prof, s);
       if ((e = launch_pass_r<R>(second, lb, n, s)) != hipSuccess) return e;
       // pass B: y_k and the window are read, v_{k+1} is written; pass C: y, v_k and
-      // v_{k-1}; pass P: y, p and the window, one written (both when p is corrected)
+      // v_{k-1} (the window too where p is projected); pass P: y, p and the window
       const int moved = second == kPassC ? (k > 0 ? 4 : 3)
                         : second == kPassP ? k + 3 : k - i0 + 3;
       if (prof) profiler_stop(prof, s, kProfPassB, moved * vb);
