@@ -45,7 +45,19 @@ __device__ __forceinline__ double turned(double v) {
   return (threadIdx.x & 1u) ? -p : p;
 }
 
-// Four amplitudes of four vectors: dots into d0 + d1, update into zr, zi.
+// Four amplitudes of four vectors: dots into d0 + d1.
+template <typename V>
+__device__ __forceinline__ void unit_mfma(const V (&q)[4], const double (&b)[4],
+                                          const double (&bp)[4], double& d0, double& d1) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const double qr = q[t].x, qi = q[t].y;
+    d0 = __builtin_amdgcn_mfma_f64_4x4x4f64(qr, b[t], d0, 0, 0, 0);
+    d1 = __builtin_amdgcn_mfma_f64_4x4x4f64(qi, bp[t], d1, 0, 0, 0);
+  }
+}
+
+// The same with the update into zr, zi.
 template <typename V>
 __device__ __forceinline__ void unit_rows(const V (&q)[4], const double (&b)[4],
                                           const double (&bp)[4], cplx_d w, double (&zr)[4],
@@ -60,9 +72,14 @@ __device__ __forceinline__ void unit_rows(const V (&q)[4], const double (&b)[4],
   }
 }
 
-// The dots of four vectors over the unit: every lane of row l >> 4 (the
-// vector) holds the total of column l & 3.
-__device__ __forceinline__ double unit_dots(double v) {
+// The dots of four vectors over the unit from their two accumulators: every lane of
+// row l >> 4 (the vector) holds the total of column l & 3.  A v_mfma_f64_4x4x4 result
+// may be read by the vector unit after six wait states; the wait is written out here,
+// since hipcc 7.2 leaves it out where a branch ends between the two (the sums then
+// held the registers' old values).
+__device__ __forceinline__ double unit_dots(double d0, double d1) {
+  asm volatile("s_nop 7" : "+v"(d0), "+v"(d1));
+  double v = d0 + d1;
   v += dpp_f64<0x124>(v);   // row_ror:4 and :8: the instruction's four blocks
   v += dpp_f64<0x128>(v);
   return v;

@@ -427,15 +427,15 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
       double e0 = 0.0, e1 = 0.0, f0 = 0.0, f1 = 0.0;
       unit_rows(q[0], b, bp, cf[i0 + w0 + (int)c], zr, zi, e0, e1);
       if (two) unit_rows(q[1], b, bp, cf[i0 + w0 + 4 + (int)c], zr, zi, f0, f1);
-      const auto put = [&](int w, double v) {
-        const double e = unit_dots(v);
+      const auto put = [&](int w, double d0, double d1) {
+        const double e = unit_dots(d0, d1);
         if ((lane & 12u) == 0u && w < nw) {
           double& d = row[4 * w + (int)c];
           d = r == 0 ? e : d + e;
         }
       };
-      put(w0 + (int)(lane >> 4), e0 + e1);
-      if (two) put(w0 + 4 + (int)(lane >> 4), f0 + f1);
+      put(w0 + (int)(lane >> 4), e0, e1);
+      if (two) put(w0 + 4 + (int)(lane >> 4), f0, f1);
       if (more) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {

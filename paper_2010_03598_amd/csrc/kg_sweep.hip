@@ -7,27 +7,25 @@
 // step.  Independent sweeps (the forward states and the costates of a
 // gradient, the columns of an operator) are the blocks of one launch.
 //
-// Such a step is a serial chain on one compute unit: H v from LDS, the window,
-// the sums over the block, the scalars.  It is bound by that chain's latency,
-// so it is kept short: one amplitude per thread with its neighbour list in
-// registers; the single-pass step of kg_step.h, which needs one block-wide sum
-// where projecting against the finished u_k needs the sum before the update;
-// the dots by MFMA, with u_k and y_k as two more rows of the window, so that
-// one pass gives every measurement; and with up to four wavefronts (one per
-// SIMD) every wavefront computes the scalars itself, which saves a second
-// barrier and a round trip through LDS.  With more wavefronts they would
-// compete for the SIMDs, and wavefront 0 computes for all.
+// Such a step is a serial chain on one compute unit: H v from LDS, the window's
+// dots, the sums over the block, the scalars, the update.  It is bound by that
+// chain's latency, so it is kept short: one amplitude per thread with its neighbour
+// list in registers; the dots by MFMA, ||u_k||^2 among them; and every wavefront
+// computes the scalars itself, which saves a barrier and a round trip through LDS.
 //
-// Measured against one launch per call with two block-wide sums per step, in
-// complex128: the gradient of 50 slices at D = 256, m = 10 takes 1.14 ms
-// (2.88), the centred one of 584 slices at D = 146 13.9 ms (45.2), one call
-// alone at D = 256 25.6 us (29.5), at D = 512 and m = 12 39.6 us (42.0).  Of a step's 2.2 us the H v takes 0.3, the
-// rows and their MFMA 0.6, the sums over the wavefronts 0.3 and the scalars
-// 0.7.
+// Every dot is taken with y_k = H u_k itself, and w_k is complete in FP64 before it
+// is rounded: the single-pass step of kg_step.h (one barrier a step here) defers a
+// subtraction of the size of alpha_k past that rounding, and its accuracy falls with
+// |alpha_k| / beta_{k+1}.
 //
-// LDS: slot i (stride DS) holds u_i; w'_k waits in slot k + 2 until step
-// k + 2 overwrites it with its u, so H v of step k + 1 can read it while
-// u_{k+1} is written.
+// Measured against one launch per call with two block-wide sums and three barriers per
+// step, in complex128: the gradient of 50 slices at D = 256, m = 10 takes 0.91 ms
+// (2.88), the centred one of 584 slices at D = 146 10.9 ms (45.2), one call alone at
+// D = 256 20.1 us (29.5), at D = 512 and m = 12 37.3 us (42.0).  The single-pass step
+// took 1.18 ms, 14.2 ms, 25.5 us and 39.3 us: its scalars are a longer chain than the
+// second barrier.
+//
+// LDS: slot i (stride DS) holds u_i, then one slot of y in units of wavefronts.
 
 #include <hip/hip_runtime.h>
 
@@ -47,8 +45,7 @@ namespace {
 
 constexpr int kSweepNbr = 12;             // neighbours per row held in registers
 constexpr size_t kSweepLds = 160u << 10;  // LDS of a compute unit
-constexpr size_t kSweepStatic = sizeof(LzStore) + 256;   // static LDS of the larger form
-constexpr int kRedThreads = 256;          // up to here every wavefront computes the scalars
+constexpr int kSweepThreads = 512;        // largest block
 
 struct SweepBatch {
   SweepJob job[kSweepJobs];
@@ -63,18 +60,16 @@ __host__ __device__ inline uint32_t slot_stride(uint32_t D) {
 }
 
 // Rows per thread: one up to eight wavefronts; beyond, two (16 wavefronts of
-// one row would run four to a SIMD and repeat the per-wavefront work).  At
-// D = 512, m = 12, complex128: one row per thread 39.6 us, two on four
-// wavefronts 42.4.
-inline int sweep_rows(uint32_t D) { return D <= 2u * kRedThreads ? 1 : 2; }
+// one row would run four to a SIMD and repeat the per-wavefront work).
+inline int sweep_rows(uint32_t D) { return D <= (uint32_t)kSweepThreads ? 1 : 2; }
 
 template <typename R>
 inline size_t sweep_lds_bytes(uint32_t D, int m) {
   const size_t na = sweep_rows(D), nw = (D + 64 * na - 1) / (64 * na);
-  const size_t vecs = ((size_t)(m + 1) * slot_stride<R>(D) + na * nw * 64) * sizeof(typename VT<R>::T);
-  const size_t meas = 2 * nw * (size_t)(4 * (m + 2)) * sizeof(double);
-  const size_t coef = (nw <= kRedThreads / 64 ? nw : 1) * 2 * (kMaxM + 8) * sizeof(cplx_d);
-  return ((vecs + 15) / 16) * 16 + meas + coef + 64;
+  const size_t vecs = ((size_t)m * slot_stride<R>(D) + na * nw * 64) * sizeof(typename VT<R>::T);
+  const size_t meas = nw * (size_t)(4 * m) * sizeof(double);
+  const size_t coef = nw * kMaxM * sizeof(cplx_d);
+  return ((vecs + 15) / 16) * 16 + meas + coef;
 }
 
 // Address of call q's output.
@@ -97,9 +92,8 @@ __device__ __forceinline__ V* sweep_out(const SweepJob& J, int q, int j) {
   return reinterpret_cast<V*>(J.out + at * J.vb);
 }
 
-// NA: rows per thread, blockDim apart.  TH: largest block.  RED: every
-// wavefront computes the scalars.  PE: the reduced basis.
-template <typename R, int NA, int TH, bool RED, bool PE>
+// NA: rows per thread, blockDim apart.  TH: largest block.  PE: the reduced basis.
+template <typename R, int NA, int TH, bool PE>
 __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
   using V = typename VT<R>::T;
   const SweepJob& J = Bt.job[blockIdx.x];
@@ -110,28 +104,15 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
   const uint32_t D = J.D, DS = slot_stride<R>(D);
   const int m = J.m;
   V* ub = reinterpret_cast<V*>(smem_raw);
-  V* yst = ub + (size_t)(m + 1) * DS;
-  const uint32_t vecs = (uint32_t)(m + 1) * DS + NA * T;
+  V* yst = ub + (size_t)m * DS;
+  const uint32_t vecs = (uint32_t)m * DS + NA * T;
   double* wred = reinterpret_cast<double*>(smem_raw + (((size_t)vecs * sizeof(V) + 15) / 16) * 16);
-  const uint32_t rowlen = 4u * (uint32_t)(m + 2);
-  cplx_d* cfs = reinterpret_cast<cplx_d*>(wred + 2 * nwv * rowlen) + (RED ? wv * 2u * (kMaxM + 8) : 0u);
-  cplx_d* dcs = cfs + kMaxM + 8;
-  // wavefront 0's scalars when it computes for all
-  struct Shared {
-    LzStore lz;
-    StepNext nx;
-    double normT, beta0, sk, rp, gp;
-    int m_eff, go;
-  };
-  __shared__ Shared sh;
+  const uint32_t rowlen = 4u * (uint32_t)m;
+  cplx_d* cfs = reinterpret_cast<cplx_d*>(wred + nwv * rowlen) + wv * (uint32_t)kMaxM;
 
   // rows past D (and the padding that whole units read) stay finite
   if (D != NA * T)
     for (uint32_t i = tid; i < vecs; i += T) ub[i] = V{(R)0, (R)0};
-  if (RED || wv == 0) {
-    cfs[lane] = cplx_d{0.0, 0.0};
-    if (lane < 8u) cfs[64 + lane] = cplx_d{0.0, 0.0};
-  }
 
   // this thread's rows: diagonal d0 + u dz, neighbours and their weights
   const int L = J.hv.L;
@@ -203,102 +184,70 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
 #pragma unroll
   for (int n = 0; n < NA; ++n)
     xin[n] = in[n] ? reinterpret_cast<const V*>(J.in)[row[n]] : V{(R)0, (R)0};
-  uint32_t par = 0;
   double unext = J.u ? J.u[J.j0 - 1] : J.hv.u_val;
   for (int q = 0; q < J.n; ++q) {
     const int j = J.j0 + q * J.dj;
     const double u = unext;
     if (J.u && q + 1 < J.n) unext = J.u[j + J.dj - 1];
     const R cu = sx ? (R)(0.5 * u) : (R)0;
-    LzLane s;
-    LzRun run;
-    StepNext nx{cplx_d{0.0, 0.0}, 1.0, 1.0};
+    // the recurrence's scalars, vector i in lane i of every wavefront
+    double al = 0.0, of = 0.0, sc = 0.0;
+    double normT = 0.0, beta0 = 0.0;
+    int me = m;
 #pragma unroll
     for (int n = 0; n < NA; ++n)
       if (in[n]) ub[row[n]] = xin[n];
-    if (RED || wv == 0) cfs[lane] = cplx_d{lane == 1u ? -1.0 : 0.0, 0.0};   // y of step 0
-    if constexpr (!RED) {
-      if (wv == 0) put_lane(sh.lz, s);
-    }
     __syncthreads();
-    V up[NA], yp[NA];
     for (int k = 0; k < m; ++k) {
       const bool last = k == m - 1;
-      const int i0 = window_first(k, m, J.reorth), nw = k - i0;
-      V* uk = ub + (size_t)k * DS;
-      const V* src = k == 0 ? ub : ub + (size_t)(k + 1) * DS;
+      const int i0 = window_first(k, m, J.reorth), nrows = k - i0 + 1;
+      const V* uk = ub + (size_t)k * DS;
+      R hr[NA], hi[NA];
 #pragma unroll
       for (int n = 0; n < NA; ++n) {
-        // ---- H v of the source on this row, in the vector type
-        const V xs = src[row[n]], xf = src[flip[n]];
+        // ---- y = H u_k on this row, in the vector type
+        const V xs = uk[row[n]], xf = uk[flip[n]];
         const R diag = d0[n] + (R)u * dz[n];
-        R hr = diag * xs.x, hi = diag * xs.y;
+        R yr = diag * xs.x, yi = diag * xs.y;
         // four neighbours' reads in flight together; unused slots have weight 0
 #pragma unroll
         for (int i = 0; i < kSweepNbr; i += 4) {
           if (i < slots) {
             V x[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = src[nb[n][i + e]];
+            for (int e = 0; e < 4; ++e) x[e] = uk[nb[n][i + e]];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              hr += wt[n][i + e] * x[e].x;
-              hi += wt[n][i + e] * x[e].y;
+              yr += wt[n][i + e] * x[e].x;
+              yi += wt[n][i + e] * x[e].y;
             }
           }
         }
-        hr += cu * xf.x;
-        hi += cu * xf.y;
-        // ---- u_k and y_k, rounded as stored
-        V uo, yo;
-        if (k == 0) {
-          uo = xs;
-          yo.x = hr;
-          yo.y = hi;
-        } else {
-          const double sg = nx.sig;
-          uo.x = (R)(sg * (double)xs.x - (nx.c.re * (double)up[n].x - nx.c.im * (double)up[n].y));
-          uo.y = (R)(sg * (double)xs.y - (nx.c.re * (double)up[n].y + nx.c.im * (double)up[n].x));
-          yo.x = (R)(sg * (double)hr - (nx.c.re * (double)yp[n].x - nx.c.im * (double)yp[n].y));
-          yo.y = (R)(sg * (double)hi - (nx.c.re * (double)yp[n].y + nx.c.im * (double)yp[n].x));
-          if (in[n]) uk[row[n]] = uo;
-        }
-        if (!in[n]) uo = yo = V{(R)0, (R)0};
-        yst[tid + n * T] = yo;
-        up[n] = uo;
-        yp[n] = yo;
+        yr += cu * xf.x;
+        yi += cu * xf.y;
+        hr[n] = in[n] ? yr : (R)0;
+        hi[n] = in[n] ? yi : (R)0;
+        yst[tid + n * T] = V{hr[n], hi[n]};
       }
       wave_lds_fence();
-      // ---- rows [i0, k), u_k, y_k against (y_k, u_k), a unit of 64 per n
+      // ---- rows [i0, k] against (y, u_k), a unit of 64 per n
       double b[NA][4], bp[NA][4];
 #pragma unroll
       for (int n = 0; n < NA; ++n) {
-        const V* src2 = c < 2u ? yst : uk;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const uint32_t sa = ((wv + nwv * n) << 6) + unit_amp(t, a);
-          const R v = reinterpret_cast<const R*>(src2 + sa)[c & 1u];
+          const R v = reinterpret_cast<const R*>((c < 2u ? yst : uk) + sa)[c & 1u];
           b[n][t] = sa < D ? (double)v : 0.0;
           bp[n][t] = turned(b[n][t]);
         }
       }
-      const int nrows = nw + (last ? 1 : 2);
-      double zr[NA][4], zi[NA][4];
-#pragma unroll
-      for (int n = 0; n < NA; ++n) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) zr[n][t] = zi[n][t] = 0.0;
-      }
-      double* wrow = wred + (par * nwv + wv) * rowlen;
+      double* wrow = wred + wv * rowlen;
       for (int r0 = 0; r0 < nrows; r0 += 8) {
         const bool two = r0 + 4 < nrows;
-        const auto at = [&](int r) {
-          return r < nw ? ub + (size_t)(i0 + r) * DS : (r == nw ? uk : yst);
-        };
+        const auto at = [&](int r) { return ub + (size_t)(i0 + min(r, nrows - 1)) * DS; };
         const V* p0 = at(r0 + (int)c);
         const V* p1 = at(r0 + 4 + (int)c);
-        const cplx_d w0 = cfs[min(i0 + r0 + (int)c, kMaxM + 7)];
-        const cplx_d w1 = cfs[min(i0 + r0 + 4 + (int)c, kMaxM + 7)];
         double e0 = 0.0, e1 = 0.0, f0 = 0.0, f1 = 0.0;
 #pragma unroll
         for (int n = 0; n < NA; ++n) {
@@ -310,111 +259,107 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) q1[t] = p1[s0 + unit_amp(t, a)];
           }
-          unit_rows(q0, b[n], bp[n], w0, zr[n], zi[n], e0, e1);
-          if (two) unit_rows(q1, b[n], bp[n], w1, zr[n], zi[n], f0, f1);
+          unit_mfma(q0, b[n], bp[n], e0, e1);
+          if (two) unit_mfma(q1, b[n], bp[n], f0, f1);
         }
         const int r = r0 + (int)(lane >> 4);
-        const double e = unit_dots(e0 + e1);
+        const double e = unit_dots(e0, e1);
         if ((lane & 12u) == 0u && r < nrows) wrow[4 * r + (int)c] = e;
         if (two) {
-          const double f = unit_dots(f0 + f1);
+          const double f = unit_dots(f0, f1);
           if ((lane & 12u) == 0u && r + 4 < nrows) wrow[4 * (r + 4) + (int)c] = f;
-        }
-      }
-      if (!last) {
-#pragma unroll
-        for (int n = 0; n < NA; ++n) {
-          const uint32_t sa = ((wv + nwv * n) << 6) + unit_amp((int)c, a);
-          const double wr = -quad_z(zr[n]), wi = -quad_z(zi[n]);
-          if (sa < D) ub[(size_t)(k + 2) * DS + sa] = V{(R)wr, (R)wi};
         }
       }
       __syncthreads();
       // ---- totals over the wavefronts, in order, and the scalars
-      bool go = false;
-      if (RED || wv == 0) {
-        const int r = (int)lane - i0;
-        double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
-        if (r >= 0 && r < nrows) {
-          const double* p = wred + par * nwv * rowlen + 4 * r;
-          for (uint32_t w0 = 0; w0 < nwv; w0 += 4) {
-            double2 x[4], y[4];
+      const int r = (int)lane - i0;
+      double tr = 0.0, ti = 0.0, tg = 0.0;   // <u_i|y>, Re <u_i|u_k>
+      if (r >= 0 && r < nrows) {
+        const double* p = wred + 4 * r;
+        for (uint32_t w0 = 0; w0 < nwv; w0 += 4) {
+          double2 x[4];
+          double g[4];
 #pragma unroll
-            for (uint32_t e = 0; e < 4; ++e) {
-              const double2* pw = reinterpret_cast<const double2*>(p + min(w0 + e, nwv - 1u) * rowlen);
-              x[e] = pw[0];
-              y[e] = pw[1];
-            }
+          for (uint32_t e = 0; e < 4; ++e) {
+            const double* pw = p + min(w0 + e, nwv - 1u) * rowlen;
+            x[e] = *reinterpret_cast<const double2*>(pw);
+            g[e] = pw[2];
+          }
 #pragma unroll
-            for (uint32_t e = 0; e < 4; ++e) {
-              if (w0 + e < nwv) {
-                t0 += x[e].x;
-                t1 += x[e].y;
-                t2 += y[e].x;
-                t3 += y[e].y;
-              }
+          for (uint32_t e = 0; e < 4; ++e) {
+            if (w0 + e < nwv) {
+              tr += x[e].x;
+              ti += x[e].y;
+              tg += g[e];
             }
           }
         }
-        const cplx_d A{t0, t1}, G{t2, t3};
-        if constexpr (!RED) {
-          get_lane(sh.lz, s);
-          if (k > 0) {
-            run.normT = sh.normT;
-            run.beta0 = sh.beta0;
-            run.sk = sh.sk;
-            run.rp = sh.rp;
-            run.gp = sh.gp;
-          }
-        }
-        go = step_scalars(s, run, k, m, J.reorth, J.tol, A, G, lane_cplx(A, k), lane_value(t2, k),
-                          lane_value(t0, min(k + 1, 63)), nx);
-        // row k + 2 of the next step is its y
-        cfs[lane] = (int)lane == k + 2 ? cplx_d{-nx.s, 0.0} : s.cw;
-        if constexpr (!RED) {
-          put_lane(sh.lz, s);
-          if (lane == 0) {
-            sh.normT = run.normT;
-            sh.beta0 = run.beta0;
-            sh.sk = run.sk;
-            sh.rp = run.rp;
-            sh.gp = run.gp;
-            sh.m_eff = run.m_eff;
-            sh.nx = nx;
-            sh.go = go ? 1 : 0;
-          }
-        }
       }
-      par ^= 1u;
-      if constexpr (RED) {
-        wave_lds_fence();
-      } else {
-        __syncthreads();
-        nx = sh.nx;
-        go = sh.go != 0;
+      const double gkk = lane_value(tg, k), akk = lane_value(tr, k);
+      if (k == 0 && !(gkk > 0.0)) {
+        // a zero input gives a zero output; a non-finite one a NaN output
+        me = gkk == 0.0 ? 0 : 1;
+        beta0 = NAN;
+        break;
       }
-      if (!go) break;
-    }
-    // ---- exp(-itT) e_1 and the combination
-    if constexpr (RED) {
-      dcs[lane] = comb_coef(s, run, J.t);
+      const double sk = rsqrt(gkk);
+      const double nrm = gkk > 0.0 ? gkk * sk : gkk;   // u_k = 0 is a breakdown
+      const double off = k > 0 ? nrm : 0.0;
+      if (k == 0) beta0 = nrm;
+      // ||u_k|| small against ||T||: an invariant Krylov space of dimension k
+      if (k > 0 && off <= J.tol * fmax(1.0, normT)) {
+        me = k;
+        break;
+      }
+      const double alpha = sk * sk * akk;
+      normT = fmax(normT, fabs(alpha) + off);
+      if ((int)lane == k) {
+        al = alpha;
+        of = off;
+        sc = sk;
+      }
+      if (last) break;
+      // ---- w = s_k y - sum_i c_i u_i, c_i = s_i^2 s_k <u_i|y>, stored as u_{k+1}
+      const double f = sc * sc * sk;
+      cfs[lane] = cplx_d{f * tr, f * ti};
       wave_lds_fence();
-    } else {
-      run.beta0 = sh.beta0;
-      run.m_eff = sh.m_eff;
-      if (wv == 0) {
-        get_lane(sh.lz, s);
-        dcs[lane] = comb_coef(s, run, J.t);
+      double wr[NA], wi[NA];
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+        wr[n] = sk * (double)hr[n];
+        wi[n] = sk * (double)hi[n];
       }
+#pragma unroll 4
+      for (int i = i0; i <= k; ++i) {
+        const cplx_d d = cfs[i];
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          const V x = ub[(size_t)i * DS + row[n]];
+          wr[n] -= d.re * x.x - d.im * x.y;
+          wi[n] -= d.re * x.y + d.im * x.x;
+        }
+      }
+#pragma unroll
+      for (int n = 0; n < NA; ++n)
+        if (in[n]) ub[(size_t)(k + 1) * DS + row[n]] = V{(R)wr[n], (R)wi[n]};
       __syncthreads();
     }
-    const int me = run.m_eff;
+    // ---- exp(-itT) e_1 and the combination
+    LzLane s;
+    LzRun run;
+    s.al = al;
+    s.of = of;
+    s.sc = sc;
+    run.beta0 = beta0;
+    run.m_eff = me;
+    cfs[lane] = comb_coef(s, run, J.t);
+    wave_lds_fence();
     double orr[NA], oi[NA];
 #pragma unroll
     for (int n = 0; n < NA; ++n) orr[n] = oi[n] = 0.0;
 #pragma unroll 4
     for (int i = 0; i < me; ++i) {
-      const cplx_d d = dcs[i];
+      const cplx_d d = cfs[i];
 #pragma unroll
       for (int n = 0; n < NA; ++n) {
         const V x = ub[(size_t)i * DS + row[n]];
@@ -432,7 +377,7 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
   }
 }
 
-template <typename R, int NA, int TH, bool RED, bool PE>
+template <typename R, int NA, int TH, bool PE>
 hipError_t launch_sweep_t(const SweepBatch& b, int n, size_t lds, uint32_t threads, hipStream_t s) {
   // the basis exceeds the default 64 KiB of dynamic LDS: raise the limit of
   // this kernel once per device
@@ -442,13 +387,13 @@ hipError_t launch_sweep_t(const SweepBatch& b, int n, size_t lds, uint32_t threa
   if (e != hipSuccess) return e;
   const uint64_t bit = (dev < 64) ? (1ull << dev) : 0ull;
   if (!bit || !(raised.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep<R, NA, TH, RED, PE>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep<R, NA, TH, PE>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(kSweepLds - kSweepStatic));
+                            (int)kSweepLds);
     if (e != hipSuccess) return e;
     raised.fetch_or(bit, std::memory_order_acq_rel);
   }
-  hipLaunchKernelGGL((k_sweep<R, NA, TH, RED, PE>), dim3(n), dim3(threads), lds, s, b);
+  hipLaunchKernelGGL((k_sweep<R, NA, TH, PE>), dim3(n), dim3(threads), lds, s, b);
   return hipGetLastError();
 }
 
@@ -458,10 +403,10 @@ hipError_t launch_sweep_r(const SweepBatch& b, int n, hipStream_t s) {
   const int na = sweep_rows(D);
   const uint32_t threads = (D + 64u * na - 1u) / (64u * na) * 64u;
   const size_t lds = sweep_lds_bytes<R>(D, b.job[0].m);
-  if (threads <= (uint32_t)kRedThreads && na == 1)
-    return launch_sweep_t<R, 1, kRedThreads, true, PE>(b, n, lds, threads, s);
-  if (na == 1) return launch_sweep_t<R, 1, 2 * kRedThreads, false, PE>(b, n, lds, threads, s);
-  return launch_sweep_t<R, 2, 2 * kRedThreads, false, PE>(b, n, lds, threads, s);
+  if (na == 1)
+    return threads <= 256u ? launch_sweep_t<R, 1, 256, PE>(b, n, lds, threads, s)
+                           : launch_sweep_t<R, 1, kSweepThreads, PE>(b, n, lds, threads, s);
+  return launch_sweep_t<R, 2, kSweepThreads, PE>(b, n, lds, threads, s);
 }
 
 // The brackets of a run of slices, one block each: block b takes slice
@@ -527,7 +472,7 @@ int sweep_neighbours(const PeArgs* pe, int L) {
 bool sweep_fits(int prec, uint32_t D, int m, int nbr) {
   if (D < 1 || D > kSweepMaxD || nbr > kSweepNbr) return false;
   const size_t need = prec == 0 ? sweep_lds_bytes<double>(D, m) : sweep_lds_bytes<float>(D, m);
-  return need + kSweepStatic <= kSweepLds;
+  return need <= kSweepLds;
 }
 
 // The one-block form applies when its vectors fit in LDS and no tile size is
