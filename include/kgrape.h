@@ -125,8 +125,9 @@ int32_t kg_version(void);
  * for this chain, Krylov dimension and precision: two Krylov slots (scalars,
  * reduction partials, m-1 basis vectors and one vector H v_k each; the
  * second slot advances the segment recomputation beside the backward sweep)
- * and one costate vector; where one block does not hold the basis, also a
- * vector a slot up to 2^18 amplitudes and one spare state up to 2^22.
+ * and one costate vector; where one block does not hold the basis, also one
+ * (complex64: three) vectors a slot up to 2^18 amplitudes and one spare state up
+ * to 2^22.
  * Returns 0 for invalid arguments. */
 size_t kg_workspace_bytes(const kg_xxz* h, const kg_krylov* k, int32_t prec);
 
@@ -159,7 +160,7 @@ kg_status krylov_expv(const kg_xxz* h, double u, double t, const kg_krylov* k, i
 /* krylov_expv for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same operation, kernels and results, with the scratch in a static device
- * array of kg_static_scratch_bytes() (64 MiB; the array itself is 4 MiB longer)
+ * array of kg_static_scratch_bytes() (64 MiB; the array itself is 6 MiB longer)
  * that each GPU the library runs on holds until the process ends, instead of a caller's workspace.  The call
  * allocates nothing (no hipMalloc, hipFree or allocating library routine); the
  * caller still passes the vectors.  It needs one Krylov slot, 4.4 MB of

@@ -133,25 +133,25 @@ HvArgs make_hv(const kg_xxz* h, const double* u_ptr, double u_val) {
 
 size_t vbytes(uint64_t D, int32_t prec) { return (size_t)D * (prec == KG_C128 ? 16 : 8); }
 
-// A Krylov slot: scalars, reduction partials, basis vectors 1..m-1 (and one
-// more for the single-pass steps) and the vector y_k = H v_k of the running step.
-// Vectors that one block keeps in LDS, complex128 ones too, need neither that one
-// nor `tmp`.  Both are counted in 16-byte amplitudes, so that the workspaces of the
-// two precisions differ by their m basis vectors and H v a slot and the costate.
-bool in_lds(uint64_t D, const kg_krylov* k) {
-  return D <= kStepMaxD && sweep_fits(KG_C128, (uint32_t)D, k->m, 0);
+// A Krylov slot: scalars, reduction partials, basis vectors 1..m-1 (for the
+// single-pass steps one more and, in complex64, two of remainders) and the vector y_k =
+// H v_k of the running step.
+// Vectors that one block keeps in LDS need none of these extra ones.
+bool in_lds(uint64_t D, const kg_krylov* k, int32_t prec) {
+  return D <= kStepMaxD && sweep_fits(prec, (uint32_t)D, k->m, 0);
 }
 
-size_t step_bytes(uint64_t D, const kg_krylov* k) {
-  return (D <= kStepMaxD && k->m > 1 && !in_lds(D, k)) ? align_up(vbytes(D, KG_C128), 256) : 0;
+size_t step_bytes(uint64_t D, const kg_krylov* k, int32_t prec) {
+  if (D > kStepMaxD || k->m < 2 || in_lds(D, k, prec)) return 0;
+  return (prec == KG_C64 ? 3 : 1) * align_up(vbytes(D, prec), 256);
 }
 
-size_t tmp_bytes(uint64_t D, const kg_krylov* k) {
-  return (D <= kPairMaxD && !in_lds(D, k)) ? align_up(vbytes(D, KG_C128), 256) : 0;
+size_t tmp_bytes(uint64_t D, const kg_krylov* k, int32_t prec) {
+  return (D <= kPairMaxD && !in_lds(D, k, prec)) ? align_up(vbytes(D, KG_C128), 256) : 0;
 }
 
 size_t basis_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec) {
-  return align_up(vbytes(D, prec) * (size_t)(k->m - 1), 256) + step_bytes(D, k);
+  return align_up(vbytes(D, prec) * (size_t)(k->m - 1), 256) + step_bytes(D, k, prec);
 }
 
 size_t slot_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec) {
@@ -161,7 +161,7 @@ size_t slot_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec) {
 // workspace of vectors of D amplitudes; `extended` adds the two node vectors
 size_t ws_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec, bool extended) {
   const size_t vb = align_up(vbytes(D, prec), 256);
-  return 2 * slot_bytes_d(D, k, prec) + vb + tmp_bytes(D, k) + (extended ? 2 * vb : 0);
+  return 2 * slot_bytes_d(D, k, prec) + vb + tmp_bytes(D, k, prec) + (extended ? 2 * vb : 0);
 }
 
 // The workspace holds two Krylov slots (scalars, reduction partials, m-1
@@ -201,8 +201,8 @@ kg_status carve_d(void* ws, size_t ws_bytes, uint64_t D, const kg_krylov* k, int
     o->yk = q;
     o->lam = p + 2 * slot_bytes_d(D, k, prec);
     char* after = static_cast<char*>(o->lam) + vb;
-    o->tmp = tmp_bytes(D, k) ? after : nullptr;
-    after += tmp_bytes(D, k);
+    o->tmp = tmp_bytes(D, k, prec) ? after : nullptr;
+    after += tmp_bytes(D, k, prec);
     o->node_a = extended ? after : nullptr;
     o->node_b = extended ? after + vb : nullptr;
     // past the rows of the steps and the measurement columns of m's windows,
@@ -1082,7 +1082,7 @@ kg_status krylov_expv_static(const kg_xxz* h, double u, double t, const kg_krylo
     return fail(KG_EINVAL, "v_in and v_out overlap without being equal");
   if (m_eff_dev && (uintptr_t)m_eff_dev % 4) return fail(KG_EINVAL, "m_eff_dev misaligned");
   // one Krylov slot (scalars, partials, m-1 basis vectors and H v_k)
-  // the limit is that of m vectors; the array has room for one more up to kStepMaxD
+  // the limit is that of m vectors; the array has room for the steps' extra ones
   const size_t need = ws_fixed_bytes() + align_up(vbytes(geo.D, prec) * (size_t)(k->m - 1), 256) +
                       align_up(vbytes(geo.D, prec), 256);
   if (need > kStaticScratchBytes)

@@ -105,7 +105,7 @@ int tile_override_from_env();
 struct Workspace {         // carved from the caller's workspace
   KState* st;
   cplx_d* partials;        // [kMaxScal][kPartialRows]: column major, one row per block
-  void* basis;             // stored Krylov vectors 1..m-1 (and one more up to kStepMaxD)
+  void* basis;             // stored Krylov vectors 1..m-1 (and the steps' extra ones)
   void* yk;                // one vector: y_k = H v_k of the running step
   void* lam;               // one vector (costate)
   void* node_a;            // quadrature workspaces only: psi at a node
@@ -180,8 +180,10 @@ struct KrylovCall {
 };
 hipError_t launch_krylov(const KrylovCall& c, const Workspace& ws, hipStream_t s);
 // One launch per Lanczos step (kg_step.hip) for vectors of up to kStepMaxD
-// amplitudes; needs one more basis vector in the workspace.
+// amplitudes; needs more basis vectors in the workspace, of kStepExtra bytes an
+// amplitude at most: one, and in complex64 two of remainders.
 constexpr uint64_t kStepMaxD = 1ull << 18;
+constexpr uint64_t kStepExtra = 3 * 8;
 // Pairs in the table that no tiled call uses (kg_step.hip's rows and scalars
 // come first), from this offset of the partials.
 size_t step_table_pairs();

@@ -1,5 +1,5 @@
 // Scratch of the allocation-free Krylov entry point (krylov_expv_static), with
-// room for the vector that the single-pass steps use more than the limit counts: a
+// room for the vectors that the single-pass steps use more than the limit counts: a
 // file-scope device array that each GPU holds for the life of the process.  In
 // host code the array's name is only a stand-in; its device address comes from
 // hipGetSymbolAddress, taken once per device with that device current and kept
@@ -15,7 +15,7 @@ namespace kg {
 
 namespace {
 
-__device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStepMaxD * 16 + 256];
+__device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStepMaxD * kStepExtra + 3 * 256];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;

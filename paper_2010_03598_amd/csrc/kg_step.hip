@@ -15,11 +15,20 @@
 // which needs none of them.  All blocks compute the same scalars from the same
 // sums in the same order; block 0 keeps them for the next launch.
 //
-// A launch is about 5.9 us at L = 13 (two passes: 14.4): 1.6 between launches,
-// the rest a chain of two trips to memory, the scalars (0.7) and the block's
-// sums.  Calls at m = 16, complex64, two passes and this form: L=13 231 -> 101
-// us, L=15 232 -> 117, L=16 233 -> 138, L=17 240 -> 160, L=18 267 -> 209;
-// complex128 L=16 241 -> 145, L=18 323 -> 252.
+// w'_k is rounded before its largest part, c_k u_k, is subtracted, and y_k follows a
+// recurrence; both lose |alpha_k| / beta_{k+1}.  In complex64 the rounding's remainder
+// is therefore kept beside w'_k (lo: two vectors by the parity of the step) and
+// enters u_{k+1}; and past the limit kMaxGrowth all blocks agree, from the same
+// scalars, to form y_k = H u_k in that launch, each partner's u_k from w'_{k-1}, lo,
+// u_{k-1} and u_{k-2}, which nobody writes meanwhile.  L=12, m=30, S^z field of 100,
+// complex64: error 6.5e-8; without it 2.3e-4, two passes 1.8e-7.
+//
+// A launch is about 6.4 us at L = 13 (two passes: 14.4): the gap between launches, a
+// chain of two trips to memory, the scalars (0.8) and the block's sums; lo and the
+// path that forms y cost 0.5 of it (where that path is taken, a launch takes 7.3 us in
+// complex128 and 9.3 in complex64).  Calls at m = 16, complex64, two passes and this
+// form: L=13 231 -> 109 us, L=15 232 -> 124, L=16 234 -> 144, L=17 239 -> 167, L=18 265
+// -> 221; complex128 L=16 239 -> 149, L=18 322 -> 254.
 
 #include <hip/hip_runtime.h>
 
@@ -42,7 +51,7 @@ constexpr int kStepJobs = 2;
 struct StepState {
   LzStore lz[2];
   LzStore fin;
-  double run[2][5];       // normT, beta0, sk, rp, gp
+  double run[2][7];       // normT, beta0, sk, rp, gp, g, ig
   double fin_beta0;
   int32_t fin_m_eff;
   int32_t done;
@@ -54,6 +63,7 @@ struct StepArgs {
   const void* slot0;
   void* basis;            // slots 1..m
   void* y;
+  void* lo;               // complex64: w'_k less its stored value, [2][D] by k & 1
   StepState* st;
   cplx_d* rows;           // [2][kStepRows][kStepCols]
   int32_t k, m, reorth;
@@ -72,6 +82,9 @@ struct StepBatch {
   StepArgs job[kStepJobs];
 };
 
+template <typename R>
+constexpr double kUnit = sizeof(R) == 4 ? 0x1p-24 : 0x1p-53;
+
 template <typename V>
 __device__ __forceinline__ V* step_slot(const StepArgs& a, int i) {
   return i == 0 ? reinterpret_cast<V*>(const_cast<void*>(a.slot0))
@@ -84,11 +97,13 @@ __device__ __forceinline__ void get_run(const StepState& st, int b, LzRun& r) {
   r.sk = st.run[b][2];
   r.rp = st.run[b][3];
   r.gp = st.run[b][4];
+  r.g = st.run[b][5];
+  r.ig = st.run[b][6];
 }
 
 // The scalars of step k on one wavefront from its totals (LDS: window vector w
 // at 2w, 2w + 1, then <u_k|y_k> and (||u_k||^2, ||y_k||^2)).
-__device__ bool run_scalars(const StepArgs& a, int k, const cplx_d* tot, LzLane& s, LzRun& r,
+__device__ bool run_scalars(const StepArgs& a, double unit, int k, const cplx_d* tot, LzLane& s, LzRun& r,
                             StepNext& nx) {
   const int lane = threadIdx.x & 63;
   const int i0 = window_first(k, a.m, a.reorth), nw = k - i0;
@@ -99,7 +114,7 @@ __device__ bool run_scalars(const StepArgs& a, int k, const cplx_d* tot, LzLane&
     G = tot[2 * w + 1];
   }
   const cplx_d akk = tot[2 * nw], x = tot[2 * nw + 1];
-  return step_scalars(s, r, k, a.m, a.reorth, a.tol, A, G, akk, x.re, x.im, nx);
+  return step_scalars(s, r, k, a.m, a.reorth, a.tol, unit, A, G, akk, x.re, x.im, nx);
 }
 
 // The arguments in registers after one wait: read where they are used, each
@@ -107,7 +122,7 @@ __device__ bool run_scalars(const StepArgs& a, int k, const cplx_d* tot, LzLane&
 __device__ __forceinline__ void hold_args(const StepArgs& a) {
   asm volatile("" ::"s"(a.hv.L), "s"(a.hv.hc_kind), "s"(a.hv.hc_bit), "s"(a.hv.sz_count),
                "s"(a.hv.sz_mask), "s"(a.hv.half_J), "s"(a.hv.c_zz), "s"(a.hv.u_ptr), "s"(a.hv.u_val),
-               "s"(a.geo.D), "s"(a.geo.TB), "s"(a.geo.ntiles), "s"(a.slot0), "s"(a.basis), "s"(a.y),
+               "s"(a.geo.D), "s"(a.geo.TB), "s"(a.geo.ntiles), "s"(a.slot0), "s"(a.basis), "s"(a.y), "s"(a.lo),
                "s"(a.st), "s"(a.rows), "s"(a.k), "s"(a.m), "s"(a.reorth), "s"(a.tol));
 }
 
@@ -181,7 +196,7 @@ struct RowGather {
 
 // The extra wavefront: the previous step's totals, the coefficients for the
 // others, and (in block 0) the scalars for the next launch.
-template <bool FIRST>
+template <typename R, bool FIRST>
 __device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl, uint32_t G, uint32_t NW,
                                                  cplx_d* part, cplx_d* tot, cplx_d* cf, StepNext* nxs,
                                                  int* gos) {
@@ -192,7 +207,7 @@ __device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl,
     cf[lane] = cplx_d{0.0, 0.0};
     if (lane < 8u) cf[64 + lane] = cplx_d{0.0, 0.0};
     if (lane == 0) {
-      *nxs = StepNext{cplx_d{0.0, 0.0}, 1.0, 1.0};
+      *nxs = StepNext{cplx_d{0.0, 0.0}, 1.0, 1.0, cplx_d{0.0, 0.0}, 0.0};
       *gos = 1;
     }
     __syncthreads();
@@ -230,8 +245,8 @@ __device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl,
     tot[col] = cplx_d{re, im};
   }
   wave_lds_fence();
-  StepNext nx{cplx_d{0.0, 0.0}, 1.0, 1.0};
-  const bool go = done == 0 && run_scalars(a, k - 1, tot, s, r, nx);
+  StepNext nx{cplx_d{0.0, 0.0}, 1.0, 1.0, cplx_d{0.0, 0.0}, 0.0};
+  const bool go = done == 0 && run_scalars(a, kUnit<R>, k - 1, tot, s, r, nx);
   cf[lane] = s.cw;
   if (lane < 8u) cf[64 + lane] = cplx_d{0.0, 0.0};
   if (lane == 0) {
@@ -244,9 +259,9 @@ __device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl,
     if (go) {
       put_lane(ss.lz[k & 1], s);
       if (lane == 0) {
-        const double v[5] = {r.normT, r.beta0, r.sk, r.rp, r.gp};
+        const double v[7] = {r.normT, r.beta0, r.sk, r.rp, r.gp, r.g, r.ig};
 #pragma unroll
-        for (int e = 0; e < 5; ++e) ss.run[k & 1][e] = v[e];
+        for (int e = 0; e < 7; ++e) ss.run[k & 1][e] = v[e];
       }
     } else if (done == 0) {
       put_lane(ss.fin, s);
@@ -262,6 +277,57 @@ __device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl,
 
 __device__ __forceinline__ void hold_pe_args(const PeArgs& p) {
   asm volatile("" ::"s"(p.reps), "s"(p.scnt), "s"(p.nbr), "s"(p.nbr_slots), "s"(p.L), "s"(p.dim));
+}
+
+// u_k at one amplitude from w'_{k-1} (x, and lo in complex64) and u_{k-1} (p), rounded
+// as stored.
+template <typename V>
+__device__ __forceinline__ V next_u(const StepNext& nx, V x, V lo, V p) {
+  using R = decltype(x.x);
+  const double ar = nx.sig * ((double)x.x + (double)lo.x), ai = nx.sig * ((double)x.y + (double)lo.y);
+  return V{(R)(ar - (nx.c.re * (double)p.x - nx.c.im * (double)p.y)),
+           (R)(ai - (nx.c.re * (double)p.y + nx.c.im * (double)p.x))};
+}
+
+// The same with the remainder d on u_{k-2} (p2).  Written with fma, so that every place
+// forms the same value.
+template <typename V>
+__device__ __forceinline__ V next_u(const StepNext& nx, V x, V lo, V p, V p2) {
+  using R = decltype(x.x);
+  double ar = nx.sig * ((double)x.x + (double)lo.x), ai = nx.sig * ((double)x.y + (double)lo.y);
+  ar = fma(nx.c.im, (double)p.y, fma(-nx.c.re, (double)p.x, ar));
+  ai = fma(-nx.c.im, (double)p.x, fma(-nx.c.re, (double)p.y, ai));
+  ar = fma(nx.d.im, (double)p2.y, fma(-nx.d.re, (double)p2.x, ar));
+  ai = fma(-nx.d.im, (double)p2.x, fma(-nx.d.re, (double)p2.y, ai));
+  return V{(R)ar, (R)ai};
+}
+
+// Row s of (H0 + u Hc) x on the full space, x given by amplitude; four bonds in flight.
+// Returns x at s.
+template <typename R, typename XAt>
+__device__ __forceinline__ typename VT<R>::T row_at(const HvArgs& a, double u, uint32_t s, XAt xat, R& yr, R& yi) {
+  using V = typename VT<R>::T;
+  const int L = a.L;
+  const uint32_t act = (s ^ (s >> 1)) & ((1u << (L - 1)) - 1u);
+  const R hJ = (R)a.half_J;
+  R d = (R)a.c_zz * (R)(L - 1 - 2 * (int)__popc(act));
+  if (a.hc_kind == 1) d += (R)u * ((R)(0.5 * a.sz_count) - (R)__popc(s & a.sz_mask));
+  const V x = xat(s), f = xat(a.hc_kind == 0 ? s ^ (1u << a.hc_bit) : s);
+  const R cu = a.hc_kind == 0 ? (R)(0.5 * u) : (R)0;
+  yr = d * x.x + cu * f.x;
+  yi = d * x.y + cu * f.y;
+  for (int p0 = 0; p0 < L - 1; p0 += 4) {
+    V q[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[e] = xat(((act >> (p0 + e)) & 1u) ? s ^ (3u << (p0 + e)) : s);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const R c = ((act >> (p0 + e)) & 1u) ? hJ : (R)0;
+      yr += c * q[e].x;
+      yi += c * q[e].y;
+    }
+  }
+  return x;
 }
 
 // RAG: the last tile reaches past the vector.  FIRST: step 0.  PE: the reduced
@@ -293,17 +359,20 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
   double* meas = reinterpret_cast<double*>(stage + NW * 256u);
   cplx_d* part = reinterpret_cast<cplx_d*>(meas + NW * nv);
   if (wv == NW) {
-    step_scalar_wave<FIRST>(a, bl, G, NW, part, tot, cf, &nxs, &gos);
+    step_scalar_wave<R, FIRST>(a, bl, G, NW, part, tot, cf, &nxs, &gos);
     return;
   }
   const int ip = window_first(FIRST ? 0 : k - 1, m, a.reorth);
   const V* src = FIRST ? step_slot<const V>(a, 0) : step_slot<const V>(a, k + 1);
   V* yb = reinterpret_cast<V*>(a.y);
+  constexpr bool kLo = sizeof(R) == 4;   // w'_0 = y_0 has no remainder
+  const V* lo_in = reinterpret_cast<const V*>(a.lo) + (size_t)((k - 1) & 1) * D;
+  V* lo_out = reinterpret_cast<V*>(a.lo) + (size_t)(k & 1) * D;
   const uint32_t tile = tile_of(g, 0, bl, G);
   const uint32_t base = tile << g.TB;
   const uint32_t sw = base | (wv << (6 + RB));                  // this wavefront's amplitudes
   Tile<R, RB> T;
-  V up[NR], yp[NR];
+  V up[NR], yp[NR], lo[NR];
   V w0q[2][4];   // the first window vectors of the first unit, in flight beside the scalars
   const auto load = [&](uint32_t s0, int w, V (&q)[4]) {
     const V* p = step_slot<const V>(a, min(i0 + w, k - 1));
@@ -348,6 +417,12 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
                  2u * (uint32_t)(k - 1 - ip) + 2u, wv, NW + 1u);
     load_slots<V, NR>(step_slot<const V>(a, k - 1), sw | lane, !RAG, D, up);
     load_slots<V, NR>(yb, sw | lane, !RAG, D, yp);
+    if (kLo && k >= 2) {
+      load_slots<V, NR>(lo_in, sw | lane, !RAG, D, lo);
+    } else {
+#pragma unroll
+      for (int r = 0; r < NR; ++r) lo[r] = V{(R)0, (R)0};
+    }
     apply_h([&] {
       window_first_loads();
       rg.sum(part + wv * kStepCols);
@@ -361,6 +436,31 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
   R* st = stage + wv * 256u;
   double* row = meas + wv * nv;
   double kr = 0.0, ki = 0.0, kk = 0.0, yy = 0.0;
+  const bool fresh = !FIRST && uniform_u32((uint32_t)(nx.fresh != 0.0));
+  if (!FIRST && fresh) {
+    const V* pu = step_slot<const V>(a, k - 1);
+    const V* pu2 = step_slot<const V>(a, max(k - 2, 0));   // k = 1: d is 0
+    const auto u_at = [&](uint32_t i) {
+      return next_u<V>(nx, src[i], (kLo && k >= 2) ? lo_in[i] : V{(R)0, (R)0}, pu[i], pu2[i]);
+    };
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      if constexpr (PE) {
+        const uint32_t sl = min((sw >> 6) + r, ((D + 63u) >> 6) - 1u), b = min((sl << 6) | lane, D - 1u);
+        bool bad;
+        pe_row_nbr<R>(a.hv, a.pe, u, sl, b, lane, u_at, T.yr[r], T.yi[r], bad);
+        if (bad) T.yr[r] = T.yi[r] = (R)NAN;
+        const V x = u_at(b);
+        T.xr[r] = x.x;
+        T.xi[r] = x.y;
+      } else {
+        const uint32_t s = sw | ((uint32_t)r << 6) | lane;
+        const V x = row_at<R>(a.hv, u, RAG ? min(s, D - 1u) : s, u_at, T.yr[r], T.yi[r]);
+        T.xr[r] = x.x;
+        T.xi[r] = x.y;
+      }
+    }
+  }
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const uint32_t s0 = sw | ((uint32_t)r << 6), sl = s0 | lane;
@@ -371,10 +471,13 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
       uo = V{T.xr[r], T.xi[r]};
       yo = V{T.yr[r], T.yi[r]};
     } else {
-      uo.x = (R)(nx.sig * (double)T.xr[r] - (nx.c.re * (double)up[r].x - nx.c.im * (double)up[r].y));
-      uo.y = (R)(nx.sig * (double)T.xi[r] - (nx.c.re * (double)up[r].y + nx.c.im * (double)up[r].x));
+      uo = next_u<V>(nx, V{T.xr[r], T.xi[r]}, lo[r], up[r]);
       yo.x = (R)(nx.sig * (double)T.yr[r] - (nx.c.re * (double)yp[r].x - nx.c.im * (double)yp[r].y));
       yo.y = (R)(nx.sig * (double)T.yi[r] - (nx.c.re * (double)yp[r].y + nx.c.im * (double)yp[r].x));
+      if (fresh) {   // both formed above
+        uo = V{T.xr[r], T.xi[r]};
+        yo = V{T.yr[r], T.yi[r]};
+      }
       if (in) uk[sl] = uo;
     }
     if (RAG && !in) uo = yo = V{(R)0, (R)0};
@@ -448,7 +551,11 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
       const uint32_t s = s0 | unit_amp((int)c, aa);
       const R* o = st + unit_amp((int)c, aa) * 4u;
       const double wr = nx.s * (double)o[0] - quad_z(zr), wi = nx.s * (double)o[1] - quad_z(zi);
-      if (!RAG || s < D) wk[s] = V{(R)wr, (R)wi};
+      const V w{(R)wr, (R)wi};
+      if (!RAG || s < D) {
+        wk[s] = w;
+        if (kLo) lo_out[s] = V{(R)(wr - (double)w.x), (R)(wi - (double)w.y)};
+      }
     }
     wave_lds_fence();
   }
@@ -521,7 +628,7 @@ __global__ void __launch_bounds__(kCombBlock) k_step_combine(StepBatch B, uint32
       }
       wave_lds_fence();
       StepNext nx;
-      (void)run_scalars(a, k, tot, s, r, nx);
+      (void)run_scalars(a, kUnit<R>, k, tot, s, r, nx);
     } else {
       get_lane(ss.fin, s);
       r.beta0 = ss.fin_beta0;
@@ -599,6 +706,7 @@ hipError_t launch_krylov_steps_r(const KrylovCall* calls, const Workspace* const
     a.slot0 = c.v_in;
     a.basis = wss[j]->basis;
     a.y = wss[j]->yk;
+    a.lo = static_cast<char*>(wss[j]->basis) + (size_t)c.m * c.step.D * sizeof(typename VT<R>::T);
     a.rows = wss[j]->partials;
     a.st = reinterpret_cast<StepState*>(wss[j]->partials + 2 * (size_t)kStepRows * kStepCols);
     a.m = c.m;
@@ -626,7 +734,7 @@ hipError_t launch_krylov_steps_r(const KrylovCall* calls, const Workspace* const
     }
     if (e != hipSuccess) return e;
     // as a pass A (v_k read, y written but in the last step) and, before the
-    // last step, a pass B (y and the window read, v_{k+1} written)
+    // last step, a pass B (y and the window read, v_{k+1} written); lo is not counted
     const int i0 = k == m - 1 ? k : (calls[0].reorth ? 0 : (k > 0 ? k - 1 : 0));
     if (prof && calls[0].pe)
       profiler_stop(prof, s, kProfHv, n * pe_gather_bytes(*calls[0].pe, vb / n), kProfPassB,

@@ -13,7 +13,7 @@ import torch
 
 import paper_2010_03598_amd as kg
 from gpu_util import dev_vec, host, rel_err
-from oracle import grape, krylov, model
+from oracle import grape, krylov, model, pe
 import workloads
 
 pytestmark = pytest.mark.gpu
@@ -44,6 +44,46 @@ def test_one_block(L, J, delta, kind, sites, u, t, m, reorth):
     ref = krylov.expv(lambda x: model.apply_h(L, J, delta, kind, sites, u, x), v, t, m, reorth)
     out = kg.krylov_expv(kg.XXZ(L, J, delta, kind, sites), u, t, dev_vec(v, C64), kg.Krylov(m, reorth))
     assert rel_err(host(out), ref) <= bound(m, C64)
+
+
+# one launch per step: short windows and long ones, a vector beyond the one-block form's LDS
+LONG = [(12, 1.0, 0.5, SZ, 1, 100.0, 1.0, 30, True), (11, 1.0, 0.5, SZ, 1, -60.0, 1.0, 30, True),
+        (12, 0.2, 20.0, SX, 1, 1.0, 1.0, 24, True), (12, 1.0, 10.0, SX, 1, 1.0, 1.0, 40, False),
+        (9, 1.0, 0.5, SZ, 1, 70.0, 0.5, 30, True), (14, 1.0, 4.0, SX, 1 << 5, 3.0, 0.5, 18, True),
+        (17, 1.0, 0.5, SZ, 0b10001, 50.0, 0.3, 14, True)]
+
+
+@pytest.mark.parametrize("L,J,delta,kind,sites,u,t,m,reorth", LONG)
+def test_one_launch_per_step(L, J, delta, kind, sites, u, t, m, reorth):
+    v = domain_wall(L)
+    ref = krylov.expv(lambda x: model.apply_h(L, J, delta, kind, sites, u, x), v, t, m, reorth)
+    out = kg.krylov_expv(kg.XXZ(L, J, delta, kind, sites), u, t, dev_vec(v, C64), kg.Krylov(m, reorth))
+    assert rel_err(host(out), ref) <= bound(m, C64)
+
+
+@pytest.mark.parametrize("L,delta,kind,u,t,m", [(11, 2.0, SZ, 12.0, 0.4, 24), (12, 6.0, SX, 2.0, 0.3, 20),
+                                                (16, 1.0, SZ, 8.0, 0.2, 16)])
+def test_one_launch_per_step_c128(L, delta, kind, u, t, m):
+    v = domain_wall(L)
+    ref = krylov.expv(lambda x: model.apply_h(L, 1.0, delta, kind, 1, u, x), v, t, m, True)
+    out = kg.krylov_expv(kg.XXZ(L, 1.0, delta, kind, 1), u, t, dev_vec(v, C128), kg.Krylov(m))
+    assert rel_err(host(out), ref) <= 8.0 * bound(m, C128)     # both sides round in FP64
+
+
+@pytest.mark.parametrize("dtype", [C64, C128])
+@pytest.mark.parametrize("L,K,u,t,m", [(14, 7, 30.0, 0.2, 20), (16, 8, 15.0, 0.3, 16)])
+def test_reduced_basis_steps(L, K, u, t, m, dtype):
+    """The states of a forward sweep in the reduced basis, from the task's product state."""
+    B, sites, N = kg.ReducedBasis(L, K), 1 | (1 << (L - 1)), 3
+    P = pe.PEChain(L, K, 1.0, 3.0, sites)
+    psi0, f = np.zeros(B.dim, complex), workloads.random_state(np.random.default_rng(1), B.dim)
+    psi0[B.dim // 3] = 1.0
+    us = u * np.array([1.0, -1.0, 0.5])
+    ref, _ = grape.forward(P, us, psi0, t, m, keep=False)
+    r = kg.grape_gradient_pe(kg.XXZ(L, 1.0, 3.0, kg.KG_HC_SZ, sites), B, torch.tensor(us, device="cuda"), t,
+                             kg.Krylov(m), dev_vec(psi0, dtype), dev_vec(f, dtype))
+    got = host(r.states).reshape(N, -1)[-1]
+    assert rel_err(got, ref) <= N * (1.0 if dtype == C64 else 8.0) * bound(m, dtype)
 
 
 @pytest.mark.parametrize("L,u,delta,pos,sites", [
