@@ -9,6 +9,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "kg_internal.h"
 
 namespace kg {
@@ -24,6 +26,22 @@ inline void kg_launch(F kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s
   } else {
     hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
   }
+}
+
+// A launch with more than the default 64 KiB of dynamic LDS: raises the kernel's limit
+// to `most`, once per device.  One `raised` per kernel.
+template <typename F>
+inline hipError_t allow_lds(F kernel, size_t lds, size_t most, std::atomic<uint64_t>& raised) {
+  if (lds <= ((size_t)64 << 10)) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = (dev < 64) ? (1ull << dev) : 0ull;
+  if (bit && (raised.load(std::memory_order_acquire) & bit)) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)most);
+  if (e == hipSuccess) raised.fetch_or(bit, std::memory_order_acq_rel);
+  return e;
 }
 
 namespace {

@@ -664,23 +664,31 @@ __global__ void __launch_bounds__(kCombBlock) k_step_combine(StepBatch B, uint32
   }
 }
 
+// Up to 116 KB of dynamic LDS (a forced 2^12 tile of complex128); by itself a launch
+// passes 64 KiB at 2^10 tiles, complex128, from m = 56 on.
+constexpr size_t kStepLds = 150u << 10;
+
+template <typename R, int RB, bool RAG, int TH, bool PE>
+hipError_t launch_step_t(const StepBatch& b, int n, size_t lds, hipStream_t s) {
+  const Geo& g = b.job[0].geo;
+  const dim3 grid(g.grid * n), block(64u * ((1u << g.WB) + 1u));
+  static std::atomic<uint64_t> raised[2];
+  const int later = b.job[0].k == 0 ? 0 : 1;
+  const auto kernel = later ? k_step<R, RB, RAG, TH, false, PE> : k_step<R, RB, RAG, TH, true, PE>;
+  const hipError_t e = allow_lds(kernel, lds, kStepLds, raised[later]);
+  if (e != hipSuccess) return e;
+  kg_launch(kernel, grid, block, lds, s, b);
+  return hipGetLastError();
+}
+
 template <typename R, int RB>
 hipError_t launch_step_rb(const StepBatch& b, int n, size_t lds, hipStream_t s) {
   const Geo& g = b.job[0].geo;
-  const dim3 grid(g.grid * n), block(64u * ((1u << g.WB) + 1u));
-  const bool first = b.job[0].k == 0;
-  const auto go = [&](auto zero, auto later) { kg_launch(first ? zero : later, grid, block, lds, s, b); };
-  if (b.job[0].pe.nbr && g.WB <= 2)
-    go(k_step<R, RB, true, 320, true, true>, k_step<R, RB, true, 320, false, true>);
-  else if (b.job[0].pe.nbr)
-    go(k_step<R, RB, true, 576, true, true>, k_step<R, RB, true, 576, false, true>);
-  else if (g.small)
-    go(k_step<R, RB, true, 576, true>, k_step<R, RB, true, 576, false>);
-  else if (g.WB <= 2)
-    go(k_step<R, RB, false, 320, true>, k_step<R, RB, false, 320, false>);
-  else
-    go(k_step<R, RB, false, 576, true>, k_step<R, RB, false, 576, false>);
-  return hipGetLastError();
+  if (b.job[0].pe.nbr)
+    return g.WB <= 2 ? launch_step_t<R, RB, true, 320, true>(b, n, lds, s)
+                     : launch_step_t<R, RB, true, 576, true>(b, n, lds, s);
+  return g.WB <= 2 ? launch_step_t<R, RB, false, 320, false>(b, n, lds, s)
+                   : launch_step_t<R, RB, false, 576, false>(b, n, lds, s);
 }
 
 template <typename R>

@@ -34,8 +34,6 @@
 #include <stdlib.h>
 #include <string.h>
 
-#include <atomic>
-
 #include "kg_device.h"
 #include "kg_internal.h"
 #include "kg_step.h"
@@ -379,20 +377,9 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
 
 template <typename R, int NA, int TH, bool PE>
 hipError_t launch_sweep_t(const SweepBatch& b, int n, size_t lds, uint32_t threads, hipStream_t s) {
-  // the basis exceeds the default 64 KiB of dynamic LDS: raise the limit of
-  // this kernel once per device
   static std::atomic<uint64_t> raised{0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  const hipError_t e = allow_lds(&k_sweep<R, NA, TH, PE>, lds, kSweepLds, raised);
   if (e != hipSuccess) return e;
-  const uint64_t bit = (dev < 64) ? (1ull << dev) : 0ull;
-  if (!bit || !(raised.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep<R, NA, TH, PE>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kSweepLds);
-    if (e != hipSuccess) return e;
-    raised.fetch_or(bit, std::memory_order_acq_rel);
-  }
   hipLaunchKernelGGL((k_sweep<R, NA, TH, PE>), dim3(n), dim3(threads), lds, s, b);
   return hipGetLastError();
 }
