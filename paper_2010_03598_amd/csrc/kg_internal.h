@@ -191,7 +191,7 @@ size_t step_table_pairs();
 // and the largest that do it in the same launches (beyond, on two streams).
 constexpr uint64_t kPairMaxD = 1ull << 22;
 constexpr uint64_t kPairLaunchMaxD = 1ull << 15;
-Geo make_geo_step(int L, int tile_bits_override);
+Geo make_geo_step(int L);
 Geo make_geo_step_pe(int L, uint64_t dim);
 hipError_t launch_krylov_steps(const KrylovCall* calls, const Workspace* const* wss, int n,
                                hipStream_t s);
@@ -224,6 +224,9 @@ struct SweepJob {
 };
 int sweep_neighbours(const PeArgs* pe, int L);
 bool sweep_fits(int prec, uint32_t D, int m, int nbr);
+// KG_TILE_BITS or KG_NO_FUSED in the environment: Krylov calls of every size take the
+// tiled passes.
+bool passes_forced();
 // Whether a Krylov call takes the one-block form, and the sweep that is that call.
 struct KrylovCall;
 bool sweep_applies(const KrylovCall& c);

@@ -21,7 +21,7 @@
 // Lanczos (App. A, Algorithm 2 with the full re-orthonormalisation it
 // describes).  Vectors of more than 2^18 amplitudes (shorter ones take a launch
 // per step or a block per call, kg_step.hip and kg_sweep.hip; these passes serve
-// them too when a tile size is forced).  With full re-orthonormalisation two
+// them too when KG_TILE_BITS forces a tile size or KG_NO_FUSED is set).  With full re-orthonormalisation two
 // steps share one pass over the basis (pass C and pass P, described there); the
 // plain two-vector window takes two passes a step:
 //   pass A(k): x = stored v_k; y = H x, stored (the H v vector); each block
@@ -1812,15 +1812,15 @@ hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss,
     for (int j = 0; j < n; ++j) jobs[j] = sweep_job(calls[j]);
     return launch_sweeps(c0.prec, jobs, n, s);
   }
-  // one launch per step; a call that KG_TILE_BITS or KG_NO_FUSED keeps from the
-  // one-block form takes the passes (its workspace has no room for the steps)
-  const bool steps = c0.geo.D <= kStepMaxD && (!c0.pe || c0.pe->nbr);
+  // one launch per step; vectors that fit the one-block form but do not take it (the
+  // passes are forced, or more neighbours than it holds) have no room for the steps
+  const bool steps = c0.geo.D <= kStepMaxD && (!c0.pe || c0.pe->nbr) && !passes_forced();
   if (steps && !sweep_fits(c0.prec, c0.geo.D, c0.m, 0)) {
     KrylovCall c[kMaxJobs];
     for (int j = 0; j < n; ++j) {
       c[j] = calls[j];
       c[j].step = c0.pe ? make_geo_step_pe(c0.hv.L, c0.geo.D)
-                        : make_geo_step(c0.hv.L, tile_override_from_env());
+                        : make_geo_step(c0.hv.L);
     }
     return launch_krylov_steps(c, wss, n, s);
   }

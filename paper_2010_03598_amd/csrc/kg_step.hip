@@ -664,9 +664,8 @@ __global__ void __launch_bounds__(kCombBlock) k_step_combine(StepBatch B, uint32
   }
 }
 
-// Up to 116 KB of dynamic LDS (a forced 2^12 tile of complex128); by itself a launch
-// passes 64 KiB at 2^10 tiles, complex128, from m = 56 on.
-constexpr size_t kStepLds = 150u << 10;
+// The most dynamic LDS of a launch: 68 KB at 2^10 tiles, complex128, m = 64.
+constexpr size_t kStepLds = 80u << 10;
 
 template <typename R, int RB, bool RAG, int TH, bool PE>
 hipError_t launch_step_t(const StepBatch& b, int n, size_t lds, hipStream_t s) {
@@ -734,12 +733,7 @@ hipError_t launch_krylov_steps_r(const KrylovCall* calls, const Workspace* const
     for (int j = 0; j < n; ++j) b.job[j].k = k;
     if (prof) profiler_start(prof, s);
     const size_t lds = step_lds<R>(g, k, calls[0].m, calls[0].reorth);
-    switch (g.RB) {
-      case 0: e = launch_step_rb<R, 0>(b, n, lds, s); break;
-      case 1: e = launch_step_rb<R, 1>(b, n, lds, s); break;
-      case 2: e = launch_step_rb<R, 2>(b, n, lds, s); break;
-      default: e = launch_step_rb<R, 3>(b, n, lds, s); break;
-    }
+    e = g.RB == 0 ? launch_step_rb<R, 0>(b, n, lds, s) : launch_step_rb<R, 1>(b, n, lds, s);
     if (e != hipSuccess) return e;
     // as a pass A (v_k read, y written but in the last step) and, before the
     // last step, a pass B (y and the window read, v_{k+1} written); lo is not counted

@@ -462,13 +462,15 @@ bool sweep_fits(int prec, uint32_t D, int m, int nbr) {
   return need <= kSweepLds;
 }
 
-// The one-block form applies when its vectors fit in LDS and no tile size is
-// forced (KG_TILE_BITS) and KG_NO_FUSED is unset.
-bool sweep_applies(const KrylovCall& c) {
-  if (!sweep_fits(c.prec, c.geo.D, c.m, sweep_neighbours(c.pe, c.hv.L))) return false;
+bool passes_forced() {
   const char* tb = getenv("KG_TILE_BITS");
   const char* nf = getenv("KG_NO_FUSED");
-  return !(tb && *tb) && !(nf && *nf && strcmp(nf, "0") != 0);
+  return (tb && *tb) || (nf && *nf && strcmp(nf, "0") != 0);
+}
+
+// The one-block form applies when its vectors fit in LDS.
+bool sweep_applies(const KrylovCall& c) {
+  return sweep_fits(c.prec, c.geo.D, c.m, sweep_neighbours(c.pe, c.hv.L)) && !passes_forced();
 }
 
 SweepJob sweep_job(const KrylovCall& c) {
