@@ -125,9 +125,8 @@ int32_t kg_version(void);
  * for this chain, Krylov dimension and precision: two Krylov slots (scalars,
  * reduction partials, m-1 basis vectors and one vector H v_k each; the
  * second slot advances the segment recomputation beside the backward sweep)
- * and one costate vector; where one block does not hold the basis, also one
- * (complex64: three) vectors a slot up to 2^18 amplitudes and one spare state up
- * to 2^22.
+ * and one costate vector; up to 2^18 amplitudes that one block does not hold, also
+ * one vector a slot in complex128 and three in complex64.
  * Returns 0 for invalid arguments. */
 size_t kg_workspace_bytes(const kg_xxz* h, const kg_krylov* k, int32_t prec);
 

@@ -146,10 +146,6 @@ size_t step_bytes(uint64_t D, const kg_krylov* k, int32_t prec) {
   return (prec == KG_C64 ? 3 : 1) * align_up(vbytes(D, prec), 256);
 }
 
-size_t tmp_bytes(uint64_t D, const kg_krylov* k, int32_t prec) {
-  return (D <= kPairMaxD && !in_lds(D, k, prec)) ? align_up(vbytes(D, KG_C128), 256) : 0;
-}
-
 size_t basis_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec) {
   return align_up(vbytes(D, prec) * (size_t)(k->m - 1), 256) + step_bytes(D, k, prec);
 }
@@ -161,7 +157,7 @@ size_t slot_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec) {
 // workspace of vectors of D amplitudes; `extended` adds the two node vectors
 size_t ws_bytes_d(uint64_t D, const kg_krylov* k, int32_t prec, bool extended) {
   const size_t vb = align_up(vbytes(D, prec), 256);
-  return 2 * slot_bytes_d(D, k, prec) + vb + tmp_bytes(D, k, prec) + (extended ? 2 * vb : 0);
+  return 2 * slot_bytes_d(D, k, prec) + vb + (extended ? 2 * vb : 0);
 }
 
 // The workspace holds two Krylov slots (scalars, reduction partials, m-1
@@ -201,8 +197,6 @@ kg_status carve_d(void* ws, size_t ws_bytes, uint64_t D, const kg_krylov* k, int
     o->yk = q;
     o->lam = p + 2 * slot_bytes_d(D, k, prec);
     char* after = static_cast<char*>(o->lam) + vb;
-    o->tmp = tmp_bytes(D, k, prec) ? after : nullptr;
-    after += tmp_bytes(D, k, prec);
     o->node_a = extended ? after : nullptr;
     o->node_b = extended ? after + vb : nullptr;
     // past the rows of the steps and the measurement columns of m's windows,
@@ -444,9 +438,9 @@ const SideStream* side_stream(hipStream_t caller) {
 // of the forward sweep (lambda_N is the target; beta only scales the brackets
 // at the end), so they run on the second stream while psi moves forward.  In
 // the first half each sweep fills its own end of the state buffer; in the
-// second each meets what the other stored: psi_j is formed beside lambda_j in
-// its slot, the bracket is taken and psi_j replaces lambda_j, and lambda_j
-// meets psi_j.  One sweep's launches leave the chip mostly waiting for small
+// second each meets what the other stored: psi_j is formed beside lambda_j (in the
+// Krylov slot's vector H v, which no combination reads), the bracket is taken and psi_j
+// replaces lambda_j, and lambda_j meets psi_j.  One sweep's launches leave the chip mostly waiting for small
 // vectors, and its launch tails uncovered for large ones.  Timed store-all
 // gradients (60 slices, m = 16), one sweep after the other against side by
 // side: L=11 complex64 11.4 -> 6.1 ms and L=15 14.2 -> 7.7 in the same
@@ -501,13 +495,13 @@ kg_status paired_sweeps(const SweepArgs& a, const States& S, const SideStream* s
     const int jf = h + i, jb = h + 1 - i;
     RawBracket rf{}, rb{};
     const bool met = i > 1, back = jb > 0 || (jb == 0 && centred);
-    if (met) rf = RawBracket{lam_at(jf - 1), a.ws.tmp, S.at(jf - 1), a.ws.st, a.ws.partials, raw + (jf - 2)};
+    if (met) rf = RawBracket{lam_at(jf - 1), a.ws.yk, S.at(jf - 1), a.ws.st, a.ws.partials, raw + (jf - 2)};
     if (back)
       rb = RawBracket{a.ws.lam, S.at0(jb), nullptr, a.ws1.st, a.ws1.partials, jb > 0 ? raw + (jb - 1) : raw + N};
     KG_HIP(brackets(met ? &rf : nullptr, back ? &rb : nullptr), "paired brackets");
     KrylovCall f, b;
     const bool more_f = jf <= N, more_b = jb > 1 || (jb == 1 && centred);
-    if (more_f) f = krylov_call(a, jf, a.dt, S.at0(jf - 1), a.ws.tmp);
+    if (more_f) f = krylov_call(a, jf, a.dt, S.at0(jf - 1), a.ws.yk);
     if (more_b) b = krylov_call(a, jb, -a.dt, a.ws.lam, a.ws.lam);
     KG_HIP(calls(more_f ? &f : nullptr, more_b ? &b : nullptr), "paired sweeps");
   }
@@ -521,7 +515,7 @@ kg_status paired_sweeps(const SweepArgs& a, const States& S, const SideStream* s
 // the other.
 bool take_pairs(const SweepArgs& a, const States& S, int chains, const SideStream** side) {
   *side = nullptr;
-  if (S.c != 0 || a.N < 2 || !a.ws.tmp || profiling() || getenv("KG_ONE_STREAM")) return false;
+  if (S.c != 0 || a.N < 2 || a.geo.D > kPairMaxD || profiling() || getenv("KG_ONE_STREAM")) return false;
   if ((int64_t)chains * (a.N + 1) > a.ws.raw_len) return false;
   if (a.geo.D <= kPairLaunchMaxD) return true;
   *side = side_stream(a.stream);

@@ -110,7 +110,6 @@ struct Workspace {         // carved from the caller's workspace
   void* lam;               // one vector (costate)
   void* node_a;            // quadrature workspaces only: psi at a node
   void* node_b;            //   and lambda at the node
-  void* tmp;               // one vector up to kPairMaxD amplitudes (psi beside its costate)
   cplx_d* raw;             // slot 0: brackets before beta is known
   int64_t raw_len;
   char* area;              // slot 0: everything after the scalars, free while no
