@@ -284,7 +284,12 @@ __device__ __forceinline__ void hold_pe_args(const PeArgs& p) {
 template <typename V>
 __device__ __forceinline__ V next_u(const StepNext& nx, V x, V lo, V p) {
   using R = decltype(x.x);
-  const double ar = nx.sig * ((double)x.x + (double)lo.x), ai = nx.sig * ((double)x.y + (double)lo.y);
+  double xr = x.x, xi = x.y;
+  if constexpr (sizeof(R) == 4) {
+    xr += (double)lo.x;
+    xi += (double)lo.y;
+  }
+  const double ar = nx.sig * xr, ai = nx.sig * xi;
   return V{(R)(ar - (nx.c.re * (double)p.x - nx.c.im * (double)p.y)),
            (R)(ai - (nx.c.re * (double)p.y + nx.c.im * (double)p.x))};
 }
@@ -346,7 +351,10 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
   __shared__ int gos;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wv = uniform_u32(threadIdx.x >> 6);
-  const Geo& g = a.geo;
+  Geo g = a.geo;
+  // a full-space tile is never longer than the vector; known here, hv_tile's loads
+  // have no masked alternative to wait for
+  if constexpr (!RAG) g.small = 0;
   const uint32_t NW = 1u << g.WB;
   const uint32_t c = lane & 3u, aa = lane >> 2;
   const uint32_t D = g.D;
@@ -417,27 +425,23 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
                  2u * (uint32_t)(k - 1 - ip) + 2u, wv, NW + 1u);
     load_slots<V, NR>(step_slot<const V>(a, k - 1), sw | lane, !RAG, D, up);
     load_slots<V, NR>(yb, sw | lane, !RAG, D, yp);
-    if (kLo && k >= 2) {
-      load_slots<V, NR>(lo_in, sw | lane, !RAG, D, lo);
-    } else {
-#pragma unroll
-      for (int r = 0; r < NR; ++r) lo[r] = V{(R)0, (R)0};
-    }
+    if constexpr (kLo) load_slots<V, NR>(lo_in, sw | lane, !RAG, D, lo);   // not used at k = 1
     apply_h([&] {
       window_first_loads();
       rg.sum(part + wv * kStepCols);
     });
   }
   __syncthreads();
-  if (!gos) return;
-  const StepNext nx = nxs;
+  const int go = gos;
+  const StepNext nx = nxs;   // both in one trip to LDS
+  if (!go) return;
   V* uk = FIRST ? nullptr : step_slot<V>(a, k);
   V* wk = last ? nullptr : step_slot<V>(a, k + 2);
   R* st = stage + wv * 256u;
   double* row = meas + wv * nv;
   double kr = 0.0, ki = 0.0, kk = 0.0, yy = 0.0;
   const bool fresh = !FIRST && uniform_u32((uint32_t)(nx.fresh != 0.0));
-  if (!FIRST && fresh) {
+  if (__builtin_expect(!FIRST && fresh, 0)) {   // out of the ordinary path's way
     const V* pu = step_slot<const V>(a, k - 1);
     const V* pu2 = step_slot<const V>(a, max(k - 2, 0));   // k = 1: d is 0
     const auto u_at = [&](uint32_t i) {
@@ -471,7 +475,7 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
       uo = V{T.xr[r], T.xi[r]};
       yo = V{T.yr[r], T.yi[r]};
     } else {
-      uo = next_u<V>(nx, V{T.xr[r], T.xi[r]}, lo[r], up[r]);
+      uo = next_u<V>(nx, V{T.xr[r], T.xi[r]}, (kLo && k >= 2) ? lo[r] : V{(R)0, (R)0}, up[r]);
       yo.x = (R)(nx.sig * (double)T.yr[r] - (nx.c.re * (double)yp[r].x - nx.c.im * (double)yp[r].y));
       yo.y = (R)(nx.sig * (double)T.yi[r] - (nx.c.re * (double)yp[r].y + nx.c.im * (double)yp[r].x));
       if (fresh) {   // both formed above
