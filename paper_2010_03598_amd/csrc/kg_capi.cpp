@@ -817,10 +817,10 @@ Geo make_geo(int L, int prec, int tile_bits_override, int grid_cap, bool standal
 // Every block sums the rows of all, so the grid stays at 256 where the tile
 // allows; a tile takes up to eight wavefronts and two amplitudes per thread.
 // Timed calls (m = 16, us) at tiles of 2^7, 2^8, 2^9, 2^10 amplitudes, complex64,
-// before the checks of kMaxGrowth (which add 7 to 13): L=11 98, 104, 119, 155; L=14 115,
+// before the checks of kMaxGrowth (which add 1 to 11): L=11 98, 104, 119, 155; L=14 115,
 // 107, 135, 191; L=16 203, 138, 137, 169; L=17 -, 201, 160, 188; L=18 -, -, 290, 209.
 // complex128 the same order.  The passes that share a stream between two steps take 199
-// at L=16 (144 here), 204 at L=17 (167), 228 at L=18 (221; complex128 297, 254); at L=19
+// at L=16 (138 here), 204 at L=17 (164), 228 at L=18 (219; complex128 297, 256); at L=19
 // they are ahead (273 against 316 complex64, 377 against 496 complex128): the line is at
 // 2^18.
 Geo make_geo_step(int L) {
@@ -841,8 +841,8 @@ Geo make_geo_step(int L) {
 // The same for a reduced basis: the smallest tile of 2^8 amplitudes or more that
 // keeps the blocks at 256; the count padded to a multiple of 8 for the XCDs.
 // Timed calls (m = 10, complex64, us) as three launches a step and in this form: dim
-// 1716 149 -> 79, 24,310 160 -> 87, 92,504 171 -> 113, 176,484 196 -> 171 (complex128 219
-// -> 175); at 352,716 the three launches are ahead (260 against 277).  Up to 2^18 orbits
+// 1716 149 -> 78, 24,310 160 -> 86, 92,504 171 -> 112, 176,484 196 -> 169 (complex128 219
+// -> 174); at 352,716 the three launches are ahead (260 against 277).  Up to 2^18 orbits
 // a tile is at most 2^10, two amplitudes a thread.
 Geo make_geo_step_pe(int L, uint64_t dim) {
   Geo g;

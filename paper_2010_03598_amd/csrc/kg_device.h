@@ -10,6 +10,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "kg_internal.h"
 
@@ -671,19 +672,30 @@ __device__ __forceinline__ void next_far(uint32_t& glb, R hJ, uint32_t& flip, R&
   }
 }
 
-// y = (H0 + u Hc) x on one tile (amplitudes base .. base + 2^TB - 1).  The
-// tile's amplitudes, the S^x partners and the first far partners are requested
-// in one round trip before anything waits (partners outside the tile with
-// coherent loads when kCoh: other workgroups of the launch wrote them).
+// An amplitude of the vector that H v is applied to: from memory, or from a function
+// of the index.
+template <bool kCoh, typename V>
+__device__ __forceinline__ V hv_amp(const V* x, uint32_t s) {
+  return ld_partner<kCoh>(&x[s]);
+}
+template <bool kCoh, typename F>
+__device__ __forceinline__ auto hv_amp(const F& x, uint32_t s) -> decltype(x(s)) {
+  return x(s);
+}
+
 struct NoWork {
   __device__ __forceinline__ void operator()() const {}
 };
 
-template <typename R, int RB, bool kCoh = false, int kFar = FarSlots<R, RB>::n, typename Before = NoWork>
-__device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const Geo& g,
-                                        uint32_t tile, const typename VT<R>::T* __restrict__ x,
-                                        typename VT<R>::T* lds, double u,
-                                        Before before = Before()) {
+// y = (H0 + u Hc) x on one tile (amplitudes base .. base + 2^TB - 1).  The
+// tile's amplitudes, the S^x partners and the first far partners are requested
+// in one round trip before anything waits (partners outside the tile with
+// coherent loads when kCoh: other workgroups of the launch wrote them).  X: a
+// pointer, or a function of the index (whole tiles only).
+template <typename R, int RB, bool kCoh, int kFar, typename X, typename Before>
+__device__ __forceinline__ void hv_tile_of(Tile<R, RB>& T, const HvArgs& a, const Geo& g,
+                                           uint32_t tile, X x, typename VT<R>::T* lds, double u,
+                                           Before before) {
   using V = typename VT<R>::T;
   constexpr int NR = 1 << RB;
   constexpr int NS = kFar < FarSlots<R, RB>::n ? kFar : FarSlots<R, RB>::n;
@@ -709,7 +721,12 @@ __device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const G
 
   // ---- round trip 1: own amplitudes, S^x partners, first far partners
   V own[NR];
-  load_slots<V, NR>(x, base | eb, !g.small, g.D, own);
+  if constexpr (std::is_pointer<X>::value) {
+    load_slots<V, NR>(x, base | eb, !g.small, g.D, own);
+  } else {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) own[r] = x(base | eb | ((uint32_t)r << 6));
+  }
   uint32_t f[NS];
   R cf[NS];
 #pragma unroll
@@ -726,7 +743,7 @@ __device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const G
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
 #pragma unroll
-      for (int r = 0; r < NR; ++r) gq[j][r] = ld_partner<kCoh>(&x[(base | eb | ((uint32_t)r << 6)) ^ f[j]]);
+      for (int r = 0; r < NR; ++r) gq[j][r] = hv_amp<kCoh>(x, (base | eb | ((uint32_t)r << 6)) ^ f[j]);
     }
   }
 
@@ -773,7 +790,7 @@ __device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const G
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       const uint32_t e = eb | ((uint32_t)r << 6);
-      q[r] = (6 < TB) ? lds[e ^ flip] : ld_partner<kCoh>(&x[(base | e) ^ flip]);
+      q[r] = (6 < TB) ? lds[e ^ flip] : hv_amp<kCoh>(x, (base | e) ^ flip);
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
@@ -817,7 +834,7 @@ __device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const G
         for (int j = 0; j < NH; ++j) {
           const int r = j | (half << (RB - 1));
           const uint32_t e = eb | ((uint32_t)r << 6);
-          q[j] = in_lds ? lds[e ^ flip] : ld_partner<kCoh>(&x[(base | e) ^ flip]);
+          q[j] = in_lds ? lds[e ^ flip] : hv_amp<kCoh>(x, (base | e) ^ flip);
         }
 #pragma unroll
         for (int j = 0; j < NH; ++j) {
@@ -864,7 +881,7 @@ __device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const G
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
 #pragma unroll
-        for (int r = 0; r < NR; ++r) gq[j][r] = ld_partner<kCoh>(&x[(base | eb | ((uint32_t)r << 6)) ^ f[j]]);
+        for (int r = 0; r < NR; ++r) gq[j][r] = hv_amp<kCoh>(x, (base | eb | ((uint32_t)r << 6)) ^ f[j]);
       }
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
@@ -890,6 +907,14 @@ __device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const G
     }
   }
 
+}
+
+template <typename R, int RB, bool kCoh = false, int kFar = FarSlots<R, RB>::n, typename Before = NoWork>
+__device__ __forceinline__ void hv_tile(Tile<R, RB>& T, const HvArgs& a, const Geo& g,
+                                        uint32_t tile, const typename VT<R>::T* __restrict__ x,
+                                        typename VT<R>::T* lds, double u,
+                                        Before before = Before()) {
+  hv_tile_of<R, RB, kCoh, kFar>(T, a, g, tile, x, lds, u, before);
 }
 
 // y = (H0 + u Hc) x on one full tile of complex64 amplitudes held in pairs, so

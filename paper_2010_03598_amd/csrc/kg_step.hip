@@ -23,12 +23,13 @@
 // u_{k-1} and u_{k-2}, which nobody writes meanwhile.  L=12, m=30, S^z field of 100,
 // complex64: error 6.5e-8; without it 2.3e-4, two passes 1.8e-7.
 //
-// A launch is about 6.4 us at L = 13 (two passes: 14.4): the gap between launches, a
-// chain of two trips to memory, the scalars (0.8) and the block's sums; lo and the
-// path that forms y cost 0.5 of it (where that path is taken, a launch takes 7.3 us in
-// complex128 and 9.3 in complex64).  Calls at m = 16, complex64, two passes and this
-// form: L=13 231 -> 109 us, L=15 232 -> 124, L=16 234 -> 144, L=17 239 -> 167, L=18 265
-// -> 221; complex128 L=16 239 -> 149, L=18 322 -> 254.
+// A launch is about 6.0 us at L = 13 (two passes: 14.4): the gap between launches, a
+// chain of two trips to memory, the scalars (0.8) and the block's sums.  One that forms y
+// takes 8 to 9.  Calls at m = 16, complex64, two passes, this form, and this form with y
+// formed in every step: L=13 231, 103, 148 us; L=15 232, 118, 166; L=16 234, 138, 192;
+// L=17 239, 164, 221; L=18 265, 219, 357; complex128 L=13 230, 102, 133; L=16 239, 145,
+// 174; L=18 322, 256, 388.  Strong fields and product states form it in a third of the
+// steps.
 
 #include <hip/hip_runtime.h>
 
@@ -196,7 +197,7 @@ struct RowGather {
 
 // The extra wavefront: the previous step's totals, the coefficients for the
 // others, and (in block 0) the scalars for the next launch.
-template <typename R, bool FIRST>
+template <typename R, bool FIRST, bool PE>
 __device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl, uint32_t G, uint32_t NW,
                                                  cplx_d* part, cplx_d* tot, cplx_d* cf, StepNext* nxs,
                                                  int* gos) {
@@ -272,7 +273,10 @@ __device__ __forceinline__ void step_scalar_wave(const StepArgs& a, uint32_t bl,
       }
     }
   }
-  if (go) __syncthreads();
+  if (go) {
+    if (!PE && nx.fresh != 0.0) __syncthreads();   // the fresh tile's
+    __syncthreads();
+  }
 }
 
 __device__ __forceinline__ void hold_pe_args(const PeArgs& p) {
@@ -307,34 +311,6 @@ __device__ __forceinline__ V next_u(const StepNext& nx, V x, V lo, V p, V p2) {
   return V{(R)ar, (R)ai};
 }
 
-// Row s of (H0 + u Hc) x on the full space, x given by amplitude; four bonds in flight.
-// Returns x at s.
-template <typename R, typename XAt>
-__device__ __forceinline__ typename VT<R>::T row_at(const HvArgs& a, double u, uint32_t s, XAt xat, R& yr, R& yi) {
-  using V = typename VT<R>::T;
-  const int L = a.L;
-  const uint32_t act = (s ^ (s >> 1)) & ((1u << (L - 1)) - 1u);
-  const R hJ = (R)a.half_J;
-  R d = (R)a.c_zz * (R)(L - 1 - 2 * (int)__popc(act));
-  if (a.hc_kind == 1) d += (R)u * ((R)(0.5 * a.sz_count) - (R)__popc(s & a.sz_mask));
-  const V x = xat(s), f = xat(a.hc_kind == 0 ? s ^ (1u << a.hc_bit) : s);
-  const R cu = a.hc_kind == 0 ? (R)(0.5 * u) : (R)0;
-  yr = d * x.x + cu * f.x;
-  yi = d * x.y + cu * f.y;
-  for (int p0 = 0; p0 < L - 1; p0 += 4) {
-    V q[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) q[e] = xat(((act >> (p0 + e)) & 1u) ? s ^ (3u << (p0 + e)) : s);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const R c = ((act >> (p0 + e)) & 1u) ? hJ : (R)0;
-      yr += c * q[e].x;
-      yi += c * q[e].y;
-    }
-  }
-  return x;
-}
-
 // RAG: the last tile reaches past the vector.  FIRST: step 0.  PE: the reduced
 // basis, H v gathered through its neighbour table (a wavefront's unit of 64
 // rows is a slice of the table).  One tile per block.
@@ -367,7 +343,7 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
   double* meas = reinterpret_cast<double*>(stage + NW * 256u);
   cplx_d* part = reinterpret_cast<cplx_d*>(meas + NW * nv);
   if (wv == NW) {
-    step_scalar_wave<R, FIRST>(a, bl, G, NW, part, tot, cf, &nxs, &gos);
+    step_scalar_wave<R, FIRST, PE>(a, bl, G, NW, part, tot, cf, &nxs, &gos);
     return;
   }
   const int ip = window_first(FIRST ? 0 : k - 1, m, a.reorth);
@@ -447,9 +423,9 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
     const auto u_at = [&](uint32_t i) {
       return next_u<V>(nx, src[i], (kLo && k >= 2) ? lo_in[i] : V{(R)0, (R)0}, pu[i], pu2[i]);
     };
+    if constexpr (PE) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if constexpr (PE) {
+      for (int r = 0; r < NR; ++r) {
         const uint32_t sl = min((sw >> 6) + r, ((D + 63u) >> 6) - 1u), b = min((sl << 6) | lane, D - 1u);
         bool bad;
         pe_row_nbr<R>(a.hv, a.pe, u, sl, b, lane, u_at, T.yr[r], T.yi[r], bad);
@@ -457,12 +433,10 @@ __device__ __forceinline__ void step_body(const StepArgs a, uint32_t bl, uint32_
         const V x = u_at(b);
         T.xr[r] = x.x;
         T.xi[r] = x.y;
-      } else {
-        const uint32_t s = sw | ((uint32_t)r << 6) | lane;
-        const V x = row_at<R>(a.hv, u, RAG ? min(s, D - 1u) : s, u_at, T.yr[r], T.yi[r]);
-        T.xr[r] = x.x;
-        T.xi[r] = x.y;
       }
+    } else {
+      // the tile in LDS has served its turn; the scalar wavefront joins the barrier
+      hv_tile_of<R, RB, false, kStepFar>(T, a.hv, g, tile, u_at, lds, u, NoWork());
     }
   }
 #pragma unroll
