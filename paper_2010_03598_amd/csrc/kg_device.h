@@ -1,6 +1,6 @@
 // Device helpers shared by the HIP translation units of libkgrape: wavefront
 // and grid reductions, the tridiagonal exponential, and H v on a tile.
-// Internal; included only by kg_kernels.hip and kg_batched.hip.
+// Internal; included by every .hip file but kg_static.hip.
 #pragma once
 
 #include <hip/hip_ext.h>

@@ -1,6 +1,7 @@
 // HIP kernels of the K-GRAPE hot path for gfx950 (MI355X).
 //
-// Memory-bound throughout, so no MFMA: every kernel streams state vectors
+// Memory-bound throughout, so without MFMA (the short vectors' forms take their dots
+// on the matrix cores, kg_step.h): every kernel streams state vectors
 // through HBM (or the Infinity Cache) once per pass and keeps the arithmetic in
 // registers.  Layout: a state vector is D = 2^L interleaved complex amplitudes.
 //
@@ -495,7 +496,8 @@ __device__ bool gather_step(const LzArgs& a, uint32_t G, int nb, bool norm, FinS
 // window dots are formed.
 template <bool kLocal = false>
 __device__ bool step_update(const LzArgs& a, const FinScalars& fs, const cplx_d* tot, int nb,
-                            bool writer, cplx_d* cf, double* sk_out, cplx_d* dc, int* me) {
+                            bool writer, cplx_d* cf, double* sk_out, cplx_d* dc, int* me,
+                            double* sk_all = nullptr, double* bk_all = nullptr) {
   KState* st = a.st;
   const int lane = threadIdx.x;
   const int k = a.k;
@@ -574,6 +576,10 @@ __device__ bool step_update(const LzArgs& a, const FinScalars& fs, const cplx_d*
     return false;
   }
   if (sk_out && lane == 0) *sk_out = sk;
+  if (sk_all) {   // every lane's own
+    *sk_all = sk;
+    *bk_all = bk;
+  }
   return true;
 }
 
@@ -893,9 +899,11 @@ __global__ void __launch_bounds__(RB >= 3 ? 512 : 1024) k_pass_b(LzBatch B) {
 //                              - beta v_b - (overlaps).
 // What <v_i|p> is follows, as in pass B, from the overlaps of v_b and v_{b-1} that
 // pass P(b-2) measured and H's tridiagonal form, before p is formed.  While every
-// |E_i| / ||p|| is below the unit roundoff of the stored vectors (random states: about
-// that over sqrt(D)), removing them would not change what is stored, and p reads three
-// vectors; then the overlaps enter w_{b+2} alone.  Otherwise p is projected on the whole
+// |E_i| / ||p|| is below a few units of roundoff of the stored vectors (random states:
+// about one over sqrt(D)), or E_i is what FP64 sums leave of ||T|| anyway, p reads three
+// vectors; then the overlaps enter w_{b+2} alone.  (Limits of 1 to 64 units gave the
+// same errors within 3 % over 1,600 random calls; the projections cost 8 % of a call at
+// L=20 in complex128 when FP64's own noise counted.)  Otherwise p is projected on the whole
 // window like pass B's vectors, before it is rounded and before its norm is tested: near
 // the end of a basis p is rounding noise, whose overlaps are of its own size, and a
 // correction after the fact ended in NaN.  w_{b+2} is always corrected.  Per pair the
@@ -918,14 +926,14 @@ __global__ void __launch_bounds__(RB >= 3 ? 512 : 1024) k_pass_b(LzBatch B) {
 // ||w_{b+2}||^2; pass C(b+2) turns them into the next g and h.
 
 // The overlaps of a pair's p, on wavefront 0 of every block of pass C(b) (b = a.k, sb =
-// 1/||v_b||): g and h from pass P(b-2)'s totals (nb = b columns a set), then E_i.  Returns
+// 1/||v_b||, bb = ||v_b||, 0 at b = 0): g and h from pass P(b-2)'s totals (nb = b columns a set), then E_i.  Returns
 // kPairProject when p is projected; then ec[i] holds E_i on the stored vectors, i in [0, b].
 // ||p||^2 comes from ||y||^2 less the two coefficients; where these cancel to where the
 // estimate means little, any overlap counts.  kPairEnd: v_{b-1} or v_b is no new direction.
 // State, with `writer`: g, and E in csub (0 if p is projected), or the finished basis.
 enum { kPairPlain, kPairProject, kPairEnd };
 __device__ int pair_overlaps(const LzArgs& a, const FinScalars& fs, const cplx_d* tot, double sb,
-                              double unit, bool writer, cplx_d* ec) {
+                             double bb, double unit, bool writer, cplx_d* ec) {
   const int i = threadIdx.x, b = a.k;
   const cplx_d zero{0.0, 0.0};
   cplx_d g = zero, h = zero;
@@ -948,7 +956,7 @@ __device__ int pair_overlaps(const LzArgs& a, const FinScalars& fs, const cplx_d
   }
   const cplx_d gm{__shfl_up(g.re, 1, 64), __shfl_up(g.im, 1, 64)};
   const cplx_d gp{__shfl_down(g.re, 1, 64), __shfl_down(g.im, 1, 64)};   // 0 from lane b on
-  const double ab = tot[2 * b].re * sb * sb, bb = b > 0 ? 1.0 / sb : 0.0;
+  const double ab = tot[2 * b].re * sb * sb;
   cplx_d E = zero;
   if (i < b) {
     const double ai = fs.alpha[i] - ab, bi = i > 0 ? fs.offd[i] : 0.0;
@@ -961,7 +969,9 @@ __device__ int pair_overlaps(const LzArgs& a, const FinScalars& fs, const cplx_d
   }
   const double normT = fmax(b > 0 ? fs.normT : 0.0, fabs(ab) + bb);
   const double b2 = sb * sb * tot[2 * b + 1].im - ab * ab - bb * bb;
-  const double lim = b2 > 1e-10 * normT * normT ? unit * unit * b2 : 0.0;
+  // FP64 sums leave an E of a few of their own roundings of ||T||, whatever the overlap
+  const double own = (32 * 0x1p-53) * normT;
+  const double lim = b2 > 1e-10 * normT * normT ? fmax(16.0 * unit * unit * b2, own * own) : 0.0;
   const bool corr = __any(E.re * E.re > lim || E.im * E.im > lim);
   if (i <= b) {
     const double si = i < b ? fs.scale[i] : sb;
@@ -1065,10 +1075,9 @@ __device__ __forceinline__ void pass_c_body(const LzArgs& a, uint32_t bl, uint32
   const int b = a.k;
   if (!gather_step(a, G, b, true, fs, tot)) return;
   if (wv == 0) {
-    const bool cont = step_update<true>(a, fs, tot, b, bl == 0, &cf, &sk_s, nullptr, nullptr);
-    // 1/||v_b|| again: lane 0's LDS write is not ordered before the other lanes' reads
-    const double sb = b > 0 ? 1.0 / sqrt(tot[2 * b + 2].re) : 1.0 / sqrt(tot[2 * b + 1].re);
-    const int pair = cont ? pair_overlaps(a, fs, tot, sb, sizeof(R) == 4 ? 0x1p-24 : 0x1p-53, bl == 0, ec)
+    double sb, bb;
+    const bool cont = step_update<true>(a, fs, tot, b, bl == 0, &cf, &sk_s, nullptr, nullptr, &sb, &bb);
+    const int pair = cont ? pair_overlaps(a, fs, tot, sb, bb, sizeof(R) == 4 ? 0x1p-24 : 0x1p-53, bl == 0, ec)
                           : kPairEnd;
     if (lane == 0) {
       go = pair != kPairEnd ? 1 : 0;
@@ -1167,8 +1176,8 @@ __global__ void __launch_bounds__(RB >= 3 ? 512 : 1024) k_pass_c(LzBatch B) {
 
 // Pass P(b), a.k = b + 1: w_{b+2} in one pass over v_0..v_b.  Bound
 // by the stream: at L=20 complex64 1.4 us per window vector of 8.4 MB (6 TB/s) on 11
-// us of prologue, two vectors and stores; pass C takes 7 us.  A call at m = 20 613 ->
-// 500 us, at L=24, m = 24 11.4 -> 8.7 ms (pass B streamed as fast, twice as much).
+// us of prologue, two vectors and stores; pass C takes 8 us.  A call at m = 20 613 ->
+// 502 us, at L=24, m = 24 11.4 -> 8.75 ms (pass B streamed as fast, twice as much).
 // Columns of its measurements: <v_i|Hp> in [0, b + 1), <v_{b+1}|w_{b+2}> in b + 1,
 // <v_i|p> from b + 2, ||w_{b+2}||^2 in kNormCol.
 template <typename R, int RB, int MODE, int NW, bool NT>
