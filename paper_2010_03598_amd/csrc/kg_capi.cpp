@@ -440,13 +440,13 @@ const SideStream* side_stream(hipStream_t caller) {
 // the first half each sweep fills its own end of the state buffer; in the
 // second each meets what the other stored: psi_j is formed beside lambda_j (in the
 // Krylov slot's vector H v, which no combination reads), the bracket is taken and psi_j
-// replaces lambda_j, and lambda_j meets psi_j.  One sweep's launches leave the chip mostly waiting for small
-// vectors, and its launch tails uncovered for large ones.  Timed store-all
-// gradients (60 slices, m = 16), one sweep after the other against side by
-// side: L=11 complex64 11.4 -> 6.1 ms and L=15 14.2 -> 7.7 in the same
-// launches; on two streams L=16 16.6 -> 10.1 (complex128 17.5 -> 12.9, in the
-// same launches 14.5), L=18 12.5 -> 10.6 (30 slices), L=20 17.7 -> 14.3 (20),
-// L=22 23.9 -> 21.9 (8); hence shared launches up to 2^15.
+// replaces lambda_j, and lambda_j meets psi_j.  One sweep's launches leave the
+// chip mostly waiting for small vectors, and its launch tails uncovered for
+// large ones.  Timed store-all gradients (60 slices, m = 16), one sweep after
+// the other against side by side: L=11 complex64 11.4 -> 5.8 ms and L=15 14.3
+// -> 7.7 in the same launches; on two streams L=16 16.7 -> 10.6 (complex128
+// 17.5 -> 12.9, in the same launches 14.5), L=18 13.1 -> 11.3 (30 slices), L=20
+// 15.2 -> 12.2 (20), L=22 19.7 -> 17.6 (8); hence shared launches up to 2^15.
 // Raw brackets go to raw[0, N) (raw[N]: the one at the start of slice 1).
 // `side` nullptr: both sweeps in the same launches.
 kg_status paired_sweeps(const SweepArgs& a, const States& S, const SideStream* side, bool centred,

@@ -1,8 +1,8 @@
 // HIP kernels of the K-GRAPE hot path for gfx950 (MI355X).
 //
-// Memory-bound throughout, so without MFMA (the short vectors' forms take their dots
-// on the matrix cores, kg_step.h): every kernel streams state vectors
-// through HBM (or the Infinity Cache) once per pass and keeps the arithmetic in
+// Memory-bound throughout, so without MFMA (only the forms of short vectors take
+// their dots on the matrix cores, kg_step.h): every kernel streams state
+// vectors through HBM (or the Infinity Cache) once per pass and keeps the arithmetic in
 // registers.  Layout: a state vector is D = 2^L interleaved complex amplitudes.
 //
 // H v (Sec. III.A, Eqs. 6 and 10).  A block stages a tile of 2^TB consecutive
@@ -1857,8 +1857,8 @@ hipError_t launch_krylov_t(const KrylovCall* calls, const Workspace* const* wss,
   // windows: all stored vectors (full re-orthogonalisation) or the last two;
   // the last step only forms alpha
   int i0p = 0;
-  // full windows two steps at a time; an even m leaves the first step by itself
-  // (against a pass B per step, both timed, m = 4 / 8 / 24: complex64 L=20 81 -> 80,
+  // full windows two steps at a time, whatever m; an even m leaves the first step by
+  // itself (against a pass B per step, both timed, m = 4 / 8 / 24: complex64 L=20 81 -> 80,
   // 184 -> 169, 783 -> 619 us; complex128 L=22 442 -> 438, 1125 -> 1068, 5361 -> 4210)
   const bool paired = c0.reorth != 0;
   const int first = (c0.m - 1) & 1;
