@@ -300,8 +300,8 @@ __global__ void __launch_bounds__(TH) k_sweep(SweepBatch Bt) {
         beta0 = NAN;
         break;
       }
-      const double sk = rsqrt(gkk);
-      const double nrm = gkk > 0.0 ? gkk * sk : gkk;   // u_k = 0 is a breakdown
+      double nrm, sk;                                  // u_k = 0 is a breakdown
+      norm_and_inverse(gkk, nrm, sk);
       const double off = k > 0 ? nrm : 0.0;
       if (k == 0) beta0 = nrm;
       // ||u_k|| small against ||T||: an invariant Krylov space of dimension k
